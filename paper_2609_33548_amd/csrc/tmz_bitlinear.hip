@@ -406,13 +406,29 @@ constexpr int kDmaBM = 256, kDmaBN = 256;
 template <int BK, int NST>
 constexpr int dma_lds_bytes(int BM, int BN) { return NST * (BM * BK + BN * BK / 4); }
 
-template <int BM, int BN, int WM, int WN, typename TY, int MODE, int BK, int NST>
+// Sixteen zero bytes: the direct loads' source for activations past the end of K.
+__device__ const v4u kZero16 = {0u, 0u, 0u, 0u};
+
+// How much of a tile the shape guarantees.
+//   kFullTile  every row, column and K step whole (the requirements above);
+//   kEdgeTile  any M and N, whole K steps: buffer loads whose descriptors end with the
+//              matrices (rows past the end fetch nothing), and the outputs of rows and
+//              columns past the end are not stored;
+//   kOddTile   any M and N and K % 16 == 0: rows and columns past the end read the last
+//              one, activations past K read zeros (so the codes there do not matter), and
+//              the codes, whose rows are only 4-byte aligned, come in 4-byte direct loads,
+//              four times as many for the same bytes.
+constexpr int kFullTile = 0, kEdgeTile = 1, kOddTile = 2;
+
+template <int BM, int BN, int WM, int WN, typename TY, int MODE, int BK, int NST, int EDGE = kFullTile>
 __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
-                                              const uint32_t* __restrict__ codes, int64_t K,
+                                              const uint32_t* __restrict__ codes, int64_t M,
+                                              int64_t K,
                                               int64_t N, const GemmOut& out, int32_t* acc_out,
                                               int64_t m0, int64_t n0, int8_t* lds,
                                               const float* __restrict__ s,
                                               const int32_t* __restrict__ rs) {
+  constexpr bool FULL = EDGE == kFullTile;
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int AROW = BK;                        // bytes per A row per stage (no pad)
   constexpr int BROW = BK / 4;                    // bytes of packed codes per B row per stage
@@ -423,44 +439,64 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
   constexpr int HK = KS / 4;                      // 16-byte code reads per lane per fragment
   constexpr int NW = (BM / WM) * (BN / WN);       // waves per block
   constexpr int ARPI = 1024 / AROW;               // A rows per 1 KB load instruction
-  constexpr int BRPI = 1024 / BROW;               // B rows per 1 KB load instruction
+  constexpr int BLB = EDGE == kOddTile ? 4 : 16; // bytes per lane of a code load
+  constexpr int BRPI = 64 * BLB / BROW;           // B rows per load instruction
   constexpr int AJ = BM / (ARPI * NW);            // A loads per wave per stage
   constexpr int BW = BN / BRPI < NW ? BN / BRPI : NW;      // waves holding distinct B rows
   constexpr int BJ = BN / BRPI > NW ? BN / (BRPI * NW) : 1;  // B loads per wave per stage
   constexpr int DJ = AJ + BJ;                     // direct loads per wave per stage
   static_assert(AJ >= 1 && BM % (ARPI * NW) == 0 && (BN / BRPI <= NW || BN % (BRPI * NW) == 0) &&
-                    DJ * (NST - 1) < 64 && (BK == 128 || BK == 256), "tile");
+                    DJ * (NST - 2) < 64 && (BK == 128 || BK == 256), "tile");
   const int tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int wm = wid / (BN / WN), wn = wid % (BN / WN);
   const int64_t KW = K / 16;
-  const int nk = (int)(K / BK);
+  const int nk = EDGE == kOddTile ? (int)((K + BK - 1) / BK) : (int)(K / BK);
+  // kEdgeTile: the tile's activation rows and all the codes, as buffers (32-bit offsets:
+  // a layer's codes take at most 2^23 bytes and three layers share a launch at most)
+  const v4i arsrc = buffer_of(xq + m0 * K, (uint32_t)(min((int64_t)BM, M - m0) * K));
+  const v4i brsrc = buffer_of(codes, (uint32_t)(N * KW * 4));
 
   // Per-lane global sources.  A: wave w fills 1 KB chunks AJ w .. AJ w + AJ-1
   // (ARPI rows each); lane i -> row ARPI j + i / ACH, physical chunk i % ACH.
   // B: wave w fills the BRPI-row blocks BJ (w % BW) .. + BJ-1, BU lanes
   // (physical units) per row (with BW < NW several waves write the same bytes).
   const int8_t* asrc[AJ];
+  uint32_t aoff[AJ];                              // kEdgeTile: byte offsets in arsrc
+  int achunk[AJ];                                 // K offset of the lane's chunk in a stage
 #pragma unroll
   for (int j = 0; j < AJ; ++j) {
     const int row = ARPI * (AJ * wid + j) + lane / ACH;
     const int chunk = (lane % ACH) ^ aswz<BK>(row);
-    asrc[j] = xq + (m0 + row) * K + 16 * chunk;
+    const int64_t m = FULL ? m0 + row : min(m0 + row, M - 1);
+    achunk[j] = 16 * chunk;
+    asrc[j] = xq + m * K + 16 * chunk;
+    aoff[j] = (uint32_t)(row * K) + 16 * chunk;
   }
   const int bw = wid % BW;
+  constexpr int BLR = BROW / BLB;                 // lanes per B row of a load
   const uint32_t* bsrc[BJ];
+  uint32_t boff[BJ];                              // kEdgeTile: byte offsets in brsrc
+  int bword[BJ];                                  // word of the lane's load in a stage row
 #pragma unroll
   for (int j = 0; j < BJ; ++j) {
-    const int brow_l = BRPI * (BJ * bw + j) + lane / BU;
+    const int brow_l = BRPI * (BJ * bw + j) + lane / BLR;
     int64_t crow = n0 + brow_l;                   // code row of tile row brow_l
     if constexpr (MODE == kGemmSwiGLU) {
       // column 64 p + c holds gate row 32 p + c (c < 32) or up row F + 32 p + c - 32, so
       // a wave's column blocks b = 0 and 1 hold the gate and the up values of the same
       // 32 features in the same lanes
-      const int64_t p = crow >> 6, c = crow & 63;
-      crow = c < 32 ? 32 * p + c : (N >> 1) + 32 * p + (c - 32);
+      const int64_t p = crow >> 6, c = crow & 63, f = 32 * p + (c & 31);
+      crow = (c < 32 ? 0 : N >> 1) + (EDGE == kOddTile ? min(f, (N >> 1) - 1) : f);
+    } else if constexpr (EDGE == kOddTile) {
+      crow = min(crow, N - 1);
     }
-    bsrc[j] = codes + crow * KW + 4 * ((lane % BU) ^ bswz<BK>(brow_l));
+    if constexpr (BLB == 16)
+      bword[j] = 4 * ((lane % BU) ^ bswz<BK>(brow_l));
+    else
+      bword[j] = 4 * (((lane % BLR) / 4) ^ bswz<BK>(brow_l)) + lane % 4;
+    bsrc[j] = codes + crow * KW + bword[j];
+    boff[j] = (uint32_t)(4 * (crow * KW + bword[j]));
   }
 
   static_assert(MODE != kGemmSwiGLU || WN == 64, "SwiGLU: gate and up blocks of one wave");
@@ -474,11 +510,37 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
   auto issue = [&](int kt, int8_t* Ad, uint32_t* Bd) __attribute__((always_inline)) {
     const int64_t koff = (int64_t)kt * BK;
     const uint32_t abase = lds_offset(Ad) + 1024u * AJ * wa;
+    const uint32_t bbase = lds_offset(Bd) + 64u * BLB * BJ * wb;
+    if constexpr (EDGE == kEdgeTile) {
+#pragma unroll
+      for (int j = 0; j < AJ; ++j) dma16_buf(aoff[j], arsrc, (uint32_t)koff, abase + 1024u * j);
+#pragma unroll
+      for (int j = 0; j < BJ; ++j) dma16_buf(boff[j], brsrc, (uint32_t)koff / 4, bbase + 1024u * j);
+      return;
+    }
+    if (EDGE == kOddTile && koff + BK > K) {                  // the last, partial K step (uniform)
+      const int left = (int)(K - koff);
+#pragma unroll
+      for (int j = 0; j < AJ; ++j)
+        dma16(achunk[j] < left ? (const void*)(asrc[j] + koff) : (const void*)&kZero16,
+              abase + 1024u * j);
+#pragma unroll
+      for (int j = 0; j < BJ; ++j) {
+        // past the end of the row: its first word of this step instead (in bounds)
+        const uint32_t* p = bsrc[j] + koff / 16 - (16 * bword[j] < left ? 0 : bword[j]);
+        dma4(p, bbase + 256u * j);
+      }
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < AJ; ++j) dma16(asrc[j] + koff, abase + 1024u * j);
-    const uint32_t bbase = lds_offset(Bd) + 1024u * BJ * wb;
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) dma16(bsrc[j] + koff / 16, bbase + 1024u * j);
+    for (int j = 0; j < BJ; ++j) {
+      if constexpr (BLB == 16)
+        dma16(bsrc[j] + koff / 16, bbase + 1024u * j);
+      else
+        dma4(bsrc[j] + koff / 16, bbase + 256u * j);
+    }
   };
 
   // Accumulator register r of tile (a, b) is token wm WM + 32 a + 8 (r / 4) + 4 h + r % 4
@@ -489,10 +551,10 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
   v16i acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a) {
-    const int32_t* rp = rs + m0 + wm * WM + 32 * a + 4 * h;
+    const int64_t mr = m0 + wm * WM + 32 * a + 4 * h;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const v4i r4 = *reinterpret_cast<const v4i*>(rp + 8 * q);
+      const v4i r4 = *reinterpret_cast<const v4i*>(rs + mr + 8 * q);   // rs is padded to whole tiles
 #pragma unroll
       for (int b = 0; b < TN; ++b)
 #pragma unroll
@@ -566,7 +628,7 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
 #pragma unroll
   for (int p = 0; p < NST - 1; ++p)
     if (p < nk) issue(p, Ast(p), Bst(p));
-  if (NST == 3 && nk > 1) wait_vmcnt_le<DJ>(); else __builtin_amdgcn_s_waitcnt(0);
+  if (NST > 2 && nk >= NST - 1) wait_vmcnt_le<(NST - 2) * DJ>(); else __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   first(Ast(0), Bst(0));
   int cur = 0;
@@ -579,8 +641,8 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
 #pragma unroll
     for (int b = 0; b < TN; ++b)   // the last sub-step's codes unpacked before the barrier
       asm volatile("" : "+v"(bfc[b]));
-    // the loads of step kt + 1 have landed (NST = 3: those of kt + 2 may still be in flight)
-    if (NST == 3 && kt + 2 < nk) wait_vmcnt_le<DJ>(); else __builtin_amdgcn_s_waitcnt(0);
+    // the loads of step kt + 1 have landed (those of kt + 2 .. kt + NST - 1 may be in flight)
+    if (NST > 2 && kt + NST - 1 < nk) wait_vmcnt_le<(NST - 2) * DJ>(); else __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (kt + 1 < nk) first(Ast(nst), Bst(nst));
     mfmas((KS - 1) & 1);                              // the last sub-step of step kt
@@ -608,7 +670,8 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
 #pragma unroll
   for (int sg = 0; sg < kMaxSeg; ++sg)
     if (sg < out.nseg)
-      for (int t = tid; t < BM; t += NW * 64) fac[sg * BM + t] = __fdiv_rn(bet[sg], s[m0 + t]);
+      for (int t = tid; t < BM; t += NW * 64)
+        fac[sg * BM + t] = __fdiv_rn(bet[sg], s[FULL ? m0 + t : min(m0 + t, M - 1)]);
   __syncthreads();
   // the output scales of the lane's 16 tokens of slice a
   auto load_fac = [&](int a, int sg, float f[16]) __attribute__((always_inline)) {
@@ -644,7 +707,13 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
     }
   };
   const int64_t fbase = MODE == kGemmSwiGLU ? (n0 + wn * WN) / 2 : n0 + wn * WN;
-  // output unit i (of RPL) of slice a of this lane
+  // whether output unit i (of RPL) of slice a of this lane lies in the matrix
+  const int64_t nout = MODE == kGemmSwiGLU ? N >> 1 : N;
+  auto unit_in = [&](int a, int i) __attribute__((always_inline)) {
+    const int c = 64 * i + lane;
+    return FULL || (m0 + wm * WM + 32 * a + c / UPR < M && fbase + (int64_t)(c % UPR) * UB < nout);
+  };
+  // its address
   auto unit_ptr = [&](int a, int i) __attribute__((always_inline)) {
     const int c = 64 * i + lane, row = c / UPR, u = c % UPR;
     const int64_t tok = m0 + wm * WM + 32 * a + row;
@@ -665,13 +734,15 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
-      for (int i = 0; i < RPL; ++i) hin[a][i] = *unit_ptr(a, i);
+      for (int i = 0; i < RPL; ++i)
+        if (unit_in(a, i)) hin[a][i] = *unit_ptr(a, i);
   }
 #pragma unroll
   for (int a = 0; a < TM; ++a) {
     if constexpr (HPRE == 1) {
 #pragma unroll
-      for (int i = 0; i < RPL; ++i) hin[0][i] = *unit_ptr(a, i);
+      for (int i = 0; i < RPL; ++i)
+        if (unit_in(a, i)) hin[0][i] = *unit_ptr(a, i);
     }
     if constexpr (MODE == kGemmSwiGLU) {
       // block 0: gate, block 1: up values of feature fbase + n
@@ -698,8 +769,10 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
         stage16(32 * b + n, v);
         if (acc_out) {   // int32 accumulators (parity only), straight from the registers
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            acc_out[(m0 + wm * WM + 32 * a + 8 * (r >> 2) + 4 * h + (r & 3)) * N + nb + n] = acc[a][b][r];
+          for (int r = 0; r < 16; ++r) {
+            const int64_t m = m0 + wm * WM + 32 * a + 8 * (r >> 2) + 4 * h + (r & 3);
+            if (FULL || (m < M && nb + n < N)) acc_out[m * N + nb + n] = acc[a][b][r];
+          }
         }
       }
     }
@@ -708,6 +781,7 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
     for (int i = 0; i < RPL; ++i) {
       const int c = 64 * i + lane, row = c / UPR, u = c % UPR;
       const v4u v = *reinterpret_cast<const v4u*>(wl + row * RB + 16 * (u ^ (row % UPR)));
+      if (!unit_in(a, i)) continue;
       v4u* p = unit_ptr(a, i);
       if constexpr (MODE == kGemmResidual)   // h <- round(h + y), y already rounded
         *p = add_units(hin[HPRE == TM ? a : 0][i], v, (TY*)nullptr);
@@ -742,10 +816,10 @@ __global__ void __launch_bounds__(512)
   const int64_t m0 = tm * kDmaBM + (quarter ? 128 * (q >> 1) : 0);
   const int64_t n0 = tn * kDmaBN + (quarter ? 128 * (q & 1) : 0);
   if (!quarter)
-    gemm_tile_dma<256, 256, 128, 64, TY, MODE, BK, NST>(xq, codes, K, N, out, acc_out, m0, n0, lds, s,
+    gemm_tile_dma<256, 256, 128, 64, TY, MODE, BK, NST>(xq, codes, M, K, N, out, acc_out, m0, n0, lds, s,
                                                         rs);
   else
-    gemm_tile_dma<128, 128, 64, 32, TY, MODE, BK, NST>(xq, codes, K, N, out, acc_out, m0, n0, lds, s,
+    gemm_tile_dma<128, 128, 64, 32, TY, MODE, BK, NST>(xq, codes, M, K, N, out, acc_out, m0, n0, lds, s,
                                                        rs);
 }
 
@@ -763,8 +837,32 @@ __global__ void __launch_bounds__(256, 2)
   __shared__ __attribute__((aligned(1024))) int8_t lds[dma_lds_bytes<128, 3>(kHalfBM, kHalfBN)];
   int64_t tm, tn;
   tile_of_block(M / kHalfBM, N / kHalfBN, tm, tn);
-  gemm_tile_dma<kHalfBM, kHalfBN, 128, 64, TY, MODE, 128, 3>(xq, codes, K, N, out, acc_out,
+  gemm_tile_dma<kHalfBM, kHalfBN, 128, 64, TY, MODE, 128, 3>(xq, codes, M, K, N, out, acc_out,
                                                              tm * kHalfBM, tn * kHalfBN, lds, s, rs);
+}
+
+// ---------------------------------------------------------------------------
+// The same tile on any M and N, one tile per block, BPC blocks per compute unit.  What
+// bounds these shapes is the serial chain of a tile's K steps and how many compute units
+// have a tile at all: 389 x 2560 -> 2560 as 128 x 128 blocks was 80 blocks of 20 steps
+// staged through registers (26.7 us), as 64 x 64 tiles with direct loads it is 280 blocks
+// (10.8 us); 389 x 6912 -> 2560 53 -> 21 us, 8000 x 2560 -> 6912 227 -> 150 us.  Ragged
+// edges cost nothing inside the loop: the buffer descriptors end with the matrices, and the
+// row sums are padded to whole tiles so that the accumulators start from 16-byte loads
+// (with clamped 4-byte loads the 128 x 256 tile spilled and took 179 us on that shape).
+// ---------------------------------------------------------------------------
+template <int BM, int BN, int WM, int WN, typename TY, int MODE, int BK, int NST, int EDGE, int BPC>
+__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, BPC * (BM / WM) * (BN / WN) / 4)
+    k_gemm_i8_edge(const int8_t* __restrict__ xq, const float* __restrict__ s,
+                   const int32_t* __restrict__ rs, const uint32_t* __restrict__ codes, int64_t M,
+                   int64_t K, int64_t N, GemmOut out, int32_t* __restrict__ acc_out) {
+  __shared__ __attribute__((aligned(1024))) int8_t lds[dma_lds_bytes<BK, NST>(BM, BN)];
+  // SwiGLU: columns in groups of 32 gate and 32 up features, the last one partial
+  const int64_t cols = MODE == kGemmSwiGLU ? 2 * ((N / 2 + 31) / 32 * 32) : N;
+  int64_t tm, tn;
+  tile_of_block((M + BM - 1) / BM, (cols + BN - 1) / BN, tm, tn);
+  gemm_tile_dma<BM, BN, WM, WN, TY, MODE, BK, NST, EDGE>(xq, codes, M, K, N, out, acc_out, tm * BM,
+                                                         tn * BN, lds, s, rs);
 }
 
 // ---------------------------------------------------------------------------
@@ -1340,27 +1438,62 @@ static hipError_t launch_tile(const int8_t* xq, const float* s, const uint32_t* 
   return hipGetLastError();
 }
 
-// Tile choice: the small-M kernel up to kGemvMaxM tokens.  When every tile is in bounds
-// and the outputs allow 4-wide stores, the direct-to-LDS kernels: 128 x 256 tiles, two
-// blocks per compute unit (k_gemm_i8_dma_h), when the 256 x 256 grid is below one round
-// of the n_cu compute units or spans at least three rounds, and always for the SwiGLU
-// gate|up product; otherwise 256 x 256 tiles of 8 waves (128 x 64 per wave, two waves per
-// SIMD) with the last round cut into 128 x 128 quarter tiles when it would fill at most
-// half of the compute units (n_cu = 0: never).  Other shapes: the register-staged
-// kernel, 256 x 256 blocks of 8 waves when the grid fills the chip, 128 x 128 blocks of 4
-// waves otherwise.
-bool gemm_swiglu_ok(int64_t M, int64_t K, int64_t N, termezo_dtype ydt) {
-  return ydt == TERMEZO_BF16 && M % kDmaBM == 0 && N % kDmaBN == 0 && K % kBK == 0 && M > 0 &&
-         K > 0;
+// Tile choice: the small-M kernel up to kGemvMaxM tokens.  Outputs that come in whole
+// 16-byte units take the direct-to-LDS kernels: on whole 256 x 256 tiles that fill the n_cu
+// compute units at least once, 128 x 256 tiles, two blocks per compute unit
+// (k_gemm_i8_dma_h), from three rounds of them and always for the SwiGLU gate|up product,
+// below that 256 x 256 tiles of 8 waves (128 x 64 per wave, two waves per SIMD) with the last
+// round cut into 128 x 128 quarter tiles when it would fill at most half of the compute
+// units; every other shape the edge tiles (k_gemm_i8_edge), which measured 1.1-3x faster
+// below one round (256 x 2560 -> 2560: 21.8 -> 8.4 us; 1024 x 6912 -> 2560: 49 -> 28 us) and
+// level with the whole-tile kernels at one to three rounds.  Other outputs: the
+// register-staged kernel, 256 x 256 blocks of 8 waves when the grid fills the chip,
+// 128 x 128 blocks of 4 waves otherwise.
+// The tiles of k_gemm_i8_edge and what a launch of T of them takes (us): the first tile of a
+// compute unit c0 + l K, each further one a + b K, fitted (rms error 7%) to the nine widths
+// of the decoders at 256 to 8192 tokens.  The tile with the least estimate is taken, which
+// is within 2.5% of the best of the measured tiles on average: the small tile while it is
+// what fills the compute units, the large ones when there are several per compute unit (a
+// 256-column tile moves half the bytes per product).
+struct EdgeTile {
+  int bm, bn;
+  float c0, l, a, b;
+};
+constexpr EdgeTile kEdge64 = {64, 64, 3.53f, 1.67e-3f, 0.72f, 1.16e-3f};
+constexpr EdgeTile kEdge128 = {128, 128, 5.72f, 2.90e-3f, 2.24f, 3.36e-3f};
+constexpr EdgeTile kEdge256 = {128, 256, 8.60f, 5.24e-3f, 3.28f, 6.42e-3f};
+constexpr EdgeTile kEdgeGlu = {64, 128, 5.23f, 2.25e-3f, 1.20f, 2.05e-3f};
+
+static float edge_cost(const EdgeTile& t, int64_t M, int64_t K, int64_t N, int n_cu) {
+  const int64_t T = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  const int64_t cu = n_cu > 0 ? n_cu : 256;
+  return t.c0 + t.l * (float)K + (float)((T + cu - 1) / cu - 1) * (t.a + t.b * (float)K);
+}
+
+// Whole 16-byte output units and 16-byte aligned code rows: what every full or edge tile of
+// the direct-load kernels needs beyond its shape (kOddTile: the outputs only).
+static bool units_ok(const GemmOut& out, termezo_dtype ydt) {
+  const int64_t ue = ydt == TERMEZO_F32 ? 4 : 8;       // outputs per 16-byte unit
+  bool ok = true;
+  for (int i = 0; i < out.nseg; ++i)
+    ok = ok && out.ld[i] % ue == 0 && reinterpret_cast<uintptr_t>(out.y[i]) % 16 == 0 &&
+         (i == 0 || out.nstart[i] % 32 == 0);
+  return ok && out.nstart[out.nseg] % ue == 0;
+}
+
+// kGemmSwiGLU: whole 256-tiles take the direct-load grid of the 2B shape, other token and
+// feature counts its edge tiles.  Up to kGemvMaxM tokens the small-M kernel and a row kernel
+// are taken instead.
+bool gemm_swiglu_ok(int64_t M, int64_t K, int64_t N, termezo_dtype ydt, const uint32_t* codes) {
+  return ydt == TERMEZO_BF16 && M > kGemvMaxM && N % 16 == 0 && K % kBK == 0 && K > 0 &&
+         reinterpret_cast<uintptr_t>(codes) % 16 == 0;
 }
 
 // Two blocks per compute unit (128 x 256 tiles) measured faster than the 256 x 256
-// grid with a quarter-tile tail when the 256 x 256 grid is below one round of compute
-// units (M = 2048: 1.2-1.4x) or spans at least three rounds (gate|up at the 2B shape:
-// 1.04-1.07x), and slower in between (1.25 and 1.9 rounds: 0.9x).
-static bool use_half_tiles(int64_t M, int64_t T, int n_cu) {
-  return n_cu > 0 && M % kHalfBM == 0 && (T < n_cu || T >= 3 * (int64_t)n_cu);
-}
+// grid with a quarter-tile tail when the 256 x 256 grid spans at least three rounds of
+// compute units (gate|up at the 2B shape: 1.04-1.07x), and slower below (1.25 and 1.9
+// rounds: 0.9x).
+static bool use_half_tiles(int64_t T, int n_cu) { return n_cu > 0 && T >= 3 * (int64_t)n_cu; }
 
 // Launch plan of the full-tile path: blocks [0, full) take 256 x 256 tiles, the rest take
 // quarters of the remaining ones.
@@ -1373,18 +1506,64 @@ static int64_t dma_full_tiles(int64_t T, int n_cu) {
   return full;
 }
 
+#define TMZ_EDGE(BM, BN, WM, WN, TY, MD, BK, NS, ED, BPC)                                         \
+  hipExtLaunchKernelGGL((k_gemm_i8_edge<BM, BN, WM, WN, TY, MD, BK, NS, ED, BPC>),                \
+                        dim3((unsigned)(((M + BM - 1) / BM) *                                     \
+                                        (((MD == kGemmSwiGLU ? 2 * ((N / 2 + 31) / 32 * 32) : N) + \
+                                          BN - 1) / BN))),                                        \
+                        dim3((BM / WM) * (BN / WN) * 64), 0, st, ev.start, ev.stop, 0, xq, s, rs, \
+                        codes, M, K, N, out, acc)
+
+// Any M and N (whole output units): the cheapest edge tile, or the odd-K one.
+template <typename TY, int MD>
+static hipError_t launch_edge(const int8_t* xq, const float* s, const int32_t* rs,
+                              const uint32_t* codes, int64_t M, int64_t K, int64_t N,
+                              const GemmOut& out, int32_t* acc, int n_cu, hipStream_t st,
+                              LaunchEvents ev) {
+  if (K % 128 != 0 || reinterpret_cast<uintptr_t>(codes) % 16 != 0) {
+    TMZ_EDGE(64, 64, 32, 32, TY, MD, 256, 2, kOddTile, 4);
+    return hipGetLastError();
+  }
+  const float c64 = edge_cost(kEdge64, M, K, N, n_cu), c128 = edge_cost(kEdge128, M, K, N, n_cu),
+              c256 = edge_cost(kEdge256, M, K, N, n_cu);
+  const bool k256 = K % 256 == 0;                // K steps of 256 where they are whole
+  if (c256 <= c64 && c256 <= c128)
+    TMZ_EDGE(128, 256, 64, 64, TY, MD, 128, 3, kEdgeTile, 2);
+  else if (c128 <= c64) {
+    if (k256)
+      TMZ_EDGE(128, 128, 64, 32, TY, MD, 256, 2, kEdgeTile, 2);
+    else
+      TMZ_EDGE(128, 128, 64, 32, TY, MD, 128, 3, kEdgeTile, 2);
+  } else if (k256)
+    TMZ_EDGE(64, 64, 32, 32, TY, MD, 256, 2, kEdgeTile, 4);
+  else
+    TMZ_EDGE(64, 64, 32, 32, TY, MD, 128, 4, kEdgeTile, 4);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, const uint32_t* codes,
                           int64_t M,
                           int64_t K, int64_t N, const GemmOut& out, termezo_dtype ydt, int mode,
                           int32_t* acc, int n_cu, hipStream_t st, LaunchEvents ev) {
-  // the full-tile paths read the row sums, four tokens per 16-byte load
-  if (M > kGemvMaxM && (!rs || reinterpret_cast<uintptr_t>(rs) % 16 != 0)) return hipErrorInvalidValue;
+  // the direct-load paths read the row sums, four tokens per 16-byte load
+  const bool rs_ok = rs && reinterpret_cast<uintptr_t>(rs) % 16 == 0;
+  if (M > kGemvMaxM && !rs_ok) return hipErrorInvalidValue;
   if (mode == kGemmSwiGLU) {
-    if (!gemm_swiglu_ok(M, K, N, ydt) || out.nseg != 2 || out.nstart[1] * 2 != N || acc ||
+    if (!gemm_swiglu_ok(M, K, N, ydt, codes) || out.nseg != 2 || out.nstart[1] * 2 != N || acc ||
         out.ld[0] % 8 != 0 || reinterpret_cast<uintptr_t>(out.y[0]) % 16 != 0)
       return hipErrorInvalidValue;
-    // always the two-blocks-per-CU tiles: their waves are 64 columns wide, the gate and
-    // the up block of 32 features each
+    // only tiles whose waves are 64 columns wide, the gate and the up block of 32 features
+    // each: the two-blocks-per-CU tiles on whole 256-tiles from one round of them
+    if (M % kDmaBM != 0 || N % kDmaBN != 0 || (M / kDmaBM) * (N / kDmaBN) < n_cu) {
+      const bool k256 = K % 256 == 0;
+      if (edge_cost(kEdge256, M, K, N, n_cu) <= edge_cost(kEdgeGlu, M, K, N, n_cu))
+        TMZ_EDGE(128, 256, 64, 64, uint16_t, kGemmSwiGLU, 128, 3, kEdgeTile, 2);
+      else if (k256)
+        TMZ_EDGE(64, 128, 32, 64, uint16_t, kGemmSwiGLU, 256, 2, kEdgeTile, 3);
+      else
+        TMZ_EDGE(64, 128, 32, 64, uint16_t, kGemmSwiGLU, 128, 3, kEdgeTile, 3);
+      return hipGetLastError();
+    }
     const int64_t T = (M / kHalfBM) * (N / kHalfBN);
     hipExtLaunchKernelGGL((k_gemm_i8_dma_h<uint16_t, kGemmSwiGLU>), dim3((unsigned)T), dim3(256), 0,
                           st, ev.start, ev.stop, 0, xq, s, rs, codes, M, K, N, out, acc);
@@ -1422,32 +1601,36 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
       return hipGetLastError();
     }
   }
-  const int64_t big_blocks = ((M + 255) / 256) * ((N + 255) / 256);
-  bool seg32 = true;
-  for (int i = 1; i < out.nseg; ++i) seg32 = seg32 && out.nstart[i] % 32 == 0;
-  const int64_t ue = ydt == TERMEZO_F32 ? 4 : 8;       // outputs per 16-byte unit
-  for (int i = 0; i < out.nseg; ++i)
-    seg32 = seg32 && out.ld[i] % ue == 0 && reinterpret_cast<uintptr_t>(out.y[i]) % 16 == 0;
-  const bool dma = M % 256 == 0 && N % 256 == 0 && K % kBK == 0 && seg32;
-  if (big_blocks >= 256 || (dma && n_cu > 0)) {
-    if (dma) {
-      const int64_t T = big_blocks;
-      if (use_half_tiles(M, T, n_cu)) {
-        dim3 gh((unsigned)(2 * T));
+  const int64_t T = ((M + 255) / 256) * ((N + 255) / 256);
+  if (!units_ok(out, ydt) || !rs_ok) {                     // single outputs: the register-staged kernel
+    if (T >= 256)
+      return launch_tile<256, 256, 128, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
+    return launch_tile<128, 128, 64, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
+  }
+  const bool whole = M % 256 == 0 && N % 256 == 0 && K % kBK == 0 &&
+                     reinterpret_cast<uintptr_t>(codes) % 16 == 0;
+  if (!whole || T < n_cu) {
+#define TMZ_ANY(TY, MD) launch_edge<TY, MD>(xq, s, rs, codes, M, K, N, out, acc, n_cu, st, ev)
+    if (ydt == TERMEZO_F32)
+      return mode == kGemmStore ? TMZ_ANY(float, kGemmStore) : TMZ_ANY(float, kGemmResidual);
+    return mode == kGemmStore ? TMZ_ANY(uint16_t, kGemmStore) : TMZ_ANY(uint16_t, kGemmResidual);
+#undef TMZ_ANY
+  }
+  if (use_half_tiles(T, n_cu)) {
+    dim3 gh((unsigned)(2 * T));
 #define TMZ_HALF(TY, MD) \
   hipExtLaunchKernelGGL((k_gemm_i8_dma_h<TY, MD>), gh, dim3(256), 0, st, ev.start, ev.stop, 0, xq, s, rs, \
                         codes, M, K, N, out, acc)
-        if (ydt == TERMEZO_F32) {
-          if (mode == kGemmStore) TMZ_HALF(float, kGemmStore); else TMZ_HALF(float, kGemmResidual);
-        } else {
-          if (mode == kGemmStore) TMZ_HALF(uint16_t, kGemmStore); else TMZ_HALF(uint16_t, kGemmResidual);
-        }
+    if (ydt == TERMEZO_F32) {
+      if (mode == kGemmStore) TMZ_HALF(float, kGemmStore); else TMZ_HALF(float, kGemmResidual);
+    } else {
+      if (mode == kGemmStore) TMZ_HALF(uint16_t, kGemmStore); else TMZ_HALF(uint16_t, kGemmResidual);
+    }
 #undef TMZ_HALF
-        return hipGetLastError();
-      }
-      // fewer full tiles than compute units: every tile as four 128 x 128 quarters
-      const int64_t full = T < n_cu ? 0 : dma_full_tiles(T, n_cu);
-      dim3 grid((unsigned)(full + 4 * (T - full)));
+    return hipGetLastError();
+  }
+  const int64_t full = dma_full_tiles(T, n_cu);
+  dim3 grid((unsigned)(full + 4 * (T - full)));
 #define TMZ_DMA(TY, MD, BK) \
   hipExtLaunchKernelGGL((k_gemm_i8_dma<TY, MD, BK>), grid, dim3(512), 0, st, ev.start, ev.stop, 0, xq, s, \
                         rs, codes, M, K, N, out, full, acc)
@@ -1455,18 +1638,14 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
   do {                                                 \
     if (K % 256 == 0) TMZ_DMA(TY, MD, 256); else TMZ_DMA(TY, MD, 128); \
   } while (0)
-      if (ydt == TERMEZO_F32) {
-        if (mode == kGemmStore) TMZ_DMA_K(float, kGemmStore); else TMZ_DMA_K(float, kGemmResidual);
-      } else {
-        if (mode == kGemmStore) TMZ_DMA_K(uint16_t, kGemmStore); else TMZ_DMA_K(uint16_t, kGemmResidual);
-      }
+  if (ydt == TERMEZO_F32) {
+    if (mode == kGemmStore) TMZ_DMA_K(float, kGemmStore); else TMZ_DMA_K(float, kGemmResidual);
+  } else {
+    if (mode == kGemmStore) TMZ_DMA_K(uint16_t, kGemmStore); else TMZ_DMA_K(uint16_t, kGemmResidual);
+  }
 #undef TMZ_DMA_K
 #undef TMZ_DMA
-      return hipGetLastError();
-    }
-    return launch_tile<256, 256, 128, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
-  }
-  return launch_tile<128, 128, 64, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
+  return hipGetLastError();
 }
 
 hipError_t launch_bitlinear_gemm(const int8_t* xq, const float* s, const int32_t* rs,

@@ -282,6 +282,37 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
       : "memory", "m0");
 }
 
+// The same with 4 bytes per lane (lane i of the wave writes lds_base + 4 i).
+__device__ __forceinline__ void dma4(const void* gptr, uint32_t lds_base) {
+  asm volatile(
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %0, off"
+      :
+      : "v"(gptr), "s"(lds_base)
+      : "memory", "m0");
+}
+
+// A raw buffer of `bytes` bytes at p (loads past its end return nothing), and the direct
+// load through it: 16 bytes per lane from p + voff + soff.
+typedef int v4i_rsrc __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4i_rsrc buffer_of(const void* p, uint32_t bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)p;
+  return v4i_rsrc{__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+                  __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xFFFF),
+                  __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+__device__ __forceinline__ void dma16_buf(uint32_t voff, v4i_rsrc rsrc, uint32_t soff,
+                                          uint32_t lds_base) {
+  asm volatile(
+      "s_mov_b32 m0, %3\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %0, %1, %2 offen lds"
+      :
+      : "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_base)
+      : "memory", "m0");
+}
+
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
@@ -289,8 +320,8 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_le() {
   // s_waitcnt vmcnt(N): vmcnt in bits [3:0] and [15:14]; expcnt, lgkmcnt left at their maxima
-  static_assert(N >= 0 && N < 16, "vmcnt");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8));
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
 
 }  // namespace tmz

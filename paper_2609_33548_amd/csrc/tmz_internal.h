@@ -289,7 +289,10 @@ hipError_t launch_mse(const float* y, const float* t, int64_t n, double* acc, fl
 
 // BitLinear.  The quantisers write per token the scale s and the sum of the int8
 // activations rs; the GEMM reads both (rs, 16-byte aligned, for its offset weight
-// encoding; the full-tile paths reject a null or misaligned rs).
+// encoding; the direct-load paths reject a null or misaligned rs and read it up to a whole
+// tile of tokens: it is allocated for rs_entries(M)).
+constexpr int64_t kRsPad = 256;
+inline int64_t rs_entries(int64_t M) { return (M + kRsPad - 1) / kRsPad * kRsPad; }
 hipError_t launch_act_quant(const void* x, termezo_dtype xdt, int64_t M, int64_t K, int8_t* xq,
                             float* s, int32_t* rs, hipStream_t st);
 // Optional timing of one GEMM launch: non-null events take the start and the end of the
@@ -313,8 +316,8 @@ bool gemv_fused_ok(int64_t M, int64_t K, termezo_dtype xdt);
 hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
                              const float* beta_dev, int64_t M, int64_t K, int64_t N, void* y,
                              termezo_dtype ydt, int n_cu, hipStream_t st);
-// Whether kGemmSwiGLU (full-tile path only) supports an M x K x N gate|up pair.
-bool gemm_swiglu_ok(int64_t M, int64_t K, int64_t N, termezo_dtype ydt);
+// Whether kGemmSwiGLU (direct-load paths only) supports an M x K x N gate|up pair.
+bool gemm_swiglu_ok(int64_t M, int64_t K, int64_t N, termezo_dtype ydt, const uint32_t* codes);
 hipError_t launch_bitlinear_gemm(const int8_t* xq, const float* s, const int32_t* rs,
                                  const uint32_t* codes, const float* beta_dev, int64_t M, int64_t K, int64_t N,
                                  void* y, termezo_dtype ydt, int32_t* acc, int n_cu,

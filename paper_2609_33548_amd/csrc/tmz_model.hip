@@ -1740,7 +1740,7 @@ termezo_status model_reserve(termezo_model* m, int64_t M, int S) {
   A(&m->xf, M * c.d_model * es);
   A((void**)&m->xq, M * kmax);
   A((void**)&m->xs, M * 4);
-  A((void**)&m->xrs, M * 4);
+  A((void**)&m->xrs, rs_entries(M) * 4);
   A((void**)&m->pmax, M * nvt * 4);
   A((void**)&m->psum, M * nvt * 4);
   A((void**)&m->lab, M * 4);
@@ -2094,9 +2094,9 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     o2.y[0] = m->g; o2.ld[0] = F; o2.beta[0] = betas + l0 + 4;
     o2.y[1] = m->u; o2.ld[1] = F; o2.beta[1] = betas + l0 + 5;
     o2.nstart[0] = 0; o2.nstart[1] = F; o2.nstart[2] = 2 * F;
-    // gate|up with the SwiGLU in the epilogue where the full-tile path applies (the
+    // gate|up with the SwiGLU in the epilogue where the direct-load path applies (the
     // product lands in g), else the two projections and the SwiGLU row kernel
-    const bool fused = gemm_swiglu_ok(M, d, 2 * F, adt);
+    const bool fused = gemm_swiglu_ok(M, d, 2 * F, adt, codes + Ls[4].code_off);
     chk(launch_gemm_i8(m->xq, m->xs, m->xrs, codes + Ls[4].code_off, M, d, 2 * F, o2, adt,
                        fused ? kGemmSwiGLU : kGemmStore, nullptr, c->n_cu, s,
                        span_kernel(m, 0, 2.0 * M * d * 2 * F)));

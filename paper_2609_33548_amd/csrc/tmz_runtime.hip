@@ -10,12 +10,14 @@
 using namespace tmz;
 
 // Scratch of termezo_bitlinear_forward_noalloc: the int8 activations [M][d_in] of one
-// call, then (at the next 256-byte boundary) its per-token scales [M].  Each device
+// call, then (each at the next 256-byte boundary) its per-token scales [M] and row sums [M];
+// the GEMM reads the row sums up to a whole tile of tokens, so the array is that much longer
+// than the limit on a call.  Each device
 // holds its own copy until the process ends.  In host code the name is only a
 // host-side stand-in: the device address comes from hipGetSymbolAddress, taken once
 // per device at context creation.
 constexpr int64_t kNoAllocScratchBytes = int64_t(16) << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kRsPad * 4];
 
 namespace {
 
@@ -155,7 +157,7 @@ termezo_status ensure_xs_capacity(termezo_ctx* c, int64_t M) {
     dfree(c->d_xrs);
     c->xs_cap = 0;
     TMZ_HIP(c, dalloc(&c->d_xs, (size_t)M));
-    TMZ_HIP(c, dalloc(&c->d_xrs, (size_t)M));
+    TMZ_HIP(c, dalloc(&c->d_xrs, (size_t)rs_entries(M)));
     c->xs_cap = M;
   }
   return TERMEZO_OK;
@@ -770,7 +772,7 @@ termezo_status termezo_memory_footprint(termezo_ctx* c, int64_t* library_bytes,
   b += L * 8;                                                    // |w| sums of the other sign
   if (c->mirror) b += 2 * c->wc_cap * dsz;                       // active latents (list order)
   b += (int64_t)kHistBins * 8 + (int64_t)sizeof(SelectState) + 4 * 8 + kScalLen * 4 + 4;
-  b += c->xq_cap + c->xs_cap * 8;                                // activation-quant scratch
+  b += c->xq_cap + (c->xs_cap + rs_entries(c->xs_cap)) * 4;                                // activation-quant scratch
   for (const ThetaHost& t : c->theta) b += 2 * t.n * (int64_t)dtype_size(t.dtype);
   if (c->d_codes_snap) b += c->code_words * 4 + L * 4;               // codes snapshot
   if (library_bytes) *library_bytes = b;

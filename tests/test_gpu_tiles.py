@@ -1,0 +1,112 @@
+"""Kernel variants at the edges of their tiles, against the CPU oracle through the C ABI.
+
+Integer accumulators, scales and outputs are bit for bit the oracle's; decoder losses keep the
+bars of the decoder tests (5e-3 per position, 1e-3 on the batch: bf16 storage on the device,
+64 bits on the oracle)."""
+import numpy as np
+import pytest
+
+from paper_2609_33548_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _linear(orc, torch, M, K, N, xdt, ydt, inspect):
+    from paper_2609_33548_amd import termezo
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    w = synth.latents(3, [N * K])
+    ref = orc.TerMeZOOracle([orc.Layer(N, K)], w)
+    W = torch.from_numpy(w.reshape(N, K)).cuda()
+    ctx = termezo.Context([W])
+    ctx.build_mask(0.01)
+    ref.build_mask(0.01)
+    ctx.perturb(11, 1e-3, 1)
+    codes, _, betas = ref.perturb(11, 1e-3, 1)
+    x = synth.activations(4, M, K, bf16=(xdt == "bf16"))
+    rxq, rs = orc.act_quant(x)
+    racc, ry = orc.bitlinear(rxq, rs, codes[0], betas[0])
+    if ydt == "bf16":
+        ry = orc.bf16_round(ry)
+    xd = torch.from_numpy(x).cuda().to(tdt[xdt])
+    # guard elements after the output: a tile must not write past the last row
+    buf = torch.full((M * N + 64,), 7.0, dtype=tdt[ydt], device="cuda")
+    y = buf[:M * N].view(M, N)
+    if inspect:
+        xq = torch.empty((M, K), dtype=torch.int8, device="cuda")
+        s = torch.empty(M, dtype=torch.float32, device="cuda")
+        acc = torch.full((M * N + 64,), 7, dtype=torch.int32, device="cuda")
+        ctx.bitlinear_forward(0, xd, y, xq, s, acc[:M * N])
+        assert np.array_equal(xq.cpu().numpy(), rxq)
+        assert np.array_equal(s.cpu().numpy(), rs)
+        assert np.array_equal(acc[:M * N].view(M, N).cpu().numpy(), racc)
+        assert bool((acc[M * N:] == 7).all())
+    else:
+        ctx.bitlinear_forward(0, xd, y)
+    assert np.array_equal(y.float().cpu().numpy(), ry)
+    assert bool((buf[M * N:] == 7.0).all())
+    ctx.close()
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (129, 256, 64), (191, 512, 72),          # 64-wide tiles: a partial row tile, a partial unit group
+    (256, 2560, 2560),                       # whole tiles below one round of compute units
+    (320, 128, 264), (449, 384, 1000),       # K steps of 128
+    (333, 688, 256), (200, 16, 48),          # K not a multiple of 128: zero-padded last step
+    (777, 1536, 2568), (1000, 2560, 3848),   # 128-wide tiles
+    (2049, 1536, 4104),                      # 256-wide tiles, one row in the last one
+    (150, 256, 37)])                         # no whole output units: register-staged kernel
+@pytest.mark.parametrize("xdt,ydt,inspect", [("bf16", "bf16", False), ("f32", "f32", True)])
+def test_bitlinear_tile_edges(orc, M, K, N, xdt, ydt, inspect):
+    torch = _torch()
+    print(f"tiles M={M} K={K} N={N} x={xdt} y={ydt}", flush=True)
+    _linear(orc, torch, M, K, N, xdt, ydt, inspect)
+
+
+@pytest.mark.parametrize("d,H,Hkv,F,V,S,B", [
+    (256, 4, 4, 688, 1000, 87, 3),       # gate|up: half a group of 32 features at the end
+    # several tiles of each kind, all ragged.  495 labelled positions: the per-position error is
+    # that of bf16 storage (median 8e-4, 99th percentile 3.5e-3 at d = 512), whose extreme grows
+    # with the number of positions (4.0e-3 here, 5.2e-3 of 1495 positions at 300 tokens)
+    (512, 8, 2, 1376, 515, 100, 5),
+])
+def test_decoder_ragged_tiles(orc, d, H, Hkv, F, V, S, B):
+    torch = _torch()
+    from oracle import decoder_ref as dec
+    from paper_2609_33548_amd import termezo
+    print(f"bf16 decoder d={d} H={H}/{Hkv} F={F} S={S} B={B} V={V}", flush=True)
+    cfg = dec.DecoderConfig(n_blocks=2, d_model=d, n_heads=H, n_kv_heads=Hkv, d_ffn=F, vocab=V,
+                            bf16=True)
+    shapes = cfg.layer_shapes()
+    w = synth.latents(40, [o * i for o, i in shapes], bf16=True)
+    ref = orc.TerMeZOOracle([orc.Layer(o, i) for o, i in shapes], w, bf16=True)
+    tensors, off = [], 0
+    for o, i in shapes:
+        tensors.append(torch.from_numpy(w[off:off + o * i].reshape(o, i)).cuda().to(torch.bfloat16))
+        off += o * i
+    ctx = termezo.Context(tensors)
+    emb = synth.latents(41, [V * d], bf16=True).reshape(V, d)
+    E = torch.from_numpy(emb).cuda().to(torch.bfloat16)
+    model = termezo.Model(ctx, 2, d, H, Hkv, F, V, E)
+    tok = synth.tokens(42, B, S, V)
+    ctx.build_mask(0.01)
+    ref.build_mask(0.01)
+    ctx.perturb(5, 1e-3, 1)
+    rows = torch.empty(B * S, device="cuda")
+    loss = model.loss(torch.from_numpy(tok).cuda(), row_loss_dev=rows)
+    codes, _, betas = ref.perturb(5, 1e-3, 1)
+    want = dec.forward_row_losses(cfg, emb, tok, codes, betas)
+    got = rows.cpu().numpy().reshape(want.shape)
+    rel = np.abs(got - want)[:, :-1] / np.abs(want[:, :-1])
+    print(f"  per position max {rel.max():.2e} median {np.median(rel):.2e}", flush=True)
+    assert rel.max() <= 5e-3
+    assert abs(loss - dec.mean_loss(want)) <= 1e-3 * abs(dec.mean_loss(want))
+    assert np.all(got[:, -1] == 0.0)
+    model.close()
+    ctx.close()
