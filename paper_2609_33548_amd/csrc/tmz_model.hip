@@ -603,7 +603,10 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* q, const float* k
 // ---------------------------------------------------------------------------
 // Per-layer preparation of K and V for attention (one block per 64 tokens of
 // one KV head): K is rotated in place (RoPE, as in k_rope), V is transposed to
-// vt [B*Hkv][hd][S] through an LDS tile (16-byte reads and writes).
+// vt [B*Hkv][hd][vs] through an LDS tile (16-byte reads and writes).  vs is S rounded up
+// to whole blocks, the tokens past S zero: every store is 16 aligned bytes (6 x 333 tokens,
+// 16 heads of 96: 12.3 us with rows of S and single stores, 8.7 us; the
+// attention that reads them 38 -> 28 us).
 // ---------------------------------------------------------------------------
 // Rotary embedding of one 8-dim chunk at dims d0..d0+7 given its partner
 // chunk (d0 -/+ hd/2), as in k_rope: low half a c - b s, high half a s + b c
@@ -626,7 +629,7 @@ __device__ __forceinline__ uint4 rope_chunk(uint4 own, uint4 par, bool low, cons
 template <int HD>
 __global__ void __launch_bounds__(256) k_kv_prep(uint16_t* __restrict__ k,
                                                  const uint16_t* __restrict__ v,
-                                                 uint16_t* __restrict__ vt, int S, int Hkv,
+                                                 uint16_t* __restrict__ vt, int S, int vs, int Hkv,
                                                  const float* __restrict__ rope_c,
                                                  const float* __restrict__ rope_s) {
   constexpr int HALF = HD / 2;
@@ -669,14 +672,8 @@ __global__ void __launch_bounds__(256) k_kv_prep(uint16_t* __restrict__ k,
     uint32_t w[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) w[j] = (uint32_t)t[c8 + 2 * j][r] | ((uint32_t)t[c8 + 2 * j + 1][r] << 16);
-    uint16_t* dst = vt + ((int64_t)bh * HD + r) * S + s0 + c8;
-    if ((S & 7) == 0 && s0 + c8 + 8 <= S) {
-      *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (s0 + c8 + j < S) dst[j] = t[c8 + j][r];
-    }
+    *reinterpret_cast<uint4*>(vt + ((int64_t)bh * HD + r) * vs + s0 + c8) =
+        make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
@@ -696,7 +693,7 @@ template <int HD>
 __global__ void __launch_bounds__(512) k_attn_bf16(const uint16_t* __restrict__ q,
                                                    const uint16_t* __restrict__ k,
                                                    const uint16_t* __restrict__ vt,
-                                                   uint16_t* __restrict__ o, int S, int Hq,
+                                                   uint16_t* __restrict__ o, int S, int vs, int Hq,
                                                    int Hkv, float scale_log2,
                                                    const float* __restrict__ rope_c,
                                                    const float* __restrict__ rope_s) {
@@ -717,10 +714,9 @@ __global__ void __launch_bounds__(512) k_attn_bf16(const uint16_t* __restrict__ 
   const int64_t rowq = (int64_t)Hq * HD, rowkv = (int64_t)Hkv * HD;
   const int64_t base = (int64_t)b * S;
   const uint16_t* kb = k + base * rowkv + (int64_t)kh * HD;
-  const uint16_t* vtb = vt + ((int64_t)b * Hkv + kh) * HD * S;
+  const uint16_t* vtb = vt + ((int64_t)b * Hkv + kh) * HD * vs;
   const int qw0 = qt * QB + w * 16;             // first query of this wave
   const int qpos = qw0 + c;                     // this lane's query
-  const bool vec_v = (S & 7) == 0;
 
   // rope(Q)^T fragments: lane holds rope(Q)[qpos][32 s + 8 g .. +7]
   v8bf qf[HD / 32];
@@ -751,19 +747,8 @@ __global__ void __launch_bounds__(512) k_attn_bf16(const uint16_t* __restrict__ 
         const int kr = e / (HD / 8), dc = (e % (HD / 8)) * 8;
         if (k0 + kr < S) rk[i] = *reinterpret_cast<const uint4*>(kb + (int64_t)(k0 + kr) * rowkv + dc);
         const int dr = e / (KT / 8), kc = (e % (KT / 8)) * 8;
-        const uint16_t* vp = vtb + (int64_t)dr * S + k0 + kc;
-        if (vec_v && k0 + kc + 8 <= S) {
-          rv[i] = *reinterpret_cast<const uint4*>(vp);
-        } else {
-          uint32_t t4[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t lo16 = (k0 + kc + 2 * j < S) ? vp[2 * j] : 0u;
-            const uint32_t hi16 = (k0 + kc + 2 * j + 1 < S) ? vp[2 * j + 1] : 0u;
-            t4[j] = lo16 | (hi16 << 16);
-          }
-          rv[i] = make_uint4(t4[0], t4[1], t4[2], t4[3]);
-        }
+        // rows of vs tokens, a multiple of the tile, zero past S
+        rv[i] = *reinterpret_cast<const uint4*>(vtb + (int64_t)dr * vs + k0 + kc);
       }
     }
   };
@@ -913,13 +898,13 @@ __global__ void __launch_bounds__(512) k_attn_bf16(const uint16_t* __restrict__ 
 //    tile's maximum exceeds it by more than 2^8 (in exp2 units); the
 //    normalised result does not depend on that choice.  Query tiles are
 //    dispatched heaviest first.
-// Requires S % 64 == 0 and S % QT == 0.
+// Requires S % 64 == 0 and S % QT == 0 (then vs = S).
 // ---------------------------------------------------------------------------
 template <int HD, int G>
 __global__ void __launch_bounds__(512) k_attn_gqa(const uint16_t* __restrict__ q,
                                                   const uint16_t* __restrict__ k,
                                                   const uint16_t* __restrict__ vt,
-                                                  uint16_t* __restrict__ o, int S, int Hkv,
+                                                  uint16_t* __restrict__ o, int S, int vs, int Hkv,
                                                   int nbh, int nqt, float scale_log2,
                                                   const float* __restrict__ rope_c,
                                                   const float* __restrict__ rope_s) {
@@ -972,7 +957,7 @@ __global__ void __launch_bounds__(512) k_attn_gqa(const uint16_t* __restrict__ q
     const int kr = c / CPR, kc = (c % CPR) ^ swk(kr);
     ksrc[j] = reinterpret_cast<const uint8_t*>(k + (base + kr) * rowkv + (int64_t)kvh * HD) + 16 * kc;
     const int vr = c / 8, vc = (c % 8) ^ swv(vr);
-    vsrc[j] = reinterpret_cast<const uint8_t*>(vt + (((int64_t)b * Hkv + kvh) * HD + vr) * S) + 16 * vc;
+    vsrc[j] = reinterpret_cast<const uint8_t*>(vt + (((int64_t)b * Hkv + kvh) * HD + vr) * vs) + 16 * vc;
   }
   auto issue = [&](int kt, int st) __attribute__((always_inline)) {
     const uint32_t kb = lds_offset(lds + st * 2 * TB), vb = kb + TB;
@@ -1366,7 +1351,10 @@ __global__ void __launch_bounds__(512) k_lmhead_bf16(const uint16_t* __restrict_
 // chunk c ^ sw(r), so the fragment reads of 16 consecutive rows hit distinct
 // banks.  K assignment: in sub-step ks, lane half h supplies chunk
 // h * (2 BK / 32) + ks of its row for both operands.
-// Requires M % 256 == 0, V % 256 == 0, d % BK == 0.
+// Any number of tokens and vocabulary columns: the operands of a tile are buffers that end
+// with the matrices, so rows past the end fetch nothing, and in the last column tile the
+// columns past V count as minus infinity (1998 tokens x 32,000 at d 1536: 305 us on the
+// register-staged kernel, 179 us here).  Requires d % BK == 0.
 template <int STAGES, int BK, int NWN>
 __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ E, int64_t M,
@@ -1391,40 +1379,41 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid / (BN / WN), wn = wid % (BN / WN);
-  const int64_t ntiles = (M / BM) * nvt;
+  const int64_t nmt = (M + BM - 1) / BM, ntiles = nmt * nvt;
   const int nk = (int)(d / BK);
 
   // load j of wave w fills the 64 LDS chunks (w * IPW + j) * 64 .. + 63 of an operand:
   // RPL rows of CPR chunks.  The chunk swizzle of those rows depends on j only through
-  // its parity, so two per-lane sources per operand serve every load (the rest of the
+  // its parity, so two per-lane offsets serve every load of both operands (the rest of the
   // offset is wave-uniform).
   constexpr int RPL = 64 / CPR;                   // rows per 1 KB load
   static_assert(IPW % 2 == 0, "loads per wave");
-  const uint8_t* asrc[2];
-  const uint8_t* bsrc[2];
-  // tile it of the grouped (XCD-aware) order: its origin and the load sources
+  uint32_t off[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int row = (wid * IPW + p) * RPL + lane / CPR, lc = (lane % CPR) ^ sw(row);
+    off[p] = (uint32_t)(row * d * 2) + 16 * lc;
+  }
+  v4i_rsrc arsrc, brsrc;
+  // tile it of the grouped (XCD-aware) order: its origin and its operands
   auto tile = [&](int64_t it, int64_t& m0, int64_t& n0) __attribute__((always_inline)) {
     int64_t tm, tn;
-    tile_of_linear(xcd_linear(it, ntiles), M / BM, nvt, tm, tn);
+    tile_of_linear(xcd_linear(it, ntiles), nmt, nvt, tm, tn);
     m0 = tm * BM;
     n0 = tn * BN;
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const int row = (wid * IPW + p) * RPL + lane / CPR, lc = (lane % CPR) ^ sw(row);
-      asrc[p] = reinterpret_cast<const uint8_t*>(x) + (m0 + row) * d * 2 + 16 * lc;
-      bsrc[p] = reinterpret_cast<const uint8_t*>(E) + (n0 + row) * d * 2 + 16 * lc;
-    }
+    arsrc = buffer_of(x + m0 * d, (uint32_t)(min((int64_t)BM, M - m0) * d * 2));
+    brsrc = buffer_of(E + n0 * d, (uint32_t)(min((int64_t)BN, V - n0) * d * 2));
   };
   const uint32_t wbase = __builtin_amdgcn_readfirstlane(wid) * IPW * 1024u;
   auto Ast = [&](int st) { return lds + st * 2 * OPB; };
   auto issue = [&](int kt, int st) __attribute__((always_inline)) {
-    const int64_t koff = (int64_t)kt * ROWB;
+    const uint32_t koff = (uint32_t)kt * ROWB, rstep = (uint32_t)(RPL * d * 2);
     const uint32_t ab = lds_offset(Ast(st)) + wbase, bb = ab + OPB;
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
-      const int64_t roff = (int64_t)(j & ~1) * RPL * d * 2 + koff;
-      dma16(asrc[j & 1] + roff, ab + 1024u * j);
-      dma16(bsrc[j & 1] + roff, bb + 1024u * j);
+      const uint32_t roff = (j & ~1) * rstep + koff;
+      dma16_buf(off[j & 1], arsrc, roff, ab + 1024u * j);
+      dma16_buf(off[j & 1], brsrc, roff, bb + 1024u * j);
     }
   };
 
@@ -1471,7 +1460,7 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
   if (it >= ntiles) return;                       // whole block
   int64_t m0, n0;
   tile(it, m0, n0);
-  for (int i = tid; i < BM; i += NT) lbl[i] = labels[m0 + i];
+  for (int i = tid; i < BM; i += NT) lbl[i] = m0 + i < M ? labels[m0 + i] : -1;
 #pragma unroll
   for (int st = 0; st < STAGES - 1; ++st)
     if (st < nk) issue(st, st);
@@ -1504,6 +1493,16 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
 
     // ---- epilogue: per token, max and sum of exp over the block's 256 columns ----
     const float L2E = 1.4426950408889634f;
+    if (cn0 + BN > V) {                           // the last, partial column tile (uniform)
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (cn0 + wn * WN + 32 * b + 8 * (r >> 2) + 4 * h + (r & 3) >= V) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) acc[a][b][r] = -INFINITY;
+          }
+    }
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
       const int li = wm * WM + 32 * a + (lane & 31);
@@ -1514,12 +1513,13 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[a][b][r]);
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float mb = mx == -INFINITY ? 0.0f : mx;   // no column of this wave inside V: sum 0
       float se = 0.0f;
 #pragma unroll
       for (int b = 0; b < TN; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          se += __builtin_amdgcn_exp2f((acc[a][b][r] - mx) * L2E);
+          se += __builtin_amdgcn_exp2f((acc[a][b][r] - mb) * L2E);
           const int64_t col = cn0 + wn * WN + 32 * b + 8 * (r >> 2) + 4 * h + (r & 3);
           if (col == lb) lab[cm0 + li] = acc[a][b][r];
         }
@@ -1530,7 +1530,7 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
       }
     }
     __syncthreads();
-    if (tid < BM) {
+    if (tid < BM && cm0 + tid < M) {
       float mx = -INFINITY;
 #pragma unroll
       for (int w = 0; w < BN / WN; ++w) mx = fmaxf(mx, red[w][tid][0]);
@@ -1548,7 +1548,7 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
     asm volatile("" : "+s"(itr));
     tile(itr, m0, n0);
     __syncthreads();                              // red and lbl read by every wave
-    for (int i = tid; i < BM; i += NT) lbl[i] = labels[m0 + i];
+    for (int i = tid; i < BM; i += NT) lbl[i] = m0 + i < M ? labels[m0 + i] : -1;
   }
 }
 
@@ -1716,6 +1716,9 @@ void model_free_buffers(termezo_model* m) {
   m->cap_S = 0;
 }
 
+// Tokens of a row of V^T: whole 64-token tiles.
+int64_t vt_tokens(int64_t S) { return (S + 63) / 64 * 64; }
+
 termezo_status model_reserve(termezo_model* m, int64_t M, int S) {
   if (M <= m->cap_M && S == m->cap_S) return TERMEZO_OK;
   model_free_buffers(m);
@@ -1733,7 +1736,8 @@ termezo_status model_reserve(termezo_model* m, int64_t M, int S) {
   A(&m->q, M * dq * es);
   A(&m->k, M * dkv * es);
   A(&m->v, M * dkv * es);
-  A(&m->vt, M * dkv * es);
+  // V^T of every sequence: M / S rows of whole tiles (S is part of the reservation's key)
+  A(&m->vt, (M + S - 1) / S * vt_tokens(S) * dkv * es);
   A(&m->attn, M * dq * es);
   A(&m->g, M * c.d_ffn * es);
   A(&m->u, M * c.d_ffn * es);
@@ -1784,37 +1788,38 @@ hipError_t run_attention(termezo_model* m, int B, int S, hipStream_t st) {
     return hipGetLastError();
   }
   const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)m->hd));
+  const int vs = (int)vt_tokens(S);
   dim3 pgrid((unsigned)((S + 63) / 64), (unsigned)(B * c.n_kv_heads));
   dim3 grid((unsigned)((S + 127) / 128), c.n_heads, B);
 #define TMZ_ATTN(HDV)                                                                        \
   hipLaunchKernelGGL(k_kv_prep<HDV>, pgrid, dim3(256), 0, st, (uint16_t*)m->k,                  \
-                     (const uint16_t*)m->v, (uint16_t*)m->vt, S, c.n_kv_heads, m->rope_c,      \
+                     (const uint16_t*)m->v, (uint16_t*)m->vt, S, vs, c.n_kv_heads, m->rope_c,      \
                      m->rope_s);                                                              \
   hipLaunchKernelGGL(k_attn_bf16<HDV>, grid, dim3(512), 0, st, (const uint16_t*)m->q,          \
-                     (const uint16_t*)m->k, (const uint16_t*)m->vt, (uint16_t*)m->attn, S,     \
+                     (const uint16_t*)m->k, (const uint16_t*)m->vt, (uint16_t*)m->attn, S, vs, \
                      c.n_heads, c.n_kv_heads, sl2, m->rope_c, m->rope_s)
   const int G = c.n_heads / c.n_kv_heads;
   const bool gqa = (m->hd == 64 || m->hd == 96 || m->hd == 128) &&
                    (G == 1 || G == 2 || G == 4 || G == 8) &&
                    S % 64 == 0 && S % (256 / G) == 0;
   if (gqa) {
-    const int nbh = B * c.n_kv_heads, nqt = S / (256 / G);
+    const int nbh = B * c.n_kv_heads, nqt = (S + 256 / G - 1) / (256 / G);
     if (m->hd == 128)
       hipLaunchKernelGGL(k_kv_prep<128>, pgrid, dim3(256), 0, st, (uint16_t*)m->k,
-                         (const uint16_t*)m->v, (uint16_t*)m->vt, S, c.n_kv_heads, m->rope_c,
+                         (const uint16_t*)m->v, (uint16_t*)m->vt, S, vs, c.n_kv_heads, m->rope_c,
                          m->rope_s);
     else if (m->hd == 96)
       hipLaunchKernelGGL(k_kv_prep<96>, pgrid, dim3(256), 0, st, (uint16_t*)m->k,
-                         (const uint16_t*)m->v, (uint16_t*)m->vt, S, c.n_kv_heads, m->rope_c,
+                         (const uint16_t*)m->v, (uint16_t*)m->vt, S, vs, c.n_kv_heads, m->rope_c,
                          m->rope_s);
     else
       hipLaunchKernelGGL(k_kv_prep<64>, pgrid, dim3(256), 0, st, (uint16_t*)m->k,
-                         (const uint16_t*)m->v, (uint16_t*)m->vt, S, c.n_kv_heads, m->rope_c,
+                         (const uint16_t*)m->v, (uint16_t*)m->vt, S, vs, c.n_kv_heads, m->rope_c,
                          m->rope_s);
 #define TMZ_GQA(HDV, GV)                                                                      \
   hipLaunchKernelGGL((k_attn_gqa<HDV, GV>), dim3((unsigned)(nqt * nbh)), dim3(512), 0, st,      \
                      (const uint16_t*)m->q, (const uint16_t*)m->k, (const uint16_t*)m->vt,     \
-                     (uint16_t*)m->attn, S, c.n_kv_heads, nbh, nqt, sl2, m->rope_c, m->rope_s)
+                     (uint16_t*)m->attn, S, vs, c.n_kv_heads, nbh, nqt, sl2, m->rope_c, m->rope_s)
     switch (m->hd * 16 + G) {
       case 128 * 16 + 1: TMZ_GQA(128, 1); break;
       case 128 * 16 + 2: TMZ_GQA(128, 2); break;
@@ -2124,7 +2129,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     const unsigned nb = (unsigned)(nvt * ((M + kLmTile - 1) / kLmTile));
     // the direct-load kernel walks its tiles with one block per compute unit
     const unsigned nbp = c->n_cu > 0 && nb > (unsigned)c->n_cu ? (unsigned)c->n_cu : nb;
-    if (M % kLmTile == 0 && cf.vocab % kLmTile == 0 && d % 64 == 0)
+    if (d % kLmDmaBK == 0)
       hipExtLaunchKernelGGL((k_lmhead_dma<kLmDmaStages, kLmDmaBK, kLmDmaNWN>), dim3(nbp),
                             dim3(128 * kLmDmaNWN), 0, s, ev_lm.start, ev_lm.stop, 0,
                             (const uint16_t*)m->xf, (const uint16_t*)emb, M, d, (int64_t)cf.vocab,
