@@ -760,7 +760,10 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
 #pragma unroll
       for (int b = 0; b < TN; ++b) {
         const int64_t nb = n0 + wn * WN + b * 32;
-        const int sg = (out.nseg > 2 && nb >= out.nstart[2]) ? 2 : (out.nseg > 1 && nb >= out.nstart[1]) ? 1 : 0;
+        // the segment of the block's columns; of the lane's column where a boundary may lie
+        // inside a block
+        const int64_t ns = FULL ? nb : nb + n;
+        const int sg = (out.nseg > 2 && ns >= out.nstart[2]) ? 2 : (out.nseg > 1 && ns >= out.nstart[1]) ? 1 : 0;
         float f[16], v[16];
         load_fac(a, sg, f);
 #pragma unroll
@@ -1470,14 +1473,13 @@ static float edge_cost(const EdgeTile& t, int64_t M, int64_t K, int64_t N, int n
   return t.c0 + t.l * (float)K + (float)((T + cu - 1) / cu - 1) * (t.a + t.b * (float)K);
 }
 
-// Whole 16-byte output units and 16-byte aligned code rows: what every full or edge tile of
-// the direct-load kernels needs beyond its shape (kOddTile: the outputs only).
+// Whole 16-byte output units, segment by segment: what the direct-load kernels need.
 static bool units_ok(const GemmOut& out, termezo_dtype ydt) {
   const int64_t ue = ydt == TERMEZO_F32 ? 4 : 8;       // outputs per 16-byte unit
   bool ok = true;
   for (int i = 0; i < out.nseg; ++i)
     ok = ok && out.ld[i] % ue == 0 && reinterpret_cast<uintptr_t>(out.y[i]) % 16 == 0 &&
-         (i == 0 || out.nstart[i] % 32 == 0);
+         out.nstart[i] % ue == 0;
   return ok && out.nstart[out.nseg] % ue == 0;
 }
 
@@ -1607,8 +1609,9 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
       return launch_tile<256, 256, 128, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
     return launch_tile<128, 128, 64, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
   }
-  const bool whole = M % 256 == 0 && N % 256 == 0 && K % kBK == 0 &&
-                     reinterpret_cast<uintptr_t>(codes) % 16 == 0;
+  bool whole = M % 256 == 0 && N % 256 == 0 && K % kBK == 0 &&
+               reinterpret_cast<uintptr_t>(codes) % 16 == 0;
+  for (int i = 1; i < out.nseg; ++i) whole = whole && out.nstart[i] % 32 == 0;
   if (!whole || T < n_cu) {
 #define TMZ_ANY(TY, MD) launch_edge<TY, MD>(xq, s, rs, codes, M, K, N, out, acc, n_cu, st, ev)
     if (ydt == TERMEZO_F32)

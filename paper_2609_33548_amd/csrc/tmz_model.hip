@@ -49,36 +49,34 @@ __device__ __forceinline__ float wmax(float v) {
   return v;
 }
 
-// Block (256 threads) reductions through a 4-entry LDS scratch.
-__device__ __forceinline__ float bsum(float v, float* red) {
-  v = wsum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
-}
-__device__ __forceinline__ float bmax(float v, float* red) {
-  v = wmax(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-
 __device__ __forceinline__ int8_t q8(float x, float s) {
   return (int8_t)fminf(fmaxf(__builtin_rintf(x * s), -128.0f), 127.0f);
 }
 
 
 // ---------------------------------------------------------------------------
-// h[m] = E[tok[m]].  An id outside [0, V) reads row 0 instead and sets bit 8 of
-// the deferred error word, so the embedding is never read out of bounds.
+// h[m] = E[tok[m]] and the next-token label of position m (-1 at the last position of a
+// sequence).  An id outside [0, V) reads row 0, is label 0 and sets bit 8 of the deferred
+// error word, so the embedding is never read out of bounds.  (One launch for both: a
+// launch in a chain of dependent ones takes about 4.5 us however little it does.)
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256) k_embed(const int32_t* tok, const T* E, int64_t d,
-                                               int64_t V, T* h, int32_t* err) {
+                                               int64_t V, int S, T* h, int32_t* labels,
+                                               int32_t* err) {
   const int64_t m = blockIdx.x;
   int64_t t = tok[m];
+  if (threadIdx.x == 0) {
+    int32_t l = -1;
+    if (m % S != S - 1) {
+      l = tok[m + 1];
+      if (l < 0 || (int64_t)l >= V) {
+        atomicOr(err, 8);
+        l = 0;
+      }
+    }
+    labels[m] = l;
+  }
   if (t < 0 || t >= V) {
     if (threadIdx.x == 0) atomicOr(err, 8);
     t = 0;
@@ -538,13 +536,13 @@ static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int
 }
 
 // ---------------------------------------------------------------------------
-// Rotary embedding in place on x [M][H * hd]; pairs (i, i + hd/2) rotated by
-// the angle pos * base^(-2i/hd), cos/sin from a table [S][hd/2].
+// Rotary embedding in place on q [M][Hq * hd] and k [M][Hkv * hd]; pairs (i, i + hd/2)
+// rotated by the angle pos * base^(-2i/hd), cos/sin from a table [S][hd/2].
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(256) k_rope(T* x, int64_t M, int H, int hd, int S,
+__global__ void __launch_bounds__(256) k_rope(T* q, T* k, int64_t M, int Hq, int Hkv, int hd, int S,
                                               const float* cs, const float* sn) {
-  const int half = hd / 2;
+  const int half = hd / 2, H = Hq + Hkv;
   const int64_t total = M * H * half;
   for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total;
        t += (int64_t)gridDim.x * 256) {
@@ -553,49 +551,74 @@ __global__ void __launch_bounds__(256) k_rope(T* x, int64_t M, int H, int hd, in
     const int64_t m = mh / H;
     const int h = (int)(mh % H);
     const int p = (int)(m % S);
+    T* x = h < Hq ? q + (m * Hq + h) * hd : k + (m * Hkv + h - Hq) * hd;
     const float c = cs[p * half + i], s = sn[p * half + i];
-    const int64_t base = m * (int64_t)H * hd + (int64_t)h * hd;
-    const float a = ld_act(x, base + i), b = ld_act(x, base + i + half);
-    st_act(x, base + i, a * c - b * s);
-    st_act(x, base + i + half, a * s + b * c);
+    const float a = ld_act(x, i), b = ld_act(x, i + half);
+    st_act(x, i, a * c - b * s);
+    st_act(x, i + half, a * s + b * c);
   }
 }
 
 // ---------------------------------------------------------------------------
-// Causal GQA attention, fp32 activations (small shapes): one block per
-// (query row, head); scores staged in LDS.
+// Causal GQA attention, fp32 activations (small shapes): one wave per (query row, head),
+// scores staged in LDS (S floats per wave).  Lanes take keys for the scores (16-byte loads
+// of their key rows) and dims for the output (whole rows of V per load, eight in flight).
+// The row sum adds the terms in the order of four strided groups of 64 keys.  With a block
+// of four waves per query and single loads 4 x 64 tokens, 4 heads of 64 took 15.1 us.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_attn_f32(const float* q, const float* k, const float* v,
-                                                  float* o, int S, int Hq, int Hkv, int hd,
-                                                  float scale) {
-  extern __shared__ float sc[];  // S scores
-  __shared__ float red[4];
-  const int64_t m = blockIdx.x;  // b * S + p
+__global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q,
+                                                  const float* __restrict__ k,
+                                                  const float* __restrict__ v,
+                                                  float* __restrict__ o, int64_t M, int S, int Hq,
+                                                  int Hkv, int hd, float scale) {
+  extern __shared__ float scores[];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  float* sc = scores + wid * S;
+  const int64_t mw = (int64_t)blockIdx.x * (blockDim.x >> 6) + wid;
+  const int64_t m = min(mw, M - 1);         // b * S + p (a wave past the end repeats the last)
   const int h = blockIdx.y;
   const int p = (int)(m % S);
   const int64_t b0 = m - p;
   const int kh = h / (Hq / Hkv);
+  const int64_t ldk = (int64_t)Hkv * hd;
   const float* qr = q + m * (int64_t)Hq * hd + (int64_t)h * hd;
+  const float* kb = k + b0 * ldk + (int64_t)kh * hd;
+  const float* vb = v + b0 * ldk + (int64_t)kh * hd;
   float mx = -INFINITY;
-  for (int j = threadIdx.x; j <= p; j += 256) {
-    const float* kr = k + (b0 + j) * (int64_t)Hkv * hd + (int64_t)kh * hd;
+  for (int j = lane; j <= p; j += 64) {
+    const float* kr = kb + j * ldk;
     float acc = 0.0f;
-    for (int e = 0; e < hd; ++e) acc = fmaf(qr[e], kr[e], acc);
+#pragma unroll 4
+    for (int e = 0; e < hd; e += 4) {       // hd % 16 == 0
+      const float4 a = *reinterpret_cast<const float4*>(qr + e);
+      const float4 b = *reinterpret_cast<const float4*>(kr + e);
+      acc = fmaf(a.x, b.x, acc);
+      acc = fmaf(a.y, b.y, acc);
+      acc = fmaf(a.z, b.z, acc);
+      acc = fmaf(a.w, b.w, acc);
+    }
     sc[j] = acc * scale;
     mx = fmaxf(mx, sc[j]);
   }
-  mx = bmax(mx, red);
-  float sum = 0.0f;
-  for (int j = threadIdx.x; j <= p; j += 256) {
-    const float e = expf(sc[j] - mx);
-    sc[j] = e;
-    sum += e;
+  mx = wmax(mx);
+  float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    if (64 * g > p) break;                  // uniform in the wave
+    for (int j = 64 * g + lane; j <= p; j += 256) {
+      const float e = expf(sc[j] - mx);
+      sc[j] = e;
+      part[g] += e;
+    }
+    part[g] = wsum(part[g]);
   }
-  sum = bsum(sum, red);
+  const float sum = (part[0] + part[1]) + (part[2] + part[3]);
   __syncthreads();
-  for (int e = threadIdx.x; e < hd; e += 256) {
+  if (mw >= M) return;
+  for (int e = lane; e < hd; e += 64) {
     float acc = 0.0f;
-    for (int j = 0; j <= p; ++j) acc = fmaf(sc[j], v[(b0 + j) * (int64_t)Hkv * hd + (int64_t)kh * hd + e], acc);
+#pragma unroll 8
+    for (int j = 0; j <= p; ++j) acc = fmaf(sc[j], vb[j * ldk + e], acc);
     o[m * (int64_t)Hq * hd + (int64_t)h * hd + e] = acc / sum;
   }
 }
@@ -1147,35 +1170,99 @@ __global__ void __launch_bounds__(512) k_attn_gqa(const uint16_t* __restrict__ q
 // ---------------------------------------------------------------------------
 constexpr int kVT = 128;   // vocab columns per tile
 
-// fp32 activations: one thread per (row, column).
-__global__ void __launch_bounds__(256) k_lmhead_f32(const float* x, const float* E, int64_t M,
-                                                    int64_t d, int64_t V, const int32_t* labels,
+// fp32 activations: 32 tokens x 128 columns per block on the fp32 matrix cores
+// (v_mfma_f32_32x32x2_f32, fp32 products and sums).  8 waves: wave w takes columns
+// 32 (w % 4) .. + 31 and the K half w / 4, the halves meet in LDS.  The embedding rows are
+// the first operand, so a lane owns one token (l % 32) and 16 of its columns.  K comes in
+// steps of 32: lane half h loads the 16 consecutive values 16 h .. of its row (four 16-byte
+// loads, whole lines between the halves) and product j takes value j of both halves.  These
+// shapes are bound by latency and by the number of blocks, not by the operands (a thread per
+// logit, each reading two rows value by value, took 125 us for 256 x 1024 at d 256).
+__global__ void __launch_bounds__(512) k_lmhead_f32(const float* __restrict__ x,
+                                                    const float* __restrict__ E, int64_t M,
+                                                    int64_t d, int64_t V,
+                                                    const int32_t* __restrict__ labels,
                                                     float* pmax, float* psum, float* lab,
                                                     int64_t nvt) {
-  __shared__ float red[2][4];
-  const int64_t m = (int64_t)blockIdx.y * 2 + (threadIdx.x >> 7);
-  const int64_t n = (int64_t)blockIdx.x * kVT + (threadIdx.x & 127);
-  float logit = -INFINITY;
-  if (m < M && n < V) {
-    float acc = 0.0f;
-    for (int64_t e = 0; e < d; ++e) acc = fmaf(x[m * d + e], E[n * d + e], acc);
-    logit = acc;
-    if (labels[m] == n) lab[m] = acc;
+  __shared__ float part[4][16][64];               // K half 1's sums, then the waves' statistics
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int n = lane & 31, h = lane >> 5, wc = wid & 3, kh = wid >> 2;
+  const int64_t tv = blockIdx.x, m = (int64_t)blockIdx.y * 32 + n;
+  const int64_t c0 = tv * kVT + 32 * wc;          // first column of this wave
+  // rows past the end read the last one; their results are dropped
+  const float* xr = x + min(m, M - 1) * d;
+  const float* er = E + min(c0 + n, V - 1) * d;
+  const int64_t steps = (d + 31) / 32, half = (steps + 1) / 2;
+  const int64_t s0 = kh ? half : 0, s1 = kh ? steps : half;
+  v16f acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  float a[2][16], b[2][16];
+  auto load = [&](int64_t st, int slot) __attribute__((always_inline)) {
+    const int64_t k = 32 * st + 16 * h;           // d % 16 == 0: a lane's 16 values exist or not
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float* av = a[slot] + 8 * q;
+      float* bv = b[slot] + 8 * q;
+      if (k < d) {
+        load8(er + k + 8 * q, av);
+        load8(xr + k + 8 * q, bv);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) av[j] = bv[j] = 0.0f;
+      }
+    }
+  };
+  auto mfma = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[slot][j], b[slot][j], acc, 0, 0, 0);
+  };
+  if (s0 < s1) load(s0, 0);
+  for (int64_t st = s0; st < s1; st += 2) {
+    if (st + 1 < s1) load(st + 1, 1);
+    mfma(0);
+    if (st + 1 < s1) {
+      if (st + 2 < s1) load(st + 2, 0);
+      mfma(1);
+    }
   }
-  // per half-block (one row) reductions: 2 waves per row
-  const int half = threadIdx.x >> 7, wv = (threadIdx.x >> 6) & 1;
-  float mx = wmax(logit);
-  if ((threadIdx.x & 63) == 0) red[half][wv] = mx;
+  if (kh == 1)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wc][r][lane] = acc[r];
   __syncthreads();
-  mx = fmaxf(red[half][0], red[half][1]);
+  float mx = -INFINITY, se = 0.0f;
+  if (kh == 0) {
+    const int32_t lb = m < M ? labels[m] : -1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t col = c0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      acc[r] += part[wc][r][lane];
+      if (col >= V) acc[r] = -INFINITY;
+      if (col == lb) lab[m] = acc[r];
+      mx = fmaxf(mx, acc[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mb = mx == -INFINITY ? 0.0f : mx;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) se += expf(acc[r] - mb);
+    se += __shfl_xor(se, 32, 64);
+  }
   __syncthreads();
-  float e = (logit == -INFINITY) ? 0.0f : expf(logit - mx);
-  e = wsum(e);
-  if ((threadIdx.x & 63) == 0) red[half][2 + wv] = e;
+  if (kh == 0 && h == 0) {
+    part[wc][0][n] = mx;
+    part[wc][1][n] = se;
+  }
   __syncthreads();
-  if ((threadIdx.x & 127) == 0 && m < M) {
-    pmax[m * nvt + blockIdx.x] = mx;
-    psum[m * nvt + blockIdx.x] = red[half][2] + red[half][3];
+  if (threadIdx.x < 32 && m < M) {
+    mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, part[w][0][n]);
+    se = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) se += part[w][1][n] * expf(part[w][0][n] - mx);
+    pmax[m * nvt + tv] = mx;
+    psum[m * nvt + tv] = se;
   }
 }
 
@@ -1594,23 +1681,6 @@ __global__ void __launch_bounds__(256) k_loss_mean(const float* row_loss, int64_
   }
 }
 
-// Next-token label of every position (-1 at the last position of a sequence); an
-// id outside [0, V) becomes label 0 and sets bit 8 of the deferred error word.
-__global__ void k_labels(const int32_t* tok, int64_t M, int S, int64_t V, int32_t* labels,
-                         int32_t* err) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  int32_t t = -1;
-  if ((m % S) != S - 1) {
-    t = tok[m + 1];
-    if (t < 0 || (int64_t)t >= V) {
-      atomicOr(err, 8);
-      t = 0;
-    }
-  }
-  labels[m] = t;
-}
-
 }  // namespace tmz
 
 // ===========================================================================
@@ -1782,9 +1852,12 @@ hipError_t run_attention(termezo_model* m, int B, int S, hipStream_t st) {
   const termezo_model_config& c = m->cfg;
   const int64_t M = (int64_t)B * S;
   if (c.act_dtype == TERMEZO_F32) {
-    hipLaunchKernelGGL(k_attn_f32, dim3((unsigned)M, c.n_heads), dim3(256), S * sizeof(float), st,
-                       (const float*)m->q, (const float*)m->k, (const float*)m->v, (float*)m->attn,
-                       S, c.n_heads, c.n_kv_heads, m->hd, 1.0f / std::sqrt((float)m->hd));
+    // four queries per block while their scores fit the default 64 KB of LDS
+    const int nw = S <= 4096 ? 4 : 1;
+    hipLaunchKernelGGL(k_attn_f32, dim3((unsigned)((M + nw - 1) / nw), c.n_heads), dim3(64 * nw),
+                       nw * S * sizeof(float), st, (const float*)m->q, (const float*)m->k,
+                       (const float*)m->v, (float*)m->attn, M, S, c.n_heads, c.n_kv_heads, m->hd,
+                       1.0f / std::sqrt((float)m->hd));
     return hipGetLastError();
   }
   const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)m->hd));
@@ -2020,13 +2093,13 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
 
   if (bf)
     hipLaunchKernelGGL(k_embed<uint16_t>, dim3((unsigned)M), dim3(256), 0, s, tokens,
-                       (const uint16_t*)emb, d, (int64_t)cf.vocab, (uint16_t*)m->h, c->d_err);
+                       (const uint16_t*)emb, d, (int64_t)cf.vocab, seq, (uint16_t*)m->h, m->labels,
+                       c->d_err);
   else
     hipLaunchKernelGGL(k_embed<float>, dim3((unsigned)M), dim3(256), 0, s, tokens,
-                       (const float*)emb, d, (int64_t)cf.vocab, (float*)m->h, c->d_err);
+                       (const float*)emb, d, (int64_t)cf.vocab, seq, (float*)m->h, m->labels,
+                       c->d_err);
   chk(hipGetLastError());
-  hipLaunchKernelGGL(k_labels, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, tokens, M, seq,
-                     (int64_t)cf.vocab, m->labels, c->d_err);
   const unsigned rowg = (unsigned)((M + 3) / 4);
   // RMSNorm (weight row wr of the norm weights, one when there are none), then
   // the quantiser, or stored (the LM-head input)
@@ -2066,12 +2139,10 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
                        kGemmStore, nullptr, c->n_cu, s,
                        span_kernel(m, 0, 2.0 * M * d * (dq + 2 * dkv))));
     if (!bf) {   // bf16: the rotation is applied inside the attention kernel
-      const unsigned rg =
-          (unsigned)std::min<int64_t>(8192, (M * cf.n_heads * (m->hd / 2) + 255) / 256);
-      hipLaunchKernelGGL(k_rope<float>, dim3(rg), dim3(256), 0, s, (float*)m->q, M, cf.n_heads,
-                         m->hd, seq, m->rope_c, m->rope_s);
-      hipLaunchKernelGGL(k_rope<float>, dim3(rg), dim3(256), 0, s, (float*)m->k, M,
-                         cf.n_kv_heads, m->hd, seq, m->rope_c, m->rope_s);
+      const unsigned rg = (unsigned)std::min<int64_t>(
+          8192, (M * (cf.n_heads + cf.n_kv_heads) * (m->hd / 2) + 255) / 256);
+      hipLaunchKernelGGL(k_rope<float>, dim3(rg), dim3(256), 0, s, (float*)m->q, (float*)m->k, M,
+                         cf.n_heads, cf.n_kv_heads, m->hd, seq, m->rope_c, m->rope_s);
       chk(hipGetLastError());
     }
     const int sp = span_begin(m, 1, 4.0 * batch * cf.n_heads * m->hd * (0.5 * seq * (seq + 1.0)), s);
@@ -2140,7 +2211,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
                             (int64_t)cf.vocab, m->labels, m->pmax, m->psum, m->lab, nvt);
   }
   else
-    hipExtLaunchKernelGGL(k_lmhead_f32, dim3((unsigned)nvt, (unsigned)((M + 1) / 2)), dim3(256), 0,
+    hipExtLaunchKernelGGL(k_lmhead_f32, dim3((unsigned)nvt, (unsigned)((M + 31) / 32)), dim3(512), 0,
                           s, ev_lm.start, ev_lm.stop, 0, (const float*)m->xf, (const float*)emb, M,
                           d, (int64_t)cf.vocab, m->labels, m->pmax, m->psum, m->lab, nvt);
   chk(hipGetLastError());

@@ -1,8 +1,9 @@
 """Kernel variants at the edges of their tiles, against the CPU oracle through the C ABI.
 
 Integer accumulators, scales and outputs are bit for bit the oracle's; decoder losses keep the
-bars of the decoder tests (5e-3 per position, 1e-3 on the batch: bf16 storage on the device,
-64 bits on the oracle)."""
+bars of the decoder tests: bf16 5e-3 per position and 1e-3 on the batch (bf16 storage on the
+device, 64 bits on the oracle), fp32 1e-3 per position and 1e-4 on the batch (an int8
+activation that rounds the other way moves a projection by 1 / (127 sqrt(K)))."""
 import numpy as np
 import pytest
 
@@ -69,30 +70,34 @@ def test_bitlinear_tile_edges(orc, M, K, N, xdt, ydt, inspect):
     _linear(orc, torch, M, K, N, xdt, ydt, inspect)
 
 
-@pytest.mark.parametrize("d,H,Hkv,F,V,S,B", [
-    (256, 4, 4, 688, 1000, 87, 3),       # gate|up: half a group of 32 features at the end
+@pytest.mark.parametrize("act,d,H,Hkv,F,V,S,B", [
+    ("f32", 256, 4, 4, 688, 1000, 87, 2),    # a partial vocabulary tile, one partial key group
+    ("f32", 48, 3, 1, 80, 130, 300, 1),      # K steps of 16, more keys than the four groups of 64
+    ("bf16", 256, 4, 4, 688, 1000, 87, 3),   # gate|up: half a group of 32 features at the end
     # several tiles of each kind, all ragged.  495 labelled positions: the per-position error is
     # that of bf16 storage (median 8e-4, 99th percentile 3.5e-3 at d = 512), whose extreme grows
     # with the number of positions (4.0e-3 here, 5.2e-3 of 1495 positions at 300 tokens)
-    (512, 8, 2, 1376, 515, 100, 5),
+    ("bf16", 512, 8, 2, 1376, 515, 100, 5),
 ])
-def test_decoder_ragged_tiles(orc, d, H, Hkv, F, V, S, B):
+def test_decoder_ragged_tiles(orc, act, d, H, Hkv, F, V, S, B):
     torch = _torch()
     from oracle import decoder_ref as dec
     from paper_2609_33548_amd import termezo
-    print(f"bf16 decoder d={d} H={H}/{Hkv} F={F} S={S} B={B} V={V}", flush=True)
+    print(f"{act} decoder d={d} H={H}/{Hkv} F={F} S={S} B={B} V={V}", flush=True)
+    bf16 = act == "bf16"
+    dt = torch.bfloat16 if bf16 else torch.float32
     cfg = dec.DecoderConfig(n_blocks=2, d_model=d, n_heads=H, n_kv_heads=Hkv, d_ffn=F, vocab=V,
-                            bf16=True)
+                            bf16=bf16)
     shapes = cfg.layer_shapes()
-    w = synth.latents(40, [o * i for o, i in shapes], bf16=True)
-    ref = orc.TerMeZOOracle([orc.Layer(o, i) for o, i in shapes], w, bf16=True)
+    w = synth.latents(40, [o * i for o, i in shapes], bf16=bf16)
+    ref = orc.TerMeZOOracle([orc.Layer(o, i) for o, i in shapes], w, bf16=bf16)
     tensors, off = [], 0
     for o, i in shapes:
-        tensors.append(torch.from_numpy(w[off:off + o * i].reshape(o, i)).cuda().to(torch.bfloat16))
+        tensors.append(torch.from_numpy(w[off:off + o * i].reshape(o, i)).cuda().to(dt))
         off += o * i
     ctx = termezo.Context(tensors)
-    emb = synth.latents(41, [V * d], bf16=True).reshape(V, d)
-    E = torch.from_numpy(emb).cuda().to(torch.bfloat16)
+    emb = synth.latents(41, [V * d], bf16=bf16).reshape(V, d)
+    E = torch.from_numpy(emb).cuda().to(dt)
     model = termezo.Model(ctx, 2, d, H, Hkv, F, V, E)
     tok = synth.tokens(42, B, S, V)
     ctx.build_mask(0.01)
@@ -105,8 +110,8 @@ def test_decoder_ragged_tiles(orc, d, H, Hkv, F, V, S, B):
     got = rows.cpu().numpy().reshape(want.shape)
     rel = np.abs(got - want)[:, :-1] / np.abs(want[:, :-1])
     print(f"  per position max {rel.max():.2e} median {np.median(rel):.2e}", flush=True)
-    assert rel.max() <= 5e-3
-    assert abs(loss - dec.mean_loss(want)) <= 1e-3 * abs(dec.mean_loss(want))
+    assert rel.max() <= (5e-3 if bf16 else 1e-3)
+    assert abs(loss - dec.mean_loss(want)) <= (1e-3 if bf16 else 1e-4) * abs(dec.mean_loss(want))
     assert np.all(got[:, -1] == 0.0)
     model.close()
     ctx.close()
