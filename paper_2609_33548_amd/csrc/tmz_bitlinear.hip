@@ -16,7 +16,8 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 // Activation quantisation, one block per token row:
 //   a = max |x|, s = 127 / max(a, 1e-5), x_q = clamp(rne(x s), -128, 127),
 // and the row's sum of x_q (int32, for the offset weight encoding of the
-// full-tile GEMM).
+// full-tile GEMM).  TILED: x_q in the fragment order of the small-M kernel (xq_tile_at),
+// zeros up to whole 256-k chunks.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void load4(const float* p, float v[4]) {
   const float4 a = *reinterpret_cast<const float4*>(p);
@@ -46,7 +47,7 @@ __device__ __forceinline__ int32_t quant_byte(float x, float s) {
 // x); longer rows are read twice.
 constexpr int kActRegs = 8;
 
-template <typename T>
+template <typename T, bool TILED>
 __global__ void __launch_bounds__(256) k_act_quant(const T* __restrict__ x, int64_t K,
                                                    int8_t* __restrict__ xq, float* __restrict__ s,
                                                    int32_t* __restrict__ rs) {
@@ -54,7 +55,10 @@ __global__ void __launch_bounds__(256) k_act_quant(const T* __restrict__ x, int6
   __shared__ int ired[4];
   const int64_t m = blockIdx.x;
   const T* row = x + m * K;
-  uint32_t* out = reinterpret_cast<uint32_t*>(xq + m * K);
+  const int64_t kend = TILED ? xq_tile_chunks(K) * 256 : K;
+  auto put = [&](int64_t k, uint32_t w) __attribute__((always_inline)) {
+    *reinterpret_cast<uint32_t*>(xq + (TILED ? xq_tile_at(m, k, K) : m * K + k)) = w;
+  };
   const bool held = K <= (int64_t)kActRegs * 4 * 256;
   float v[kActRegs][4];
   float a = 0.0f;
@@ -94,13 +98,13 @@ __global__ void __launch_bounds__(256) k_act_quant(const T* __restrict__ x, int6
 #pragma unroll
     for (int i = 0; i < kActRegs; ++i) {
       const int64_t k = ((int64_t)i * 256 + threadIdx.x) * 4;
-      if (k < K) out[k / 4] = pack(v[i]);
+      if (k < kend) put(k, pack(v[i]));              // zeros past K
     }
   } else {
-    for (int64_t k = (int64_t)threadIdx.x * 4; k < K; k += 256 * 4) {
-      float w[4];
-      load4(row + k, w);
-      out[k / 4] = pack(w);
+    for (int64_t k = (int64_t)threadIdx.x * 4; k < kend; k += 256 * 4) {
+      float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (k < K) load4(row + k, w);
+      put(k, pack(w));
     }
   }
 #pragma unroll
@@ -873,17 +877,22 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, BPC * (BM / WM) * 
 // features, so even M = 1 spreads the code stream over N / 16 blocks.
 // v_mfma_i32_16x16x64_i8 with the codes as the first operand (16 features x
 // 64 k) and a group of 16 tokens as the second.  K is cut in chunks of 256
-// (16 code words per feature); in a chunk, lane l loads the 4 words
-// 4 (l / 16) .. 4 (l / 16) + 3 of feature l % 16 (one 16-byte load) and MFMA j
-// takes word j, i.e. k = 16 (4 (l / 16) + j) .. + 15, with the 16 int8
-// activations of token l % 16 at the same k.  Chunks are dealt round-robin to
-// the 8 waves; their int32 partial sums meet in LDS.
+// (16 code words per feature), dealt round-robin to the 8 waves, whose int32 partial
+// sums meet in LDS.  In MFMA j of a chunk, lane l supplies k = 64 j + 16 (l / 16) .. + 15 of
+// feature and token l % 16.
+//   Activations: every block reads all of them, 16 M K bytes per CU and round, which is what
+// bounds the kernel.  The quantiser writes them in fragment order (xq_tile_at), so a load is
+// 1 KB of consecutive bytes; read from token rows (16 pieces of 64 bytes per load) a compute
+// unit took in 34 B/ns, whatever was in flight, and 48 x 6912 -> 2560 took 12.0 us against
+// 5.7 (128 tokens: 27.5 against 10.1).  The next token group's fragments are loaded while
+// the current one's products run.
+//   Codes: a lane loads 4 consecutive words of its feature (one 16-byte load) and the four
+// lane groups exchange them (a 4 x 4 transpose by lane swaps), so that group g holds word
+// 4 j + g for MFMA j.
 // Accumulator (16 x 16, 4 values per lane): token l % 16, features
 // 4 (l / 16) .. 4 (l / 16) + 3.  Segment boundaries are multiples of 16.
 // ---------------------------------------------------------------------------
-constexpr int kGemvMaxM = 128;
-
-template <typename TY, int MODE, bool CVEC, int G, int CPW>
+template <typename TY, int MODE, bool CVEC, int G>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
     k_gemv_i8(const int8_t* __restrict__ xq, const float* __restrict__ s,
               const uint32_t* __restrict__ codes, int64_t M, int64_t K, int64_t N, GemmOut out,
@@ -897,77 +906,51 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
   const int nchunk = (int)((KW + 15) / 16);
   const int ng = (int)((M + 15) / 16);
   const int fr = lane & 15, g = lane >> 4;
-  const bool row_ok = n0 + fr < N;
-  const uint32_t* crow = codes + (row_ok ? n0 + fr : 0) * KW;
-  // Every load below reads a clamped in-bounds address and out-of-range values are
-  // zeroed afterwards; the only branches around loads are wave-uniform, so all the
-  // loads of a pass are in flight together.
+  const uint32_t* crow = codes + (n0 + fr < N ? n0 + fr : 0) * KW;
   v4i acc[G];
 #pragma unroll
   for (int tg = 0; tg < G; ++tg) acc[tg] = v4i{0, 0, 0, 0};
-  // code words of chunk c (zero outside the matrix)
-  auto cload = [&](int c, uint32_t* cw) __attribute__((always_inline)) {
-    const int64_t w0 = (int64_t)c * 16 + 4 * g;        // first code word of this lane
-    if (CVEC) {                                        // KW % 4 == 0: 4 words or none
+  const v4i* xl = reinterpret_cast<const v4i*>(xq) + lane;
+  for (int c = wid; c < nchunk; c += NW) {
+    // word 4 j + g of the chunk's 16 in cw[j] (anything past K: the activations are zero
+    // there; features past N only feed accumulators that are not stored)
+    uint32_t cw[4];
+    if (CVEC) {                                          // KW % 4 == 0: 4 words or none
+      const int64_t w0 = (int64_t)c * 16 + 4 * g;
       const v4u v = *reinterpret_cast<const v4u*>(crow + (w0 < KW ? w0 : 0));
-      const bool ok = row_ok && w0 < KW;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cw[j] = ok ? v[j] : 0u;
+      for (int j = 0; j < 4; ++j) cw[j] = v[j];
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const uint32_t v = crow[w0 + j < KW ? w0 + j : 0];
-        cw[j] = (row_ok && w0 + j < KW) ? v : 0u;
+        const int64_t w = (int64_t)c * 16 + 4 * j + g;
+        cw[j] = crow[w < KW ? w : 0];
       }
     }
-  };
-  // activations of token group tg at this lane's 4 k chunks of chunk c (zero outside)
-  auto xload = [&](int c, int tg, v4i* b) __attribute__((always_inline)) {
-    const int64_t kb = ((int64_t)c * 16 + 4 * g) * 16;
-    const int64_t m = 16 * tg + fr;
-    const int8_t* xr = xq + (m < M ? m : 0) * K;
+    v4i b[2][4];
+    auto xload = [&](int tg, v4i* o) __attribute__((always_inline)) {
+      const v4i* p = xl + ((int64_t)tg * nchunk + c) * 256;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t k = kb + 16 * j;
-      b[j] = *reinterpret_cast<const v4i*>(xr + (k < K ? k : 0));
-      if (!(m < M && k < K)) b[j] = v4i{0, 0, 0, 0};
+      for (int j = 0; j < 4; ++j) o[j] = p[64 * j];
+    };
+    xload(0, b[0]);
+    if (CVEC) {
+      const auto a = __builtin_amdgcn_permlane32_swap(cw[0], cw[2], false, false);
+      const auto e = __builtin_amdgcn_permlane32_swap(cw[1], cw[3], false, false);
+      const auto x = __builtin_amdgcn_permlane16_swap(a[0], e[0], false, false);
+      const auto y = __builtin_amdgcn_permlane16_swap(a[1], e[1], false, false);
+      cw[0] = x[0]; cw[1] = x[1]; cw[2] = y[0]; cw[3] = y[1];
     }
-  };
-  auto mfma4 = [&](const v4i* a, const v4i* b, v4i& acc_) __attribute__((always_inline)) {
+    v4i w4[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc_ = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[j], b[j], acc_, 0, 0, 0);
-  };
-  // Passes of up to CPW chunks per wave (CPW * 2048 k per pass): every code load of a
-  // pass is issued first, then the activations of each token group, so a pass costs
-  // one memory round trip.  Chunk indices are wave-uniform: chunks beyond the matrix
-  // issue no loads and contribute nothing.
-  for (int c0 = wid; c0 < nchunk; c0 += CPW * NW) {
-    uint32_t cw[CPW][4];
-#pragma unroll
-    for (int i = 0; i < CPW; ++i) {
-      if (c0 + NW * i < nchunk) {
-        cload(c0 + NW * i, cw[i]);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cw[i][j] = 0u;
-      }
-    }
+    for (int j = 0; j < 4; ++j) w4[j] = unpack16(cw[j]);
 #pragma unroll
     for (int tg = 0; tg < G; ++tg) {
       if (tg < ng) {
-        v4i b[CPW][4];
+        if (tg + 1 < G && tg + 1 < ng) xload(tg + 1, b[(tg + 1) & 1]);
 #pragma unroll
-        for (int i = 0; i < CPW; ++i)
-          if (c0 + NW * i < nchunk) xload(c0 + NW * i, tg, b[i]);
-#pragma unroll
-        for (int i = 0; i < CPW; ++i) {
-          if (c0 + NW * i < nchunk) {
-            v4i a4[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a4[j] = unpack16(cw[i][j]);
-            mfma4(a4, b[i], acc[tg]);
-          }
-        }
+        for (int j = 0; j < 4; ++j)
+          acc[tg] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w4[j], b[tg & 1][j], acc[tg], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1408,12 +1391,20 @@ hipError_t launch_gemv1_fused(const void* x, termezo_dtype xdt, const uint32_t* 
 
 // ===========================================================================
 hipError_t launch_act_quant(const void* x, termezo_dtype xdt, int64_t M, int64_t K, int8_t* xq,
-                            float* s, int32_t* rs, hipStream_t st) {
-  if (xdt == TERMEZO_F32)
-    hipLaunchKernelGGL(k_act_quant<float>, dim3(M), dim3(256), 0, st, (const float*)x, K, xq, s, rs);
-  else
-    hipLaunchKernelGGL(k_act_quant<uint16_t>, dim3(M), dim3(256), 0, st, (const uint16_t*)x, K, xq,
-                       s, rs);
+                            float* s, int32_t* rs, bool tiled, int n_cu, hipStream_t st) {
+  // one wave per row, walking the rows of a resident grid (8192 x 2560: 13.9 us, a block per
+  // row 20.9; 389 x 2560: 3.9 against 4.9), except for few long rows, where four waves share
+  // a row's latency (48 x 6912: 5.2 against 5.5 alone, but 0.5 us more with the kernel after)
+  if (K <= kRowMaxK && (K <= 2560 || M >= 4 * (int64_t)n_cu))
+    return launch_row_quant(x, xdt, M, K, xq, s, rs, tiled, n_cu, st);
+#define TMZ_AQ(T, TI) \
+  hipLaunchKernelGGL((k_act_quant<T, TI>), dim3(M), dim3(256), 0, st, (const T*)x, K, xq, s, rs)
+  if (xdt == TERMEZO_F32) {
+    if (tiled) TMZ_AQ(float, true); else TMZ_AQ(float, false);
+  } else {
+    if (tiled) TMZ_AQ(uint16_t, true); else TMZ_AQ(uint16_t, false);
+  }
+#undef TMZ_AQ
   return hipGetLastError();
 }
 
@@ -1441,7 +1432,7 @@ static hipError_t launch_tile(const int8_t* xq, const float* s, const uint32_t* 
   return hipGetLastError();
 }
 
-// Tile choice: the small-M kernel up to kGemvMaxM tokens.  Outputs that come in whole
+// Tile choice: the small-M kernel for activations in fragment order (tiled).  Outputs that come in whole
 // 16-byte units take the direct-to-LDS kernels: on whole 256 x 256 tiles that fill the n_cu
 // compute units at least once, 128 x 256 tiles, two blocks per compute unit
 // (k_gemm_i8_dma_h), from three rounds of them and always for the SwiGLU gate|up product,
@@ -1471,6 +1462,20 @@ static float edge_cost(const EdgeTile& t, int64_t M, int64_t K, int64_t N, int n
   const int64_t T = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const int64_t cu = n_cu > 0 ? n_cu : 256;
   return t.c0 + t.l * (float)K + (float)((T + cu - 1) / cu - 1) * (t.a + t.b * (float)K);
+}
+
+// Whether the launch takes the small-M kernel, whose activations come in fragment order:
+// up to kGemvMaxM tokens, unless the edge tiles are estimated faster (every block reads all
+// the activations, 1e-5 us per byte and round of blocks: 128 x 2560 -> 6912 9.7 us against
+// 8.2, but 6912 -> 2560 10.1 against 15.3).  A few tokens always do, and outputs without whole
+// units, which the edge tiles do not take; never a row so long that padding it to 16 tokens
+// would take a large buffer.
+bool gemm_tiled_xq(int64_t M, int64_t K, int64_t N, bool units, int n_cu) {
+  if (M > kGemvMaxM || xq_bytes(M, K) > (int64_t)64 << 20) return false;
+  if (M <= 16 || !units) return true;
+  const int64_t cu = n_cu > 0 ? n_cu : 256, rounds = ((N + 15) / 16 + cu - 1) / cu;
+  return 3.0f + (float)rounds * 1e-5f * (float)((M + 15) / 16 * 16 * K) <=
+         edge_cost(kEdge64, M, K, N, n_cu);
 }
 
 // Whole 16-byte output units, segment by segment: what the direct-load kernels need.
@@ -1546,12 +1551,11 @@ static hipError_t launch_edge(const int8_t* xq, const float* s, const int32_t* r
 hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, const uint32_t* codes,
                           int64_t M,
                           int64_t K, int64_t N, const GemmOut& out, termezo_dtype ydt, int mode,
-                          int32_t* acc, int n_cu, hipStream_t st, LaunchEvents ev) {
+                          int32_t* acc, bool tiled, int n_cu, hipStream_t st, LaunchEvents ev) {
   // the direct-load paths read the row sums, four tokens per 16-byte load
-  const bool rs_ok = rs && reinterpret_cast<uintptr_t>(rs) % 16 == 0;
-  if (M > kGemvMaxM && !rs_ok) return hipErrorInvalidValue;
+  if (!rs || reinterpret_cast<uintptr_t>(rs) % 16 != 0) return hipErrorInvalidValue;
   if (mode == kGemmSwiGLU) {
-    if (!gemm_swiglu_ok(M, K, N, ydt, codes) || out.nseg != 2 || out.nstart[1] * 2 != N || acc ||
+    if (tiled || !gemm_swiglu_ok(M, K, N, ydt, codes) || out.nseg != 2 || out.nstart[1] * 2 != N || acc ||
         out.ld[0] % 8 != 0 || reinterpret_cast<uintptr_t>(out.y[0]) % 16 != 0)
       return hipErrorInvalidValue;
     // only tiles whose waves are 64 columns wide, the gate and the up block of 32 features
@@ -1571,40 +1575,41 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
                           st, ev.start, ev.stop, 0, xq, s, rs, codes, M, K, N, out, acc);
     return hipGetLastError();
   }
-  if (M <= kGemvMaxM) {
-    bool seg16 = true;
-    for (int i = 1; i < out.nseg; ++i) seg16 = seg16 && out.nstart[i] % 16 == 0;
-    if (seg16) {
-      const int cvec = (K / 16) % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 16 == 0;
-      const uintptr_t vec = ydt == TERMEZO_F32 ? 16 : 8;   // 4-element store width
-      int yvec = 1;
-      for (int i = 0; i < out.nseg; ++i)
-        yvec = yvec && out.ld[i] % 4 == 0 && reinterpret_cast<uintptr_t>(out.y[i]) % vec == 0;
-      dim3 grid((unsigned)((N + 15) / 16));
-      // up to 16 tokens: one token group, 8192 k per pass; more: 8 groups, 4096 k
-#define TMZ_GEMV(TY, MD, CV)                                                                    \
-  do {                                                                                          \
-    if (M <= 16)                                                                                \
-      hipExtLaunchKernelGGL((k_gemv_i8<TY, MD, CV, 1, 4>), grid, dim3(512), 0, st, ev.start,    \
-                            ev.stop, 0, xq, s, codes, M, K, N, out, yvec, acc);                 \
-    else                                                                                        \
-      hipExtLaunchKernelGGL((k_gemv_i8<TY, MD, CV, kGemvMaxM / 16, 2>), grid, dim3(512), 0, st, \
-                            ev.start, ev.stop, 0, xq, s, codes, M, K, N, out, yvec, acc);       \
-  } while (0)
-      const bool f32 = ydt == TERMEZO_F32, store = mode == kGemmStore;
-      if (cvec) {
-        if (f32) { if (store) TMZ_GEMV(float, kGemmStore, true); else TMZ_GEMV(float, kGemmResidual, true); }
-        else { if (store) TMZ_GEMV(uint16_t, kGemmStore, true); else TMZ_GEMV(uint16_t, kGemmResidual, true); }
-      } else {
-        if (f32) { if (store) TMZ_GEMV(float, kGemmStore, false); else TMZ_GEMV(float, kGemmResidual, false); }
-        else { if (store) TMZ_GEMV(uint16_t, kGemmStore, false); else TMZ_GEMV(uint16_t, kGemmResidual, false); }
-      }
-#undef TMZ_GEMV
-      return hipGetLastError();
+  if (tiled) {
+    if (M > kGemvMaxM) return hipErrorInvalidValue;
+    const int cvec = (K / 16) % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 16 == 0;
+    const uintptr_t vec = ydt == TERMEZO_F32 ? 16 : 8;   // 4-element store width
+    int yvec = 1;
+    for (int i = 0; i < out.nseg; ++i) {
+      if (out.nstart[i] % 16 != 0) return hipErrorInvalidValue;
+      yvec = yvec && out.ld[i] % 4 == 0 && reinterpret_cast<uintptr_t>(out.y[i]) % vec == 0;
     }
+    dim3 grid((unsigned)((N + 15) / 16));
+#define TMZ_GEMVG(TY, MD, CV, GG)                                                                 \
+  hipExtLaunchKernelGGL((k_gemv_i8<TY, MD, CV, GG>), grid, dim3(512), 0, st, ev.start, ev.stop, 0, \
+                        xq, s, codes, M, K, N, out, yvec, acc)
+    // token groups: 16, 32, 64 or 128 tokens
+#define TMZ_GEMV(TY, MD, CV)                            \
+  do {                                                  \
+    if (M <= 16) TMZ_GEMVG(TY, MD, CV, 1);              \
+    else if (M <= 32) TMZ_GEMVG(TY, MD, CV, 2);         \
+    else if (M <= 64) TMZ_GEMVG(TY, MD, CV, 4);         \
+    else TMZ_GEMVG(TY, MD, CV, kGemvMaxM / 16);         \
+  } while (0)
+    const bool f32 = ydt == TERMEZO_F32, store = mode == kGemmStore;
+    if (cvec) {
+      if (f32) { if (store) TMZ_GEMV(float, kGemmStore, true); else TMZ_GEMV(float, kGemmResidual, true); }
+      else { if (store) TMZ_GEMV(uint16_t, kGemmStore, true); else TMZ_GEMV(uint16_t, kGemmResidual, true); }
+    } else {
+      if (f32) { if (store) TMZ_GEMV(float, kGemmStore, false); else TMZ_GEMV(float, kGemmResidual, false); }
+      else { if (store) TMZ_GEMV(uint16_t, kGemmStore, false); else TMZ_GEMV(uint16_t, kGemmResidual, false); }
+    }
+#undef TMZ_GEMV
+#undef TMZ_GEMVG
+    return hipGetLastError();
   }
   const int64_t T = ((M + 255) / 256) * ((N + 255) / 256);
-  if (!units_ok(out, ydt) || !rs_ok) {                     // single outputs: the register-staged kernel
+  if (!units_ok(out, ydt)) {                     // single outputs: the register-staged kernel
     if (T >= 256)
       return launch_tile<256, 256, 128, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
     return launch_tile<128, 128, 64, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
@@ -1654,7 +1659,8 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
 hipError_t launch_bitlinear_gemm(const int8_t* xq, const float* s, const int32_t* rs,
                                  const uint32_t* codes,
                                  const float* beta_dev, int64_t M, int64_t K, int64_t N, void* y,
-                                 termezo_dtype ydt, int32_t* acc, int n_cu, hipStream_t st) {
+                                 termezo_dtype ydt, int32_t* acc, bool tiled, int n_cu,
+                                 hipStream_t st) {
   GemmOut out = {};
   out.nseg = 1;
   out.y[0] = y;
@@ -1662,7 +1668,16 @@ hipError_t launch_bitlinear_gemm(const int8_t* xq, const float* s, const int32_t
   out.beta[0] = beta_dev;
   out.nstart[0] = 0;
   out.nstart[1] = N;
-  return launch_gemm_i8(xq, s, rs, codes, M, K, N, out, ydt, kGemmStore, acc, n_cu, st);
+  return launch_gemm_i8(xq, s, rs, codes, M, K, N, out, ydt, kGemmStore, acc, tiled, n_cu, st);
+}
+
+bool bitlinear_tiled_xq(int64_t M, int64_t K, int64_t N, const void* y, termezo_dtype ydt, int n_cu) {
+  GemmOut out = {};
+  out.nseg = 1;
+  out.y[0] = const_cast<void*>(y);
+  out.ld[0] = N;
+  out.nstart[1] = N;
+  return gemm_tiled_xq(M, K, N, units_ok(out, ydt), n_cu);
 }
 
 }  // namespace tmz

@@ -258,6 +258,15 @@ __device__ __forceinline__ void tile_of_block(int64_t nb_m, int64_t nb_n, int64_
   tile_of_linear(xcd_linear(blockIdx.x, nb_m * nb_n), nb_m, nb_n, tm, tn);
 }
 
+// Byte offset of x_q[m][k] in fragment order, the layout the small-M kernel reads: groups of
+// 16 tokens, chunks of 256 k (whole ones: zeros past K), in a chunk four 1 KB pieces of 64 k,
+// in a piece 16 bytes of each token for each run of 16 k.
+__host__ __device__ __forceinline__ int64_t xq_tile_chunks(int64_t K) { return (K + 255) / 256; }
+__device__ __forceinline__ int64_t xq_tile_at(int64_t m, int64_t k, int64_t K) {
+  return ((m >> 4) * xq_tile_chunks(K) + (k >> 8)) * 4096 + (((k >> 4) & 15) << 8) + ((m & 15) << 4) +
+         (k & 15);
+}
+
 // silu(g) * u as the decoder evaluates it (hardware exp2 and reciprocal), shared by the
 // SwiGLU row kernel and the SwiGLU GEMM epilogue so the two give identical results.
 __device__ __forceinline__ float silu_mul(float g, float u) {

@@ -294,7 +294,20 @@ hipError_t launch_mse(const float* y, const float* t, int64_t n, double* acc, fl
 constexpr int64_t kRsPad = 256;
 inline int64_t rs_entries(int64_t M) { return (M + kRsPad - 1) / kRsPad * kRsPad; }
 hipError_t launch_act_quant(const void* x, termezo_dtype xdt, int64_t M, int64_t K, int8_t* xq,
-                            float* s, int32_t* rs, hipStream_t st);
+                            float* s, int32_t* rs, bool tiled, int n_cu, hipStream_t st);
+// Up to kGemvMaxM tokens a GEMM may take the small-M kernel, which reads x_q in fragment order
+// (tiled quantiser output) from a buffer of xq_bytes(M, K): gemm_tiled_xq says for which
+// shapes it is the faster one (units: the outputs come in whole 16-byte units), and the caller
+// hands the choice to the quantiser and to launch_gemm_i8.
+constexpr int kGemvMaxM = 128;
+bool gemm_tiled_xq(int64_t M, int64_t K, int64_t N, bool units, int n_cu);
+inline int64_t xq_bytes(int64_t M, int64_t K) {
+  return M <= kGemvMaxM ? (M + 15) / 16 * 16 * ((K + 255) / 256 * 256) : M * K;
+}
+// The decoder's row kernel for the same (rows of at most kRowMaxK values, K % 8 == 0).
+constexpr int64_t kRowMaxK = 8192;
+hipError_t launch_row_quant(const void* x, termezo_dtype xdt, int64_t M, int64_t K, int8_t* xq,
+                            float* xs, int32_t* xrs, bool tiled, int n_cu, hipStream_t st);
 // Optional timing of one GEMM launch: non-null events take the start and the end of the
 // kernel's own execution (hipExtLaunchKernel), not the time around the launch.
 struct LaunchEvents {
@@ -302,8 +315,8 @@ struct LaunchEvents {
 };
 hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs,
                           const uint32_t* codes, int64_t M, int64_t K, int64_t N,
-                          const GemmOut& out, termezo_dtype ydt, int mode, int32_t* acc, int n_cu,
-                          hipStream_t st, LaunchEvents ev = LaunchEvents());
+                          const GemmOut& out, termezo_dtype ydt, int mode, int32_t* acc, bool tiled,
+                          int n_cu, hipStream_t st, LaunchEvents ev = LaunchEvents());
 // One token with the activation quantisation fused in (no x_q, scale or row-sum
 // buffers): gemv1_fused_ok(M, K) tells whether it applies.
 bool gemv1_fused_ok(int64_t M, int64_t K);
@@ -320,7 +333,9 @@ hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* c
 bool gemm_swiglu_ok(int64_t M, int64_t K, int64_t N, termezo_dtype ydt, const uint32_t* codes);
 hipError_t launch_bitlinear_gemm(const int8_t* xq, const float* s, const int32_t* rs,
                                  const uint32_t* codes, const float* beta_dev, int64_t M, int64_t K, int64_t N,
-                                 void* y, termezo_dtype ydt, int32_t* acc, int n_cu,
+                                 void* y, termezo_dtype ydt, int32_t* acc, bool tiled, int n_cu,
                                  hipStream_t st);
+// gemm_tiled_xq for the single output y of launch_bitlinear_gemm.
+bool bitlinear_tiled_xq(int64_t M, int64_t K, int64_t N, const void* y, termezo_dtype ydt, int n_cu);
 
 }  // namespace tmz

@@ -154,12 +154,21 @@ __device__ __forceinline__ uint4 pack8(const float v[8]) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Chunk idx (8 int8 values) of row m: in the row, or in the small-M kernel's fragment order
+// (TILED; then up to whole 256-k chunks, zeros past K).
+template <bool TILED>
+__device__ __forceinline__ void put_xq(int8_t* xq, int64_t m, int64_t K, int idx, uint32_t w0,
+                                       uint32_t w1) {
+  const int64_t at = TILED ? xq_tile_at(m, (int64_t)idx * 8, K) : m * K + (int64_t)idx * 8;
+  *reinterpret_cast<uint2*>(xq + at) = make_uint2(w0, w1);
+}
+
 // Long bf16 rows: the row stays in registers as packed bf16 (4 registers per chunk:
 // the input, or for the SwiGLU the rounded product, both bf16 numbers); the RMSNorm
 // output is recomputed from it where it is needed, with the same operations.  (For
 // rows of up to 8 chunks per lane the fp32 copy below leaves enough waves per SIMD
 // and measured faster.)
-template <int MODE, bool WEIGHTED, int CH>
+template <int MODE, bool WEIGHTED, int CH, bool TILED>
 __device__ __forceinline__ void row_bf16(const uint16_t* __restrict__ x,
                                          const uint16_t* __restrict__ u, int64_t m, int64_t K,
                                          float eps, int8_t* xq, float* xs, int32_t* xrs,
@@ -252,7 +261,9 @@ __device__ __forceinline__ void row_bf16(const uint16_t* __restrict__ x,
         w0 |= ((uint32_t)(uint8_t)q0) << (8 * j);
         w1 |= ((uint32_t)(uint8_t)q1) << (8 * j);
       }
-      *reinterpret_cast<uint2*>(xq + m * K + idx * 8) = make_uint2(w0, w1);
+      put_xq<TILED>(xq, m, K, idx, w0, w1);
+    } else if (TILED && idx < 32 * xq_tile_chunks(K)) {
+      put_xq<TILED>(xq, m, K, idx, 0u, 0u);
     }
   }
   qs = wsum_i(qs);
@@ -261,7 +272,7 @@ __device__ __forceinline__ void row_bf16(const uint16_t* __restrict__ x,
 
 // The same row work on a bf16 row already in registers (packed, 8 values per chunk):
 // modes other than kRowSwiGLU.
-template <int MODE, bool WEIGHTED, int CH>
+template <int MODE, bool WEIGHTED, int CH, bool TILED>
 __device__ __forceinline__ void row_bf16_held(const uint4 (&raw)[CH], const uint16_t* __restrict__ u,
                                               int64_t m, int64_t K, float eps, int8_t* xq,
                                               float* xs, int32_t* xrs, uint16_t* xf) {
@@ -338,7 +349,9 @@ __device__ __forceinline__ void row_bf16_held(const uint4 (&raw)[CH], const uint
         w0 |= ((uint32_t)(uint8_t)q0) << (8 * j);
         w1 |= ((uint32_t)(uint8_t)q1) << (8 * j);
       }
-      *reinterpret_cast<uint2*>(xq + m * K + idx * 8) = make_uint2(w0, w1);
+      put_xq<TILED>(xq, m, K, idx, w0, w1);
+    } else if (TILED && idx < 32 * xq_tile_chunks(K)) {
+      put_xq<TILED>(xq, m, K, idx, 0u, 0u);
     }
   }
   qs = wsum_i(qs);
@@ -350,7 +363,7 @@ __device__ __forceinline__ void row_bf16_held(const uint4 (&raw)[CH], const uint
 // current row is worked on, so a wave with two rows has both in flight.  (With one row
 // per wave the 8192 rows of a step took about 1.3 rounds of resident waves, the last
 // one mostly idle.)
-template <int MODE, bool WEIGHTED, int CH>
+template <int MODE, bool WEIGHTED, int CH, bool TILED>
 __global__ void __launch_bounds__(256) k_row_pf(const uint16_t* __restrict__ x,
                                                 const uint16_t* __restrict__ u, int64_t M,
                                                 int64_t K, float eps, int8_t* xq, float* xs,
@@ -375,13 +388,13 @@ __global__ void __launch_bounds__(256) k_row_pf(const uint16_t* __restrict__ x,
 #pragma unroll
     for (int c = 0; c < CH; ++c) cur[c] = nxt[c];
     if (m + stride < M) load(m + stride, nxt);
-    row_bf16_held<MODE, WEIGHTED, CH>(cur, u, m, K, eps, xq, xs, xrs, xf);
+    row_bf16_held<MODE, WEIGHTED, CH, TILED>(cur, u, m, K, eps, xq, xs, xrs, xf);
   }
 }
 
 // CH: chunks per lane the row needs at most (the kernel is instantiated for a few
 // row lengths so that the registers holding the row match it).
-template <int MODE, typename T, bool WEIGHTED = false, int CH = kRowChunks>
+template <int MODE, typename T, bool WEIGHTED, int CH, bool TILED>
 __global__ void __launch_bounds__(256) k_row(const T* __restrict__ x, const T* __restrict__ u,
                                              int64_t M, int64_t K, float eps, int8_t* xq,
                                              float* xs, int32_t* xrs, T* xf) {
@@ -389,7 +402,7 @@ __global__ void __launch_bounds__(256) k_row(const T* __restrict__ x, const T* _
   const int64_t m = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (m >= M) return;                       // whole wave
   if constexpr (sizeof(T) == 2 && CH > 8) {   // long rows: half the registers
-    row_bf16<MODE, WEIGHTED, CH>(x, u, m, K, eps, xq, xs, xrs, xf);
+    row_bf16<MODE, WEIGHTED, CH, TILED>(x, u, m, K, eps, xq, xs, xrs, xf);
     return;
   }
   const int nch = (int)(K / 8);
@@ -471,7 +484,9 @@ __global__ void __launch_bounds__(256) k_row(const T* __restrict__ x, const T* _
         w0 |= ((uint32_t)(uint8_t)q0) << (8 * j);
         w1 |= ((uint32_t)(uint8_t)q1) << (8 * j);
       }
-      *reinterpret_cast<uint2*>(xq + m * K + idx * 8) = make_uint2(w0, w1);
+      put_xq<TILED>(xq, m, K, idx, w0, w1);
+    } else if (TILED && idx < 32 * xq_tile_chunks(K)) {
+      put_xq<TILED>(xq, m, K, idx, 0u, 0u);
     }
   }
   qs = wsum_i(qs);
@@ -481,12 +496,12 @@ __global__ void __launch_bounds__(256) k_row(const T* __restrict__ x, const T* _
 // One row kernel launch (4 rows per block), instantiated for the chunks per lane
 // the row length needs: 3 (up to 1536 elements), 5 (2560), 8 (4096), 14 (7168),
 // else kRowChunks.
-template <int MODE, bool W, int CH>
+template <int MODE, bool W, int CH, bool TILED>
 static unsigned row_pf_grid(int64_t M, int n_cu) {
   static int per_cu = -1;                       // resident blocks per compute unit
   if (per_cu < 0) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_row_pf<MODE, W, CH>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_row_pf<MODE, W, CH, TILED>, 256, 0) !=
             hipSuccess || nb < 1)
       nb = 1;
     per_cu = nb;
@@ -496,9 +511,9 @@ static unsigned row_pf_grid(int64_t M, int n_cu) {
   return (unsigned)(need < cap ? need : cap);
 }
 
-template <int MODE, typename T, bool W = false>
-static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int64_t M, int64_t K,
-                       float eps, int8_t* xq, float* xs, int32_t* xrs, T* xf, int n_cu = 0) {
+template <int MODE, typename T, bool W, bool TILED>
+static void row_launch_as(unsigned grid, hipStream_t s, const T* x, const T* u, int64_t M, int64_t K,
+                          float eps, int8_t* xq, float* xs, int32_t* xrs, T* xf, int n_cu) {
   const int64_t need = (K / 8 + 63) / 64;
   // the prefetching walk measured faster for the quantiser alone (12.7 against 13.1 us at
   // 8192 x 2560, 32.3 against 35.3 us at 8192 x 6912) and for rows of more than 8 chunks per
@@ -506,8 +521,9 @@ static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int
   if constexpr (sizeof(T) == 2 && MODE != kRowSwiGLU) {
     if (n_cu > 0 && need <= 14 && (MODE == kRowQuant || need > 8)) {
 #define TMZ_ROWPF(CHN)                                                                        \
-  hipLaunchKernelGGL((k_row_pf<MODE, W, CHN>), dim3(row_pf_grid<MODE, W, CHN>(M, n_cu)),      \
-                     dim3(256), 0, s, x, u, M, K, eps, xq, xs, xrs, xf)
+  hipLaunchKernelGGL((k_row_pf<MODE, W, CHN, TILED>),                                         \
+                     dim3(row_pf_grid<MODE, W, CHN, TILED>(M, n_cu)), dim3(256), 0, s, x, u, M, \
+                     K, eps, xq, xs, xrs, xf)
       if (need <= 3)
         TMZ_ROWPF(3);
       else if (need <= 5)
@@ -521,7 +537,8 @@ static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int
     }
   }
 #define TMZ_ROW(CHN) \
-  hipLaunchKernelGGL((k_row<MODE, T, W, CHN>), dim3(grid), dim3(256), 0, s, x, u, M, K, eps, xq, xs, xrs, xf)
+  hipLaunchKernelGGL((k_row<MODE, T, W, CHN, TILED>), dim3(grid), dim3(256), 0, s, x, u, M, K, eps, \
+                     xq, xs, xrs, xf)
   if (need <= 3)
     TMZ_ROW(3);
   else if (need <= 5)
@@ -533,6 +550,31 @@ static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int
   else
     TMZ_ROW(kRowChunks);
 #undef TMZ_ROW
+}
+
+template <int MODE, typename T, bool W = false>
+static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int64_t M, int64_t K,
+                       float eps, int8_t* xq, float* xs, int32_t* xrs, T* xf, bool tiled,
+                       int n_cu = 0) {
+  if constexpr (MODE != kRowNormStore) {
+    if (tiled) {
+      row_launch_as<MODE, T, W, true>(grid, s, x, u, M, K, eps, xq, xs, xrs, xf, n_cu);
+      return;
+    }
+  }
+  row_launch_as<MODE, T, W, false>(grid, s, x, u, M, K, eps, xq, xs, xrs, xf, n_cu);
+}
+
+hipError_t launch_row_quant(const void* x, termezo_dtype xdt, int64_t M, int64_t K, int8_t* xq,
+                            float* xs, int32_t* xrs, bool tiled, int n_cu, hipStream_t st) {
+  const unsigned grid = (unsigned)((M + 3) / 4);
+  if (xdt == TERMEZO_BF16)
+    row_launch<kRowQuant, uint16_t>(grid, st, (const uint16_t*)x, (const uint16_t*)nullptr, M, K, 0.0f,
+                                    xq, xs, xrs, (uint16_t*)nullptr, tiled, n_cu);
+  else
+    row_launch<kRowQuant, float>(grid, st, (const float*)x, (const float*)nullptr, M, K, 0.0f, xq, xs,
+                                 xrs, (float*)nullptr, tiled);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -1812,7 +1854,8 @@ termezo_status model_reserve(termezo_model* m, int64_t M, int S) {
   A(&m->g, M * c.d_ffn * es);
   A(&m->u, M * c.d_ffn * es);
   A(&m->xf, M * c.d_model * es);
-  A((void**)&m->xq, M * kmax);
+  // row-major, or in fragment order for the small calls that this reservation also serves
+  A((void**)&m->xq, std::max(M * kmax, xq_bytes(std::min<int64_t>(M, kGemvMaxM), kmax)));
   A((void**)&m->xs, M * 4);
   A((void**)&m->xrs, rs_entries(M) * 4);
   A((void**)&m->pmax, M * nvt * 4);
@@ -2101,13 +2144,19 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
                        c->d_err);
   chk(hipGetLastError());
   const unsigned rowg = (unsigned)((M + 3) / 4);
+  // the layout of the quantised activations that each projection's GEMM takes (whole output
+  // units: every width is a multiple of 16)
+  const bool t_qkv = gemm_tiled_xq(M, d, dq + 2 * dkv, true, c->n_cu),
+             t_o = gemm_tiled_xq(M, dq, d, true, c->n_cu),
+             t_gu = gemm_tiled_xq(M, d, 2 * F, true, c->n_cu),
+             t_d = gemm_tiled_xq(M, F, d, true, c->n_cu);
   // RMSNorm (weight row wr of the norm weights, one when there are none), then
   // the quantiser, or stored (the LM-head input)
-  auto rmsq = [&](int8_t* xq, float* xs, void* xf, int wr) {
+  auto rmsq = [&](int8_t* xq, float* xs, void* xf, int wr, bool tiled) {
 #define TMZ_NORM(T, MD, W)                                                                   \
   row_launch<MD, T, W>(rowg, s, (const T*)m->h,                                              \
                        nrm ? (const T*)nrm + (int64_t)wr * d : (const T*)nullptr, M, d,      \
-                       cf.norm_eps, xq, xs, m->xrs, (T*)xf, c->n_cu)
+                       cf.norm_eps, xq, xs, m->xrs, (T*)xf, tiled, c->n_cu)
     if (bf) {
       if (xf) {
         if (nrm) TMZ_NORM(uint16_t, kRowNormStore, true); else TMZ_NORM(uint16_t, kRowNormStore, false);
@@ -2128,7 +2177,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     const int l0 = 7 * blk;
     const LayerHost* Ls = &c->layers[l0];
     // attention sub-block
-    rmsq(m->xq, m->xs, nullptr, 2 * blk);
+    rmsq(m->xq, m->xs, nullptr, 2 * blk, t_qkv);
     GemmOut o3 = {};
     o3.nseg = 3;
     o3.y[0] = m->q; o3.ld[0] = dq; o3.beta[0] = betas + l0;
@@ -2136,7 +2185,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     o3.y[2] = m->v; o3.ld[2] = dkv; o3.beta[2] = betas + l0 + 2;
     o3.nstart[0] = 0; o3.nstart[1] = dq; o3.nstart[2] = dq + dkv; o3.nstart[3] = dq + 2 * dkv;
     chk(launch_gemm_i8(m->xq, m->xs, m->xrs, codes + Ls[0].code_off, M, d, dq + 2 * dkv, o3, adt,
-                       kGemmStore, nullptr, c->n_cu, s,
+                       kGemmStore, nullptr, t_qkv, c->n_cu, s,
                        span_kernel(m, 0, 2.0 * M * d * (dq + 2 * dkv))));
     if (!bf) {   // bf16: the rotation is applied inside the attention kernel
       const unsigned rg = (unsigned)std::min<int64_t>(
@@ -2150,21 +2199,21 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     span_end(m, sp, s);
     if (bf)
       row_launch<kRowQuant, uint16_t>(rowg, s, (const uint16_t*)m->attn, (const uint16_t*)nullptr,
-                                      M, dq, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr,
+                                      M, dq, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, t_o,
                                       c->n_cu);
     else
       row_launch<kRowQuant, float>(rowg, s, (const float*)m->attn, (const float*)nullptr, M, dq,
-                                   0.0f, m->xq, m->xs, m->xrs, (float*)nullptr);
+                                   0.0f, m->xq, m->xs, m->xrs, (float*)nullptr, t_o);
     chk(hipGetLastError());
     GemmOut oo = {};
     oo.nseg = 1;
     oo.y[0] = m->h; oo.ld[0] = d; oo.beta[0] = betas + l0 + 3;
     oo.nstart[0] = 0; oo.nstart[1] = d;
     chk(launch_gemm_i8(m->xq, m->xs, m->xrs, codes + Ls[3].code_off, M, dq, d, oo, adt, kGemmResidual,
-                       nullptr, c->n_cu, s,
+                       nullptr, t_o, c->n_cu, s,
                        span_kernel(m, 0, 2.0 * M * dq * d)));
     // MLP sub-block
-    rmsq(m->xq, m->xs, nullptr, 2 * blk + 1);
+    rmsq(m->xq, m->xs, nullptr, 2 * blk + 1, t_gu);
     GemmOut o2 = {};
     o2.nseg = 2;
     o2.y[0] = m->g; o2.ld[0] = F; o2.beta[0] = betas + l0 + 4;
@@ -2172,29 +2221,30 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     o2.nstart[0] = 0; o2.nstart[1] = F; o2.nstart[2] = 2 * F;
     // gate|up with the SwiGLU in the epilogue where the direct-load path applies (the
     // product lands in g), else the two projections and the SwiGLU row kernel
-    const bool fused = gemm_swiglu_ok(M, d, 2 * F, adt, codes + Ls[4].code_off);
+    const bool fused = !t_gu && gemm_swiglu_ok(M, d, 2 * F, adt, codes + Ls[4].code_off);
     chk(launch_gemm_i8(m->xq, m->xs, m->xrs, codes + Ls[4].code_off, M, d, 2 * F, o2, adt,
-                       fused ? kGemmSwiGLU : kGemmStore, nullptr, c->n_cu, s,
+                       fused ? kGemmSwiGLU : kGemmStore, nullptr, t_gu, c->n_cu, s,
                        span_kernel(m, 0, 2.0 * M * d * 2 * F)));
     if (fused)
       row_launch<kRowQuant, uint16_t>(rowg, s, (const uint16_t*)m->g, (const uint16_t*)nullptr, M,
-                                      F, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, c->n_cu);
+                                      F, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, t_d,
+                                      c->n_cu);
     else if (bf)
       row_launch<kRowSwiGLU, uint16_t>(rowg, s, (const uint16_t*)m->g, (const uint16_t*)m->u, M,
-                                       F, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr);
+                                       F, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, t_d);
     else
       row_launch<kRowSwiGLU, float>(rowg, s, (const float*)m->g, (const float*)m->u, M, F, 0.0f,
-                                    m->xq, m->xs, m->xrs, (float*)nullptr);
+                                    m->xq, m->xs, m->xrs, (float*)nullptr, t_d);
     chk(hipGetLastError());
     GemmOut od = {};
     od.nseg = 1;
     od.y[0] = m->h; od.ld[0] = d; od.beta[0] = betas + l0 + 6;
     od.nstart[0] = 0; od.nstart[1] = d;
     chk(launch_gemm_i8(m->xq, m->xs, m->xrs, codes + Ls[6].code_off, M, F, d, od, adt, kGemmResidual,
-                       nullptr, c->n_cu, s,
+                       nullptr, t_d, c->n_cu, s,
                        span_kernel(m, 0, 2.0 * M * F * d)));
   }
-  rmsq(nullptr, nullptr, m->xf, 2 * cf.n_blocks);
+  rmsq(nullptr, nullptr, m->xf, 2 * cf.n_blocks, false);
   const LaunchEvents ev_lm = span_kernel(m, 2, 2.0 * M * d * cf.vocab);
   if (bf) {
     const unsigned nb = (unsigned)(nvt * ((M + kLmTile - 1) / kLmTile));

@@ -140,8 +140,7 @@ termezo_status ensure_wc_capacity(termezo_ctx* c, int64_t k) {
   return TERMEZO_OK;
 }
 
-termezo_status ensure_xq_capacity(termezo_ctx* c, int64_t M, int64_t K) {
-  const int64_t need = M * K;
+termezo_status ensure_xq_capacity(termezo_ctx* c, int64_t need) {
   if (need > c->xq_cap) {
     dfree(c->d_xq);
     c->xq_cap = 0;
@@ -518,16 +517,19 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
   float* xs = xscale_out;
   termezo_status st = ensure_xs_capacity(c, M);       // the row sums live here in any case
   if (st != TERMEZO_OK) return st;
-  if (!xq) {
-    st = ensure_xq_capacity(c, M, L.d_in);
+  const bool tiled = bitlinear_tiled_xq(M, L.d_in, L.d_out, y, y_dtype, c->n_cu);
+  if (!xq || tiled) {
+    st = ensure_xq_capacity(c, tiled ? xq_bytes(M, L.d_in) : M * L.d_in);
     if (st != TERMEZO_OK) return st;
     xq = c->d_xq;
   }
   if (!xs) xs = c->d_xs;
-  TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, c->stream));
+  if (xq_out && tiled)                                // the caller's copy, row-major
+    TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq_out, xs, c->d_xrs, false, c->n_cu, c->stream));
+  TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->n_cu, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, c->d_xrs, c->d_codes + L.code_off,
                                    c->d_beta_cur + layer, M, L.d_in, L.d_out, y, y_dtype, acc_out,
-                                   c->n_cu, c->stream));
+                                   tiled, c->n_cu, c->stream));
   return TERMEZO_OK;
 }
 
@@ -557,12 +559,19 @@ termezo_status termezo_bitlinear_forward_noalloc(termezo_ctx* c, int32_t layer, 
                 "16 MiB scratch");
   if (!c->noalloc_scratch) return fail(c, TERMEZO_ERR_DEVICE, "no scratch address");
   char* base = static_cast<char*>(c->noalloc_scratch);
+  // fragment order takes whole groups of tokens and K chunks: where they do not fit the
+  // array, the row-major kernels
+  const int64_t tiled_bytes = tmz::xq_bytes(M, L.d_in);
+  const bool tiled = bitlinear_tiled_xq(M, L.d_in, L.d_out, y, y_dtype, c->n_cu) &&
+                     tiled_bytes + xs_bytes + 4 * M <= kNoAllocScratchBytes;
+  const int64_t xq_size = tiled ? tiled_bytes : xq_bytes;   // both multiples of 256
   int8_t* xq = reinterpret_cast<int8_t*>(base);
-  float* xs = reinterpret_cast<float*>(base + xq_bytes);
-  int32_t* xrs = reinterpret_cast<int32_t*>(base + xq_bytes + xs_bytes);
-  TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq, xs, xrs, c->stream));
+  float* xs = reinterpret_cast<float*>(base + xq_size);
+  int32_t* xrs = reinterpret_cast<int32_t*>(base + xq_size + xs_bytes);
+  TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq, xs, xrs, tiled, c->n_cu, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, xrs, c->d_codes + L.code_off, c->d_beta_cur + layer,
-                                   M, L.d_in, L.d_out, y, y_dtype, nullptr, c->n_cu, c->stream));
+                                   M, L.d_in, L.d_out, y, y_dtype, nullptr, tiled, c->n_cu,
+                                   c->stream));
   return TERMEZO_OK;
 }
 

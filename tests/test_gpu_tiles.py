@@ -62,7 +62,12 @@ def _linear(orc, torch, M, K, N, xdt, ydt, inspect):
     (333, 688, 256), (200, 16, 48),          # K not a multiple of 128: zero-padded last step
     (777, 1536, 2568), (1000, 2560, 3848),   # 128-wide tiles
     (2049, 1536, 4104),                      # 256-wide tiles, one row in the last one
-    (150, 256, 37)])                         # no whole output units: register-staged kernel
+    (150, 256, 37),                          # no whole output units: register-staged kernel
+    # small-M kernel (activations in fragment order): one token more than each group count, a
+    # partial K chunk, code rows that are not 16-byte aligned, single outputs
+    (17, 272, 2560), (33, 688, 104), (65, 2560, 264), (128, 1040, 80), (100, 272, 37),
+    (48, 8448, 32),                          # rows beyond the row kernel
+    (120, 256, 8200)])                       # the edge tiles are the faster ones
 @pytest.mark.parametrize("xdt,ydt,inspect", [("bf16", "bf16", False), ("f32", "f32", True)])
 def test_bitlinear_tile_edges(orc, M, K, N, xdt, ydt, inspect):
     torch = _torch()
