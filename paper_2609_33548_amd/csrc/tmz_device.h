@@ -51,6 +51,17 @@ __device__ __forceinline__ U4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, ui
 // m in [sqrt(1/2), sqrt(2)); ln m = 2 atanh((m-1)/(m+1)) by its Taylor series
 // through the 11th power; ln2 split in an exact high part and a low part.
 // ---------------------------------------------------------------------------
+// The correctly rounded quotient n / d for the operands ln_unit has: d = m + 1 in [1.7, 2.5],
+// n = m - 1 zero or at least 2^-24, so nothing needs scaling and no special case occurs.  The
+// reciprocal estimate is refined once, the quotient corrected by its exact residual (equal
+// to the IEEE division for each of the 2^23 mantissas m, checked one by one).
+__device__ __forceinline__ float div_ln(float n, float d) {
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  const float q = n * r;
+  return fmaf(fmaf(-d, q, n), r, q);
+}
+
 __device__ __forceinline__ float ln_unit(float u) {
   uint32_t bits = __float_as_uint(u);
   int ex = int(bits >> 23) - 127;
@@ -61,7 +72,7 @@ __device__ __forceinline__ float ln_unit(float u) {
     ex += 1;
   }
   const float m = __uint_as_float(mb);
-  const float f = __fdiv_rn(m - 1.0f, m + 1.0f);
+  const float f = div_ln(m - 1.0f, m + 1.0f);
   const float f2 = 2.0f * f;
   const float t = f * f;
   float p = fmaf(0x1.745d18p-4f, t, 0x1.c71c72p-4f);  // 1/11, 1/9
@@ -177,6 +188,24 @@ __device__ __forceinline__ uint64_t fix_abs(float w) {
   if (sh <= -24) return 0ull;
   return m >> (-sh);
 }
+
+// The same as a double (exact: the product by 2^36 only moves the exponent): a conversion, a
+// product and a truncation where the bit pattern takes about sixteen operations with 64-bit
+// shifts.  Sums of up to 2^14 such values stay exact.  A NaN or an infinity makes the sum
+// NaN or infinite.
+__device__ __forceinline__ double fix_abs_f64(float w) {
+  return __builtin_trunc((double)fabsf(w) * 0x1p36);
+}
+
+// Whether every value of a kernel was finite and below 4 in magnitude: the largest magnitude
+// catches the finite ones and the infinities, the sums of fix_abs_f64 the NaNs.
+struct RangeCheck {
+  float mx = 0.0f;
+  bool nan = false;
+  __device__ __forceinline__ void value(float v) { mx = fmaxf(mx, fabsf(v)); }
+  __device__ __forceinline__ void sum(double s) { nan |= s != s; }
+  __device__ __forceinline__ bool bad() const { return nan || !(mx < 4.0f); }
+};
 
 // |w| < 4 and finite (4.0f = 0x40800000).
 __device__ __forceinline__ bool in_fix_range(float w) {

@@ -72,9 +72,23 @@ struct SeedList {
   uint64_t s[kMaxK];
   int32_t K;
 };
-// d_scal layout: coefficients a_k at [0, kMaxK), the last single-direction g at kMaxK
-constexpr int kScalG = kMaxK;
-constexpr int kScalLen = kMaxK + 2;
+constexpr int kScalLen = kMaxK;      // d_scal: the last update's coefficients
+
+// Where an update takes its K coefficients from: host values a; with plus non-null device
+// losses (F+_k at plus[k stride], F-_k at minus[k stride], divide: lr / K in place of lr); with
+// device set the coefficients already in d_scal.
+struct UpdateCoefs {
+  const float* a = nullptr;
+  const float* plus = nullptr;
+  const float* minus = nullptr;
+  int stride = 0;
+  float eps = 0.f, lr = 0.f;
+  bool divide = false, device = false;
+};
+
+// Rows of partial |w| sums (see k_perturb_delta): kSumSlots for each of two sums.
+constexpr int kSumSlots = 32;
+__host__ __device__ inline int64_t sum_row_len(int L) { return (L + 15) / 16 * 16; }
 
 // One registered full-precision parameter tensor (theta).
 struct ThetaHost {
@@ -123,6 +137,7 @@ struct termezo_ctx {
   bool snap_valid = false;
   int64_t* d_S_clean = nullptr;
   int64_t* d_S_cur = nullptr;
+  int64_t* d_S_part = nullptr;       // partial sums, cleared by the kernels that take them
   float* d_tau = nullptr;
   float* d_beta = nullptr;
   float* d_tau_cur = nullptr;
@@ -248,34 +263,30 @@ hipError_t launch_copy_i64(int64_t* dst, const int64_t* src, int64_t n, hipStrea
 hipError_t launch_select(termezo_ctx* c, int64_t k0);     // three radix passes -> d_sel
 hipError_t launch_mask_compact_counts(termezo_ctx* c, int inclusive);  // -> act_off
 hipError_t launch_mask_compact_write(termezo_ctx* c, int inclusive);   // -> act
-hipError_t launch_tile_ranges(termezo_ctx* c);            // d_act, d_act_off -> d_tile_act
+// d_act, d_act_off -> d_tile_act; after a shrink (old_off: the offsets before it, total: the
+// new entry count) the offsets of layers without entries are completed first
+hipError_t launch_tile_ranges(termezo_ctx* c, const int64_t* old_off, const int64_t* total);
 // codes of w with tau_cur; with patch, the actives' codes from their perturbed values d_wp
 hipError_t launch_requant(termezo_ctx* c, int patch);
 // Guarded requantisation of a perturbation: layers whose threshold moved less than
 // the frozen weights' distance keep their frozen codes and get only the actives'
-// codes (sparse); the others are re-quantised densely.
-hipError_t launch_requant_guarded(termezo_ctx* c, int force);
+// codes (sparse); the others are re-quantised densely.  take: the sums just left by a
+// perturbation pass (1: one sign, 2: a pair) are taken in first.
+hipError_t launch_requant_guarded(termezo_ctx* c, int force, int take);
 // after a dense requantisation of every layer at tau_cur (mask build): frozen codes refer
 // to tau_cur; every frozen weight is at least xi_lo from it
 hipError_t launch_ref_init(termezo_ctx* c, double xi_lo);
-// after an update: weights leaving the set are frozen at tau_ref (their distance to the new
-// clean threshold exceeds xi0, so to tau_ref at least xi_lo - |tau - tau_ref|)
-hipError_t launch_ref_after_update(termezo_ctx* c, double xi_lo);
+// after an update: the clean sums and thresholds, and the frozen weights' bound (weights
+// leaving the set are frozen at tau_ref; their distance to the new clean threshold exceeds
+// xi0, so to tau_ref at least xi_lo - |tau - tau_ref|)
+hipError_t launch_thresholds_update(termezo_ctx* c, double xi_lo);
 hipError_t launch_perturb_delta(termezo_ctx* c, int64_t k, uint64_t seed, float se, bool pair);
-hipError_t launch_set_coeff(termezo_ctx* c, float a);
-// K host coefficients to d_scal[0 .. K-1]
-hipError_t launch_set_coeffs(termezo_ctx* c, const float* a, int K);
-hipError_t launch_coeff_from_losses(termezo_ctx* c, const float* fp, const float* fm, float eps,
-                                    float lr);
-// a_k = -((lr / K) g_k), g_k = (F+_k - F-_k) / (2 eps) from device losses [2K] (F+_k, F-_k pairs)
 hipError_t launch_es_coeffs(termezo_ctx* c, const float* rewards, int N, float lr,
                             int standardize);
-hipError_t launch_coeffs_multi_from_losses(termezo_ctx* c, const float* losses, int K, float eps,
-                                           float lr);
-// coefficients from d_scal[0 .. K-1]; the updated values of the actives go to d_wp (list order)
-hipError_t launch_update(termezo_ctx* c, int64_t k, const SeedList& seeds);
+// the updated values of the actives go to d_wp (list order), the coefficients to d_scal
+hipError_t launch_update(termezo_ctx* c, int64_t k, const SeedList& seeds, const UpdateCoefs& u);
 // from d_wp (the updated values): d_act -> d_act_tmp, offsets -> tmp
-hipError_t launch_shrink(termezo_ctx* c, int64_t k);
+hipError_t launch_shrink(termezo_ctx* c, int64_t k, const int64_t** total_out);
 hipError_t launch_unpack_layer(termezo_ctx* c, int layer, int8_t* out_dev);
 // list entries [j0, j1): latent values (compact array when from_compact, else the layers)
 hipError_t launch_active_values(termezo_ctx* c, int64_t j0, int64_t j1, void* out, int to_f32,

@@ -177,6 +177,7 @@ void free_all(termezo_ctx* c) {
   dfree(c->d_S_clean);
   dfree(c->d_S_cur);
   dfree(c->d_S_alt);
+  dfree(c->d_S_part);
   dfree(c->d_tau);
   dfree(c->d_beta);
   dfree(c->d_tau_cur);
@@ -293,6 +294,8 @@ termezo_status termezo_create(const termezo_layer* layers, int32_t n_layers,
   chk(dalloc(&c->d_S_clean, n_layers), "alloc");
   chk(dalloc(&c->d_S_cur, n_layers), "alloc");
   chk(dalloc(&c->d_S_alt, n_layers), "alloc");
+  const size_t part_len = (size_t)(2 * kSumSlots * sum_row_len(n_layers));
+  chk(dalloc(&c->d_S_part, part_len), "alloc");
   chk(dalloc(&c->d_tau, n_layers), "alloc");
   chk(dalloc(&c->d_beta, n_layers), "alloc");
   chk(dalloc(&c->d_tau_cur, n_layers), "alloc");
@@ -329,6 +332,8 @@ termezo_status termezo_create(const termezo_layer* layers, int32_t n_layers,
         "copy");
     const int32_t zero = 0;
     chk(hipMemcpy(c->d_err, &zero, sizeof(zero), hipMemcpyHostToDevice), "copy");
+    const std::vector<int64_t> zeros(part_len, 0);
+    chk(hipMemcpy(c->d_S_part, zeros.data(), part_len * sizeof(int64_t), hipMemcpyHostToDevice), "copy");
   }
   if (st != TERMEZO_OK) {
     free_all(c);
@@ -389,7 +394,7 @@ termezo_status termezo_build_mask(termezo_ctx* c, float rho0, float delta, int32
   st = ensure_active_capacity(c, total);
   if (st != TERMEZO_OK) return st;
   TMZ_HIP(c, launch_mask_compact_write(c, inclusive));
-  TMZ_HIP(c, launch_tile_ranges(c));
+  TMZ_HIP(c, launch_tile_ranges(c, nullptr, nullptr));
   // sparse sets: keep the active latents in list order as well (contiguous reads in the
   // perturbation and the update instead of gathers; the update writes both copies)
   c->mirror = false;
@@ -432,6 +437,7 @@ termezo_status termezo_perturb(termezo_ctx* c, uint64_t seed, float eps, int32_t
   if (!finite(eps) || !(eps > 0.0f)) return fail(c, TERMEZO_ERR_INVALID_ARG, "eps must be > 0");
   if (!c->has_mask) return fail(c, TERMEZO_ERR_STATE, "perturb before build_mask");
   const float se = (float)sign * eps;
+  int take = 0;
   if (sign != 0 && c->pair_valid && c->pair_seed == seed && c->pair_eps == eps) {
     // the other sign of a pair: its values and sums came with the first call
     if (sign != c->pair_sign) {
@@ -442,8 +448,7 @@ termezo_status termezo_perturb(termezo_ctx* c, uint64_t seed, float eps, int32_t
   } else {
     c->pair_valid = false;
     if (sign != 0) c->z_valid = false;          // the pair pass below rewrites the draws
-    TMZ_HIP(c, launch_copy_i64(c->d_S_cur, c->d_S_clean, c->L, c->stream));
-    if (sign != 0) TMZ_HIP(c, launch_copy_i64(c->d_S_alt, c->d_S_clean, c->L, c->stream));
+    take = sign != 0 ? 2 : 1;
     TMZ_HIP(c, launch_perturb_delta(c, c->k_bound, seed, se, sign != 0));
     if (sign != 0) {
       c->pair_valid = true;
@@ -454,11 +459,10 @@ termezo_status termezo_perturb(termezo_ctx* c, uint64_t seed, float eps, int32_t
       c->pair_sign = sign;
     }
   }
-  TMZ_HIP(c, launch_thresholds(c, c->d_S_cur, c->d_tau_cur, c->d_beta_cur));
-  // guarded requantisation: the actives' codes only, while no frozen code can change
-  // (every latent re-quantised on request)
+  // thresholds and guarded requantisation: the actives' codes only, while no frozen code can
+  // change (every latent re-quantised on request)
   const int force = !c->compact && c->dense_requant;
-  TMZ_HIP(c, launch_requant_guarded(c, force));
+  TMZ_HIP(c, launch_requant_guarded(c, force, take));
   // theta: both signs of the pair come from one pass, so the second evaluation
   // of a pair (same seed and eps) only switches to the other copy
   if (!c->theta.empty() && sign != 0 &&
@@ -589,22 +593,23 @@ SeedList seed_list(const uint64_t* s, int32_t K) {
   return l;
 }
 
-// Update at the actives with the coefficients already in d_scal, then the new
-// thresholds and the shrink; the compacted list replaces the old one.
-termezo_status finish_update(termezo_ctx* c, const SeedList& seeds, int64_t* k_out) {
-  TMZ_HIP(c, launch_update(c, c->k_bound, seeds));
+// Update at the actives, then the new thresholds and the shrink; the compacted list replaces
+// the old one.
+termezo_status finish_update(termezo_ctx* c, const SeedList& seeds, const UpdateCoefs& coefs,
+                             int64_t* k_out) {
+  TMZ_HIP(c, launch_update(c, c->k_bound, seeds, coefs));
   c->pair_valid = false;
   c->z_valid = false;                          // the shrink below changes the list
   c->theta_pair_valid = false;
   c->theta_sign = 0;
   for (const ThetaHost& t : c->theta) TMZ_HIP(c, launch_theta_update(c, t, seeds));
-  TMZ_HIP(c, launch_thresholds(c, c->d_S_clean, c->d_tau, c->d_beta));
-  TMZ_HIP(c, launch_shrink(c, c->k_bound));
+  TMZ_HIP(c, launch_thresholds_update(c, c->xi_lo));
+  const int64_t* total = nullptr;
+  TMZ_HIP(c, launch_shrink(c, c->k_bound, &total));
   std::swap(c->d_act, c->d_act_tmp);
   std::swap(c->d_act_off, c->d_act_off_tmp);
   if (c->mirror) std::swap(c->d_wc, c->d_wc_tmp);
-  TMZ_HIP(c, launch_tile_ranges(c));
-  TMZ_HIP(c, launch_ref_after_update(c, c->xi_lo));
+  TMZ_HIP(c, launch_tile_ranges(c, c->d_act_off_tmp, total));
   c->codes_valid = false;
   c->pending_perturb = false;
   if (k_out) {
@@ -626,8 +631,9 @@ termezo_status termezo_update(termezo_ctx* c, float proj_grad, float lr, int64_t
     return fail(c, TERMEZO_ERR_INVALID_ARG, "projected gradient and lr must be finite");
   if (!c->pending_perturb) return fail(c, TERMEZO_ERR_STATE, "update without a perturbation");
   const float a = -(lr * proj_grad);
-  TMZ_HIP(c, launch_set_coeff(c, a));
-  return finish_update(c, one_seed(c->last_seed), k_out);
+  UpdateCoefs u;
+  u.a = &a;
+  return finish_update(c, one_seed(c->last_seed), u, k_out);
 }
 
 termezo_status termezo_update_from_losses(termezo_ctx* c, const float* loss_plus,
@@ -637,8 +643,12 @@ termezo_status termezo_update_from_losses(termezo_ctx* c, const float* loss_plus
   if (!finite(eps) || !(eps > 0.0f) || !finite(lr))
     return fail(c, TERMEZO_ERR_INVALID_ARG, "eps must be > 0 and lr finite");
   if (!c->pending_perturb) return fail(c, TERMEZO_ERR_STATE, "update without a perturbation");
-  TMZ_HIP(c, launch_coeff_from_losses(c, loss_plus, loss_minus, eps, lr));
-  return finish_update(c, one_seed(c->last_seed), nullptr);
+  UpdateCoefs u;
+  u.plus = loss_plus;
+  u.minus = loss_minus;
+  u.eps = eps;
+  u.lr = lr;
+  return finish_update(c, one_seed(c->last_seed), u, nullptr);
 }
 
 termezo_status termezo_update_multi(termezo_ctx* c, const uint64_t* seeds, const float* proj_grads,
@@ -654,8 +664,9 @@ termezo_status termezo_update_multi(termezo_ctx* c, const uint64_t* seeds, const
   float a[kMaxK];
   const float cK = lr / (float)K;
   for (int32_t q = 0; q < K; ++q) a[q] = -(cK * proj_grads[q]);
-  TMZ_HIP(c, launch_set_coeffs(c, a, K));
-  return finish_update(c, seed_list(seeds, K), k_out);
+  UpdateCoefs u;
+  u.a = a;
+  return finish_update(c, seed_list(seeds, K), u, k_out);
 }
 
 termezo_status termezo_update_multi_from_losses(termezo_ctx* c, const uint64_t* seeds,
@@ -667,8 +678,14 @@ termezo_status termezo_update_multi_from_losses(termezo_ctx* c, const uint64_t* 
   if (!finite(eps) || !(eps > 0.0f) || !finite(lr))
     return fail(c, TERMEZO_ERR_INVALID_ARG, "eps must be > 0 and lr finite");
   if (!c->pending_perturb) return fail(c, TERMEZO_ERR_STATE, "update without a perturbation");
-  TMZ_HIP(c, launch_coeffs_multi_from_losses(c, losses, K, eps, lr));
-  return finish_update(c, seed_list(seeds, K), nullptr);
+  UpdateCoefs u;
+  u.plus = losses;
+  u.minus = losses + 1;
+  u.stride = 2;
+  u.eps = eps;
+  u.lr = lr;
+  u.divide = true;
+  return finish_update(c, seed_list(seeds, K), u, nullptr);
 }
 
 // Evolution strategies on the mask: the coefficients a_n = (lr / N) Rt_n (Rt: the
@@ -704,8 +721,9 @@ termezo_status termezo_es_update(termezo_ctx* c, const uint64_t* seeds, const fl
     a[n] = cN * rt[n];
     if (!finite(a[n])) return fail(c, TERMEZO_ERR_INVALID_ARG, "ES coefficient is not finite");
   }
-  TMZ_HIP(c, launch_set_coeffs(c, a, N));
-  return finish_update(c, seed_list(seeds, N), k_out);
+  UpdateCoefs u;
+  u.a = a;
+  return finish_update(c, seed_list(seeds, N), u, k_out);
 }
 
 termezo_status termezo_es_update_from_rewards(termezo_ctx* c, const uint64_t* seeds,
@@ -717,7 +735,9 @@ termezo_status termezo_es_update_from_rewards(termezo_ctx* c, const uint64_t* se
   if (!finite(lr)) return fail(c, TERMEZO_ERR_INVALID_ARG, "lr must be finite");
   if (!c->pending_perturb) return fail(c, TERMEZO_ERR_STATE, "update without a perturbation");
   TMZ_HIP(c, launch_es_coeffs(c, rewards, N, lr, standardize ? 1 : 0));
-  return finish_update(c, seed_list(seeds, N), nullptr);
+  UpdateCoefs u;
+  u.device = true;
+  return finish_update(c, seed_list(seeds, N), u, nullptr);
 }
 
 termezo_status termezo_compact(termezo_ctx* c) {
@@ -779,6 +799,7 @@ termezo_status termezo_memory_footprint(termezo_ctx* c, int64_t* library_bytes,
   b += cap * (4 + 4 + 4 + 4 + 4) + c->blk_cap * 8 + c->flag_cap * 8;  // lists, w' of both
                                                                     // signs, z, shrink
   b += L * 8;                                                    // |w| sums of the other sign
+  b += 2 * (int64_t)kSumSlots * sum_row_len(c->L) * 8;             // partial sums
   if (c->mirror) b += 2 * c->wc_cap * dsz;                       // active latents (list order)
   b += (int64_t)kHistBins * 8 + (int64_t)sizeof(SelectState) + 4 * 8 + kScalLen * 4 + 4;
   b += c->xq_cap + (c->xs_cap + rs_entries(c->xs_cap)) * 4;                                // activation-quant scratch

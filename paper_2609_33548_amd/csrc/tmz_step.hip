@@ -78,6 +78,19 @@ __device__ unsigned long long block_sum_u64(unsigned long long v, unsigned long 
   return r;
 }
 
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ long long wave_incl_scan_i64(long long v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t lo = __shfl_up((uint32_t)v, off, 64);
+    const uint32_t hi = __shfl_up((uint32_t)((unsigned long long)v >> 32), off, 64);
+    const long long u = (long long)(((unsigned long long)hi << 32) | lo);
+    if (lane >= off) v += u;
+  }
+  return v;
+}
+
 // Exclusive prefix sum over a 256-thread block of int64 values; returns the
 // exclusive prefix and writes the block total to *total.
 __device__ long long block_excl_scan_i64(long long v, long long* lds, long long* total) {
@@ -112,21 +125,43 @@ __device__ __forceinline__ void load_offsets(int64_t* aoff, const int64_t* act_o
   __syncthreads();
 }
 
-// Flush a per-lane (layer, delta) partial into S[layer]: one atomic per wave
-// when every active lane holds the same layer, per-lane atomics otherwise.
-__device__ __forceinline__ void flush_delta(long long* S, int layer, long long d, bool valid) {
-  const unsigned long long vm = __ballot(valid);
-  if (vm == 0ull) return;
-  const int first = __shfl(layer, __builtin_ffsll((long long)vm) - 1, 64);
-  const bool uniform = __ballot(valid && layer != first) == 0ull;
-  if (uniform) {
-    const long long t = wave_sum_i64(valid ? d : 0);
-    if ((threadIdx.x & 63) == 0 && t != 0)
-      atomicAdd((unsigned long long*)&S[first], (unsigned long long)t);
-  } else if (valid && d != 0) {
-    atomicAdd((unsigned long long*)&S[layer], (unsigned long long)d);
+// Per-layer sums of the actives' |w| changes.  A block adds up its own in LDS (kSpan layers
+// from the one its range starts in) and then adds them to one of kSumSlots rows of partial
+// sums, which the threshold kernels add up and clear: atomics on one address take about 7 ns
+// each on this part, one after another, and with one per wave on the layer's sum they bound
+// these passes (both signs of 6.95e7 actives: 65,000 atomics, 464 us, 330 this way, the update
+// 457 and 235; of 2.8e5: 2,200 atomics, 21 and 11 us; of 5.5e5: 35.6 and 12.7 us).
+constexpr int kSpan = 16;
+struct BlockSums {
+  unsigned long long* lds;                       // [kSpan]
+  int64_t* row;                                  // this block's row of partial sums
+  int base;                                      // first layer of the LDS sums
+  __device__ __forceinline__ void add(int layer, long long d) const {
+    if (d == 0) return;
+    const int o = layer - base;
+    if (o < kSpan)
+      atomicAdd(&lds[o], (unsigned long long)d);
+    else
+      atomicAdd((unsigned long long*)&row[layer], (unsigned long long)d);
   }
-}
+  // a lane's last partial: one addition per wave where every lane holds the same layer
+  __device__ __forceinline__ void add_wave(int layer, long long d, bool valid) const {
+    const unsigned long long vm = __ballot(valid);
+    if (vm == 0ull) return;
+    const int first = __shfl(layer, __builtin_ffsll((long long)vm) - 1, 64);
+    if (__ballot(valid && layer != first) == 0ull) {
+      const long long t = wave_sum_i64(valid ? d : 0);
+      if ((threadIdx.x & 63) == 0) add(first, t);
+    } else if (valid) {
+      add(layer, d);
+    }
+  }
+  // all threads call, after every addition and a barrier
+  __device__ __forceinline__ void flush() const {
+    if (threadIdx.x < kSpan && lds[threadIdx.x] != 0)
+      atomicAdd((unsigned long long*)&row[base + threadIdx.x], lds[threadIdx.x]);
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Fixed-point |w| sums, one contiguous range of tiles per block.
@@ -174,10 +209,47 @@ __global__ void k_thresholds(const int64_t* S, const int64_t* n, float delta, fl
                              float* beta, int L) {
   const int l = blockIdx.x * blockDim.x + threadIdx.x;
   if (l >= L) return;
-  const double gamma = ((double)S[l] * 0x1p-36) / (double)n[l];
-  const double b = gamma + (double)delta;
+  const double b = ((double)S[l] * 0x1p-36) / (double)n[l] + (double)delta;
   beta[l] = (float)b;
   tau[l] = (float)(0.5 * b);
+}
+
+// Partial |w| sums: kSumSlots rows of the L layers (rows of whole 128-byte lines) for each of
+// two sums.  A block adds to row blockIdx % kSumSlots.
+__device__ __forceinline__ int64_t* sum_row(int64_t* part, int L, int which) {
+  const int64_t ld = sum_row_len(L);
+  return part + ((int64_t)which * kSumSlots + blockIdx.x % kSumSlots) * ld;
+}
+// The layer's partial sums added up; the rows are cleared for the next pass.
+__device__ __forceinline__ int64_t take_sum(int64_t* part, int L, int which, int l) {
+  const int64_t ld = sum_row_len(L);
+  int64_t* p = part + (int64_t)which * kSumSlots * ld + l;
+  int64_t t = 0;
+#pragma unroll 16
+  for (int i = 0; i < kSumSlots; ++i) t += p[i * ld];
+  for (int i = 0; i < kSumSlots; ++i) p[i * ld] = 0;
+  return t;
+}
+__device__ __forceinline__ double layer_scale(int64_t S, int64_t n, float delta) {
+  return ((double)S * 0x1p-36) / (double)n + (double)delta;
+}
+
+// After an update: the clean sums take the update's changes, new clean thresholds; and the
+// frozen weights' bound: a weight leaving the set has fp32 distance above xi0 to the new
+// clean threshold tau, so it lies at least xi_lo - |tau - tau_ref| from tau_ref (its code is
+// written at tau_ref by the shrink).
+__global__ void __launch_bounds__(64) k_thresholds_update(DevState st, int64_t* part, float delta,
+                                                          double xi_lo) {
+  const int l = blockIdx.x * 64 + threadIdx.x;
+  if (l >= st.L) return;
+  const int64_t S = st.S_clean[l] + take_sum(part, st.L, 0, l);
+  st.S_clean[l] = S;
+  const double b = layer_scale(S, st.n[l], delta);
+  const float tau = (float)(0.5 * b);
+  st.beta[l] = (float)b;
+  st.tau[l] = tau;
+  if (st.mref[l] >= 0.0)
+    st.mref[l] = fmin(st.mref[l], xi_lo - fabs((double)tau - (double)st.tau_ref[l]));
 }
 
 __global__ void k_fill_u64(unsigned long long* p, int64_t n, unsigned long long v) {
@@ -384,11 +456,28 @@ __global__ void __launch_bounds__(256) k_mask_write(DevState st, const SelectSta
 // Per-tile active ranges: tile_act[t] = first position of the active list
 // whose element lies in tile t or a later tile; tile_act[T] = k.  One thread
 // per tile, binary search in its layer's part of the list.
+//   After a shrink (old_off non-null) the new offsets are first completed: the shrink wrote
+// those of the layers that had entries, an empty layer takes the next such layer's offset
+// (the new total at the end).  Every block does so in its own LDS copy, the first one also
+// writes the completed offsets (the entries that others read are the ones it leaves alone).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_tile_ranges(DevState st, const uint32_t* act,
-                                                     const int64_t* act_off) {
+                                                     int64_t* act_off, const int64_t* old_off,
+                                                     const int64_t* total) {
   __shared__ int64_t aoff[kMaxLayers + 1];
-  load_offsets(aoff, act_off, st.L);
+  if (old_off) {
+    for (int l = threadIdx.x; l <= st.L; l += blockDim.x) {
+      int n = l;
+      while (n < st.L && old_off[n] == old_off[n + 1]) ++n;
+      const int64_t v = n == st.L ? *total : act_off[n];
+      aoff[l] = v;
+      if (blockIdx.x == 0 && n != l) act_off[l] = v;
+      if (blockIdx.x == 0 && l == st.L) act_off[l] = v;
+    }
+    __syncthreads();
+  } else {
+    load_offsets(aoff, act_off, st.L);
+  }
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t <= st.T;
        t += (int64_t)gridDim.x * blockDim.x) {
     if (t == st.T) {
@@ -569,25 +658,6 @@ __global__ void __launch_bounds__(kRqStream) k_requant_tile(DevState st, const u
   requant_tile<T, PATCH>(st, act, wp, blockIdx.x);
 }
 
-// The tiles of the layers the guard marked for the dense requantisation: dense_off[l]
-// is the position of layer l's first tile in that list (dense_off[L] tiles in all);
-// blocks stride over the list (none when every layer kept its frozen codes).
-template <typename T>
-__global__ void __launch_bounds__(kRqStream) k_requant_list(DevState st, const uint32_t* act,
-                                                            const float* wp,
-                                                            const int64_t* dense_off) {
-  const int64_t total = dense_off[st.L];
-  for (int64_t i = blockIdx.x; i < total; i += gridDim.x) {
-    int lo = 0, hi = st.L - 1;                   // last layer with dense_off <= i
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (dense_off[mid] <= i) lo = mid; else hi = mid - 1;
-    }
-    __syncthreads();                             // the previous tile's LDS words are consumed
-    requant_tile<T, true>(st, act, wp, st.tile0[lo] + (i - dense_off[lo]));
-  }
-}
-
 // The four draws of Philox counter quad q on a stream: one Philox call and one
 // Box-Muller pair per two ids -- the operations of gauss_at, so the values are the same.
 __device__ __forceinline__ void gauss_quad(uint64_t seed, uint64_t q, uint32_t stream, float z[4]) {
@@ -599,8 +669,8 @@ __device__ __forceinline__ void gauss_quad(uint64_t seed, uint64_t q, uint32_t s
 
 // ---------------------------------------------------------------------------
 // Perturbation at the actives: w' = fma(se, z, w), stored compactly; the
-// exact change of the fixed-point |w| sum goes to S_cur (initialised to
-// S_clean by the caller).  Each thread walks kRun consecutive entries.
+// exact change of the fixed-point |w| sum goes to the partial sums.  Each thread walks kRun
+// consecutive entries.
 // ---------------------------------------------------------------------------
 constexpr int kRun = 4;
 
@@ -642,6 +712,21 @@ __device__ __forceinline__ void gather4(const uint16_t* w, const uint32_t i[4], 
     for (int r = 0; r < 4; ++r) v[r] = r < n ? bf16_to_f32(w[i[r]]) : 0.0f;
   }
 }
+// Four values to bf16 storage and back (round to nearest-even, as storage_round; two packed
+// conversions), and the storage of values that are already bf16 numbers (their upper halves).
+__device__ __forceinline__ void round4(const float*, float[4]) {}
+__device__ __forceinline__ void round4(const uint16_t*, float v[4]) {
+  const uint32_t lo = pack_bf16x2(v[0], v[1]), hi = pack_bf16x2(v[2], v[3]);
+  v[0] = __uint_as_float(lo << 16);
+  v[1] = __uint_as_float(lo & 0xFFFF0000u);
+  v[2] = __uint_as_float(hi << 16);
+  v[3] = __uint_as_float(hi & 0xFFFF0000u);
+}
+__device__ __forceinline__ uint2 pack_exact4(const float v[4]) {
+  return make_uint2(__builtin_amdgcn_perm(__float_as_uint(v[1]), __float_as_uint(v[0]), 0x07060302u),
+                    __builtin_amdgcn_perm(__float_as_uint(v[3]), __float_as_uint(v[2]), 0x07060302u));
+}
+// (bf16: v holds bf16 numbers)
 __device__ __forceinline__ void scatter4(float* w, const uint32_t i[4], int n, const float v[4]) {
   if (n == 4 && i[3] == i[0] + 3 && (i[0] & 3u) == 0) {
     *reinterpret_cast<float4*>(w + i[0]) = make_float4(v[0], v[1], v[2], v[3]);
@@ -652,12 +737,10 @@ __device__ __forceinline__ void scatter4(float* w, const uint32_t i[4], int n, c
 }
 __device__ __forceinline__ void scatter4(uint16_t* w, const uint32_t i[4], int n, const float v[4]) {
   if (n == 4 && i[3] == i[0] + 3 && (i[0] & 3u) == 0) {
-    const uint32_t lo = (uint32_t)f32_to_bf16_rne(v[0]) | ((uint32_t)f32_to_bf16_rne(v[1]) << 16);
-    const uint32_t hi = (uint32_t)f32_to_bf16_rne(v[2]) | ((uint32_t)f32_to_bf16_rne(v[3]) << 16);
-    *reinterpret_cast<uint2*>(w + i[0]) = make_uint2(lo, hi);
+    *reinterpret_cast<uint2*>(w + i[0]) = pack_exact4(v);
   } else {
     for (int r = 0; r < 4; ++r)
-      if (r < n) w[i[r]] = f32_to_bf16_rne(v[r]);
+      if (r < n) w[i[r]] = (uint16_t)(__float_as_uint(v[r]) >> 16);
   }
 }
 // Four values to wp[j0 ..]: one 16-byte store for a whole run (8 bytes for bf16
@@ -671,11 +754,9 @@ __device__ __forceinline__ void put4(float* wp, int64_t j0, int n, const float v
 }
 __device__ __forceinline__ void put4(uint16_t* wp, int64_t j0, int n, const float v[4]) {
   if (n == 4) {
-    const uint32_t lo = (uint32_t)f32_to_bf16_rne(v[0]) | ((uint32_t)f32_to_bf16_rne(v[1]) << 16);
-    const uint32_t hi = (uint32_t)f32_to_bf16_rne(v[2]) | ((uint32_t)f32_to_bf16_rne(v[3]) << 16);
-    *reinterpret_cast<uint2*>(wp + j0) = make_uint2(lo, hi);
+    *reinterpret_cast<uint2*>(wp + j0) = pack_exact4(v);
   } else {
-    for (int r = 0; r < n; ++r) wp[j0 + r] = f32_to_bf16_rne(v[r]);
+    for (int r = 0; r < n; ++r) wp[j0 + r] = (uint16_t)(__float_as_uint(v[r]) >> 16);
   }
 }
 
@@ -702,7 +783,7 @@ __device__ __forceinline__ void list4(const uint16_t* wc, int64_t j0, int n, flo
 }
 
 // PAIR: both signs of the perturbation from one pass -- w' at +se to wp with its
-// delta in S_cur, w' at -se to wpm with its delta in S_alt (list order), so the other
+// delta in sum 0, w' at -se to wpm with its delta in sum 1 (list order), so the other
 // sign of the pair needs no generator pass; with zs the draws z themselves go to zs
 // (list order), from which a single-direction update of the same seed reads them
 // instead of drawing again.
@@ -712,28 +793,38 @@ __global__ void __launch_bounds__(256) k_perturb_delta(DevState st,
                                                        const int64_t* act_off, uint64_t seed,
                                                        float se, float* __restrict__ wp,
                                                        const T* __restrict__ wc,
-                                                       float* __restrict__ wpm,
-                                                       int64_t* S_alt, float* __restrict__ zs) {
+                                                       float* __restrict__ wpm, int64_t* part,
+                                                       float* __restrict__ zs) {
   __shared__ int64_t aoff[kMaxLayers + 1];
+  __shared__ unsigned long long bsum[2 * kSpan];
+  if (threadIdx.x < 2 * kSpan) bsum[threadIdx.x] = 0;
   load_offsets(aoff, act_off, st.L);
   const int64_t k = aoff[st.L];
   // Block b owns the contiguous entries [jb, je): a thread's layer changes
-  // rarely, so its partial sum goes out with one atomic per layer change and
-  // one wave-level atomic at the end.
+  // rarely, so its partial sum goes out once per layer change and once, over the
+  // wave, at the end.
   const int64_t per = (k + gridDim.x - 1) / gridDim.x;
   const int64_t chunk = (per + 256 * kRun - 1) / (256 * kRun) * (256 * kRun);
   const int64_t jb = (int64_t)blockIdx.x * chunk, je = min(k, jb + chunk);
-  bool bad = false, any = false;
+  const int base = jb < k ? layer_of(aoff, st.L, jb) : 0;
+  const BlockSums sum0 = {bsum, sum_row(part, st.L, 0), base};
+  const BlockSums sum1 = {bsum + kSpan, sum_row(part, st.L, 1), base};
+  bool any = false;
   int l = -1;
-  long long acc = 0, acc2 = 0;
+  double acc = 0.0, acc2 = 0.0;                // exact: integers below 2^53 (fix_abs_f64)
+  RangeCheck chk;
   GaussCache zc;
   auto flush_layer = [&]() __attribute__((always_inline)) {
     if (any) {
-      atomicAdd((unsigned long long*)&st.S_cur[l], (unsigned long long)acc);
-      if (PAIR) atomicAdd((unsigned long long*)&S_alt[l], (unsigned long long)acc2);
+      chk.sum(acc);
+      sum0.add(l, (long long)acc);
+      if (PAIR) {
+        chk.sum(acc2);
+        sum1.add(l, (long long)acc2);
+      }
     }
-    acc = 0;
-    acc2 = 0;
+    acc = 0.0;
+    acc2 = 0.0;
   };
   // the next run's indices are loaded one iteration ahead
   uint32_t inx[4] = {0u, 0u, 0u, 0u};
@@ -762,13 +853,13 @@ __global__ void __launch_bounds__(256) k_perturb_delta(DevState st,
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         v[r] = se != 0.0f ? fmaf(se, z[r], wv[r]) : wv[r];
-        bad |= !in_fix_range(v[r]);
-        const long long f0 = (long long)fix_abs(wv[r]);
-        acc += (long long)fix_abs(v[r]) - f0;
+        chk.value(v[r]);
+        const double f0 = fix_abs_f64(wv[r]);
+        acc += fix_abs_f64(v[r]) - f0;
         if (PAIR) {
           vm[r] = fmaf(-se, z[r], wv[r]);
-          bad |= !in_fix_range(vm[r]);
-          acc2 += (long long)fix_abs(vm[r]) - f0;
+          chk.value(vm[r]);
+          acc2 += fix_abs_f64(vm[r]) - f0;
         }
       }
       any = true;
@@ -789,13 +880,13 @@ __global__ void __launch_bounds__(256) k_perturb_delta(DevState st,
       if (!wc && !one) wv[r] = load1(reinterpret_cast<const T*>(st.w[l]), i[r]);
       if (se != 0.0f) z[r] = zc.get(seed, (uint64_t)(st.gid0[l] + i[r]));
       v[r] = se != 0.0f ? fmaf(se, z[r], wv[r]) : wv[r];
-      bad |= !in_fix_range(v[r]);
-      const long long f0 = (long long)fix_abs(wv[r]);
-      acc += (long long)fix_abs(v[r]) - f0;
+      chk.value(v[r]);
+      const double f0 = fix_abs_f64(wv[r]);
+      acc += fix_abs_f64(v[r]) - f0;
       if (PAIR) {
         vm[r] = fmaf(-se, z[r], wv[r]);
-        bad |= !in_fix_range(vm[r]);
-        acc2 += (long long)fix_abs(vm[r]) - f0;
+        chk.value(vm[r]);
+        acc2 += fix_abs_f64(vm[r]) - f0;
       }
       any = true;
     }
@@ -803,9 +894,14 @@ __global__ void __launch_bounds__(256) k_perturb_delta(DevState st,
     if (PAIR) put4(wpm, j0, n, vm);
     if (PAIR && zs) put4(zs, j0, n, z);
   }
-  flush_delta((long long*)st.S_cur, l, acc, any);
-  if (PAIR) flush_delta((long long*)S_alt, l, acc2, any);
-  if (bad) atomicOr(st.err, 1);
+  chk.sum(acc);
+  if (PAIR) chk.sum(acc2);
+  sum0.add_wave(l, (long long)acc, any);
+  if (PAIR) sum1.add_wave(l, (long long)acc2, any);
+  if (chk.bad()) atomicOr(st.err, 1);
+  __syncthreads();
+  sum0.flush();
+  if (PAIR) sum1.flush();
 }
 
 // ---------------------------------------------------------------------------
@@ -922,29 +1018,27 @@ __global__ void __launch_bounds__(256) k_theta_update(T* __restrict__ th, int64_
 // Masked update: w_i <- round(fma(a, z_i, w_i)), a = -(lr g); exact delta of
 // the clean fixed-point sum.
 // ---------------------------------------------------------------------------
-__global__ void k_set_coeff(float* scal, float a) {
-  scal[0] = a;
-  scal[kScalG] = 0.0f;
-}
-
-struct CoefList {
+// Where an update's K coefficients come from: host values, the device losses of the K
+// two-point estimates (F+_k, F-_k: a_k = -(c g_k), g_k = (F+_k - F-_k) / (2 eps), c = lr / K, or
+// lr itself for the single-direction call, all fp32, eq. spsa), or coefficients already on the
+// device (evolution strategies).  Every block forms them itself: one launch less, and no
+// dependent pass before the update.
+struct CoefSource {
   float a[kMaxK];
+  const float* plus;                             // losses (null: host values); stride apart
+  const float* minus;
+  const float* dev;                              // ready coefficients (null: none)
+  float* out;                                    // [kMaxK] written by the first block
+  float eps, lr;
+  int stride, divide;                            // divide: c = lr / K
+  __device__ __forceinline__ float coef(int k, int K) const {
+    if (dev) return dev[k];
+    if (!plus) return a[k];
+    const float g = __fdiv_rn(plus[k * stride] - minus[k * stride], 2.0f * eps);
+    const float c = divide ? __fdiv_rn(lr, (float)K) : lr;
+    return -(c * g);
+  }
 };
-__global__ void k_set_coeffs(float* scal, CoefList c, int K) {
-  if ((int)threadIdx.x < K) scal[threadIdx.x] = c.a[threadIdx.x];
-}
-
-// K directions: g_k = (F+_k - F-_k) / (2 eps), a_k = -((lr / K) g_k), all fp32.
-__global__ void k_coeffs_multi_from_losses(const float* losses, int K, float eps, float lr,
-                                           float* scal, int32_t* err) {
-  const int k = threadIdx.x;
-  if (k >= K) return;
-  const float g = __fdiv_rn(losses[2 * k] - losses[2 * k + 1], 2.0f * eps);
-  const float c = __fdiv_rn(lr, (float)K);
-  const float a = -(c * g);
-  scal[k] = a;
-  if (!isfinite(a)) atomicOr(err, 2);
-}
 
 // Evolution strategies on the mask (appendix on RL-based fine-tuning): a_n =
 // (lr / N) Rt_n in fp32, Rt the population z-score of the rewards in fp64 (index
@@ -979,40 +1073,50 @@ __global__ void k_es_coeffs(const float* rewards, int N, float lr, int standardi
   if (!ok) atomicOr(err, 2);
 }
 
-// g = (F+ - F-) / (2 eps) and a = -(lr g), in fp32 (eq. spsa).
-__global__ void k_coeff_from_losses(const float* fp, const float* fm, float eps, float lr,
-                                    float* scal, int32_t* err) {
-  const float g = __fdiv_rn(*fp - *fm, 2.0f * eps);
-  const float a = -(lr * g);
-  scal[0] = a;
-  scal[kScalG] = g;
-  if (!isfinite(a)) atomicOr(err, 2);
-}
-
 // The new values also go, in list order and the latent dtype, to wn (read by the
 // shrink).  With a non-finite coefficient (reported by the coefficient kernel) the
 // latents are left untouched and wn holds their current values.
 template <typename T>
 __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __restrict__ act,
                                                 const int64_t* act_off, SeedList seeds,
-                                                const float* scal, T* __restrict__ wn,
+                                                CoefSource src, T* __restrict__ wn,
                                                 T* __restrict__ wc,
                                                 int write_latents,
-                                                const float* __restrict__ zs) {
+                                                const float* __restrict__ zs, int64_t* part) {
   __shared__ int64_t aoff[kMaxLayers + 1];
+  __shared__ unsigned long long bsum[kSpan];
+  __shared__ float scal[kMaxK];
+  if (threadIdx.x < kSpan) bsum[threadIdx.x] = 0;
+  const int K = seeds.K;
+  if ((int)threadIdx.x < K) {
+    const float c = src.coef(threadIdx.x, K);
+    scal[threadIdx.x] = c;
+    if (blockIdx.x == 0) {                       // kept for the theta updates
+      src.out[threadIdx.x] = c;
+      if (src.plus && !isfinite(c)) atomicOr(st.err, 2);
+    }
+  }
   load_offsets(aoff, act_off, st.L);
   const float a = scal[0];
   const uint64_t seed = seeds.s[0];
-  const int K = seeds.K;
   const bool a_ok = coeffs_ok(scal, K);
   const int64_t k = aoff[st.L];
   const int64_t per = (k + gridDim.x - 1) / gridDim.x;
   const int64_t chunk = (per + 256 * kRun - 1) / (256 * kRun) * (256 * kRun);
   const int64_t jb = (int64_t)blockIdx.x * chunk, je = min(k, jb + chunk);
-  bool bad = false, any = false;
+  const BlockSums sum = {bsum, sum_row(part, st.L, 0), jb < k ? layer_of(aoff, st.L, jb) : 0};
+  bool any = false;
   int l = -1;
-  long long acc = 0;
+  double acc = 0.0;                            // exact: integers below 2^53 (fix_abs_f64)
+  RangeCheck chk;
   GaussCache zc;
+  auto flush_layer = [&]() __attribute__((always_inline)) {
+    if (any) {
+      chk.sum(acc);
+      sum.add(l, (long long)acc);
+    }
+    acc = 0.0;
+  };
   // the next run's indices are loaded one iteration ahead
   uint32_t inx[4] = {0u, 0u, 0u, 0u};
   int nnx = jb + (int64_t)threadIdx.x * kRun < je
@@ -1032,8 +1136,7 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
     if (one && n == 4 && i[3] == i[0] + 3 && (g0 & 3u) == 0) {
       // a whole Philox quad (dense runs): one draw per direction, same fma chain
       if (l != lr) {
-        if (any) atomicAdd((unsigned long long*)&st.S_clean[l], (unsigned long long)acc);
-        acc = 0;
+        flush_layer();
         l = lr;
       }
       T* w = reinterpret_cast<T*>(const_cast<void*>(st.w[lr]));
@@ -1055,14 +1158,15 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
           for (int r = 0; r < 4; ++r) v[r] = fmaf(scal[q], z[r], v[r]);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) nv[r] = storage_round(w, v[r]);
+        for (int r = 0; r < 4; ++r) nv[r] = v[r];
+        round4((T*)nullptr, nv);
         if (wc) put4(wc, j0, 4, nv);
         if (write_latents) scatter4(w, i, 4, nv);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        bad |= !in_fix_range(nv[r]);
-        acc += (long long)fix_abs(nv[r]) - (long long)fix_abs(wv[r]);
+        chk.value(nv[r]);
+        acc += fix_abs_f64(nv[r]) - fix_abs_f64(wv[r]);
       }
       any = true;
       put4(wn, j0, 4, nv);
@@ -1073,8 +1177,7 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
       if (l < 0) {
         l = layer_of(aoff, st.L, j);
       } else if (aoff[l + 1] <= j) {
-        if (any) atomicAdd((unsigned long long*)&st.S_clean[l], (unsigned long long)acc);
-        acc = 0;
+        flush_layer();
         any = false;
         while (aoff[l + 1] <= j) ++l;
       }
@@ -1089,15 +1192,18 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
         if (wc) store1(wc, j, nv[r]);
         if (write_latents && !one) store1(w, i[r], nv[r]);
       }
-      bad |= !in_fix_range(nv[r]);
-      acc += (long long)fix_abs(nv[r]) - (long long)fix_abs(wv[r]);
+      chk.value(nv[r]);
+      acc += fix_abs_f64(nv[r]) - fix_abs_f64(wv[r]);
       any = true;
     }
     if (write_latents && one && a_ok) scatter4(reinterpret_cast<T*>(const_cast<void*>(st.w[lr])), i, n, nv);
     put4(wn, j0, n, nv);
   }
-  flush_delta((long long*)st.S_clean, l, acc, any);
-  if (bad) atomicOr(st.err, 1);
+  chk.sum(acc);
+  sum.add_wave(l, (long long)acc, any);
+  if (chk.bad()) atomicOr(st.err, 1);
+  __syncthreads();
+  sum.flush();
 }
 
 // ---------------------------------------------------------------------------
@@ -1110,16 +1216,29 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
 // codes then refer to tau' and no bound is kept for it (mref < 0: dense until the
 // next mask build).
 // ---------------------------------------------------------------------------
-// One block: need[l] for every layer, then dense_off (the layers needing the dense
+// One block.  First the thresholds of the current codes: with take != 0 a pair pass (or, with
+// take == 1, a single one) has just left its changes of the clean sums in the partial sums,
+// and S_cur and S_alt are formed from them; otherwise S_cur holds the sums.  Then need[l] for
+// every layer and dense_off (the layers needing the dense
 // pass, their tiles listed in layer order).  A layer whose weights are all active has
 // no frozen code and always passes.  force: every layer takes the dense pass.
 // Compact mode (no frozen latents kept): a layer that fails the guard cannot be
 // re-quantised; its frozen codes stay and the deferred error bit 4 is raised.
 __global__ void __launch_bounds__(256) k_guard(DevState st, int force, int64_t* dense_off,
-                                               int compact, const int64_t* act_off) {
+                                               int compact, const int64_t* act_off, int take,
+                                               int64_t* part, int64_t* S_alt, float delta) {
   __shared__ int64_t cnt[kMaxLayers + 1];
+  __shared__ int64_t wtot[4];
   for (int l = threadIdx.x; l < st.L; l += blockDim.x) {
-    const float tc = st.tau_cur[l], tr = st.tau_ref[l];
+    if (take) {
+      const int64_t S0 = st.S_clean[l];
+      st.S_cur[l] = S0 + take_sum(part, st.L, 0, l);
+      if (take > 1) S_alt[l] = S0 + take_sum(part, st.L, 1, l);
+    }
+    const double b = layer_scale(st.S_cur[l], st.n[l], delta);
+    const float tc = (float)(0.5 * b), tr = st.tau_ref[l];
+    st.beta_cur[l] = (float)b;
+    st.tau_cur[l] = tc;
     const bool none_frozen = act_off[l + 1] - act_off[l] == st.n[l];
     const bool pass = tc == tr || none_frozen || fabs((double)tc - (double)tr) < st.mref[l];
     if (compact && !pass) atomicOr(st.err, 4);
@@ -1134,17 +1253,26 @@ __global__ void __launch_bounds__(256) k_guard(DevState st, int force, int64_t* 
     cnt[l] = keep ? 0 : (l + 1 < st.L ? st.tile0[l + 1] : st.T) - st.tile0[l];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {                        // exclusive scan in LDS
-    int64_t run = 0;
-    for (int l = 0; l < st.L; ++l) {
-      const int64_t c = cnt[l];
-      cnt[l] = run;
-      run += c;
+  // exclusive scan over the layers, 256 at a time (wave scans, then the waves' totals)
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  int64_t carry = 0;
+  for (int l0 = 0; l0 < st.L; l0 += 256) {
+    const int l = l0 + threadIdx.x;
+    const int64_t c = l < st.L ? cnt[l] : 0;
+    const int64_t inc = wave_incl_scan_i64(c);
+    if (lane == 63) wtot[wid] = inc;
+    __syncthreads();
+    int64_t before = carry, round = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      before += w < wid ? wtot[w] : 0;
+      round += wtot[w];
     }
-    cnt[st.L] = run;
+    if (l < st.L) dense_off[l] = before + inc - c;
+    carry += round;
+    __syncthreads();
   }
-  __syncthreads();
-  for (int l = threadIdx.x; l <= st.L; l += blockDim.x) dense_off[l] = cnt[l];
+  if (threadIdx.x == 0) dense_off[st.L] = carry;
 }
 
 // After a dense requantisation of every layer at tau_cur (the mask build): every
@@ -1155,16 +1283,6 @@ __global__ void k_ref_init(DevState st, double xi_lo) {
   if (l >= st.L) return;
   st.tau_ref[l] = st.tau_cur[l];
   st.mref[l] = xi_lo;
-}
-
-// After an update: a weight leaving the set has fp32 distance above xi0 to the new
-// clean threshold tau, so it lies at least xi_lo - |tau - tau_ref| from tau_ref
-// (its code is written at tau_ref by the shrink).
-__global__ void k_ref_after_update(DevState st, double xi_lo) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= st.L || st.mref[l] < 0.0) return;
-  const double m = xi_lo - fabs((double)st.tau[l] - (double)st.tau_ref[l]);
-  st.mref[l] = fmin(st.mref[l], m);
 }
 
 // Rewrite the 2-bit code of local index i of layer l (other fields of the word may
@@ -1179,18 +1297,44 @@ __device__ __forceinline__ void set_code(uint32_t* codes, int64_t code_off, uint
   if (diff) atomicXor(wp, diff);
 }
 
+// The tiles of the layers the guard marked for the dense requantisation: dense_off[l]
+// is the position of layer l's first tile in that list (dense_off[L] tiles in all);
+// nb blocks stride over the list (none when every layer kept its frozen codes).
+template <typename T>
+__device__ __forceinline__ void requant_list(const DevState& st, const uint32_t* act, const float* wp,
+                                             const int64_t* dense_off, int64_t b, int64_t nb) {
+  const int64_t total = dense_off[st.L];
+  for (int64_t i = b; i < total; i += nb) {
+    int lo = 0, hi = st.L - 1;                   // last layer with dense_off <= i
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (dense_off[mid] <= i) lo = mid; else hi = mid - 1;
+    }
+    __syncthreads();                             // the previous tile's LDS words are consumed
+    requant_tile<T, true>(st, act, wp, st.tile0[lo] + (i - dense_off[lo]));
+  }
+}
+
 // The actives' codes at their perturbed values, for the layers that kept their frozen
-// codes.  Each thread walks kRun consecutive list entries.  An entry whose code word
+// codes; the blocks from patch_blocks on take the tiles of the others (requant_list), in the
+// same launch.  Each thread walks kRun consecutive list entries.  An entry whose code word
 // holds no other active (its list neighbours lie in other words) is the word's only
 // writer and updates it with a plain read-modify-write; shared words take the atomic.
+template <typename T>
 __global__ void __launch_bounds__(256) k_patch_codes(DevState st, const uint32_t* __restrict__ act,
                                                      const int64_t* act_off,
-                                                     const float* __restrict__ wp) {
+                                                     const float* __restrict__ wp,
+                                                     const int64_t* dense_off, int patch_blocks) {
+  static_assert(kRqStream == 256, "one block size for both parts");
+  if ((int)blockIdx.x >= patch_blocks) {
+    requant_list<T>(st, act, wp, dense_off, (int)blockIdx.x - patch_blocks, gridDim.x - patch_blocks);
+    return;
+  }
   __shared__ int64_t aoff[kMaxLayers + 1];
   load_offsets(aoff, act_off, st.L);
   const int64_t k = aoff[st.L];
   for (int64_t j0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kRun; j0 < k;
-       j0 += (int64_t)gridDim.x * 256 * kRun) {
+       j0 += (int64_t)patch_blocks * 256 * kRun) {
     uint32_t i[kRun + 2];                        // i[0], i[kRun+1]: the run's list neighbours
     const int n = run_entries(act, j0, k, i + 1);
     i[0] = j0 > 0 ? act[j0 - 1] : 0xFFFFFFFFu;
@@ -1218,7 +1362,9 @@ __global__ void __launch_bounds__(256) k_patch_codes(DevState st, const uint32_t
 // actives reads its code words back into LDS (one 16-byte load per thread), rewrites
 // the actives' codes there and stores the words (the frozen codes are reused, so the
 // latents are not read); a fully active tile takes every code from w'; tiles without
-// actives, and the tiles of layers that take the dense pass, are not touched.
+// actives are not touched; the tiles of layers that take the dense pass are requantised from
+// the latents, in the same launch.
+template <typename T>
 __global__ void __launch_bounds__(kRqThreads) k_patch_tiles(DevState st,
                                                             const uint32_t* __restrict__ act,
                                                             const float* __restrict__ wp) {
@@ -1226,8 +1372,12 @@ __global__ void __launch_bounds__(kRqThreads) k_patch_tiles(DevState st,
   const int tid = threadIdx.x;
   const int64_t t = blockIdx.x;
   const int l = st.tile_layer[t];
+  if (st.need[l]) {                              // block-uniform
+    requant_tile<T, true, kRqThreads>(st, act, wp, t);
+    return;
+  }
   const int64_t a0 = st.tile_act[t], a1 = st.tile_act[t + 1];
-  if (st.need[l] || a1 == a0) return;            // block-uniform
+  if (a1 == a0) return;                          // block-uniform
   const int64_t start = st.tile_start[t];
   const int cnt = (int)min((int64_t)kTile, st.n[l] - start);   // a multiple of 16
   const int nw = cnt / 16;
@@ -1391,18 +1541,6 @@ __global__ void __launch_bounds__(256) k_shrink_count(DevState st, const int64_t
 
 // Exclusive scan of the per-block counts in place (one block of 1024 threads,
 // 1024 counts per round, the next round's counts loaded ahead); *total = sum.
-__device__ __forceinline__ long long wave_incl_scan_i64(long long v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t lo = __shfl_up((uint32_t)v, off, 64);
-    const uint32_t hi = __shfl_up((uint32_t)((unsigned long long)v >> 32), off, 64);
-    const long long u = (long long)(((unsigned long long)hi << 32) | lo);
-    if (lane >= off) v += u;
-  }
-  return v;
-}
-
 __global__ void __launch_bounds__(1024) k_blocks_scan(int64_t* blk_cnt, int64_t nb, int64_t* total) {
   __shared__ long long wsum[16];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -1436,14 +1574,27 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_shrink_write(DevState st, const uint32_t* __restrict__ act,
                                                       const int64_t* act_off,
                                                       const T* __restrict__ wn, int per,
-                                                      const int64_t* blk_off,
+                                                      const int64_t* blk_off, int scanned,
+                                                      int64_t* total,
                                                       const uint64_t* __restrict__ flags,
                                                       uint32_t* __restrict__ act_new,
                                                       int64_t* act_off_new, T* wc_new) {
   __shared__ int64_t aoff[kMaxLayers + 1];
   __shared__ int32_t cnt[kShrinkPer];       // kept entries per (r, wave), then their offsets
+  __shared__ unsigned long long red[4];
   for (int i = threadIdx.x; i <= st.L; i += blockDim.x) aoff[i] = act_off[i];
   const int64_t k = act_off[st.L];
+  // entries kept before this block: scanned beforehand, or (few blocks) added up here from
+  // the earlier blocks' counts
+  int64_t boff;
+  if (scanned) {
+    boff = blk_off[blockIdx.x];
+  } else {
+    unsigned long long v = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) v += (unsigned long long)blk_off[i];
+    boff = (int64_t)block_sum_u64(v, red);
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total = boff + blk_off[blockIdx.x];
+  }
   const int64_t base = (int64_t)blockIdx.x * 256 * per;
   const int R = per / 4;
   const uint64_t m = flags[(int64_t)blockIdx.x * 256 + threadIdx.x];
@@ -1469,7 +1620,6 @@ __global__ void __launch_bounds__(256) k_shrink_write(DevState st, const uint32_
   __syncthreads();
   const int64_t j0 = base + 4 * (int64_t)threadIdx.x;
   if (j0 >= k) return;
-  const int64_t boff = blk_off[blockIdx.x];
   int l = layer_of(aoff, st.L, j0);
   int64_t cur = aoff[l], nxt = aoff[l + 1];
   for (int r = 0; r < R; ++r) {
@@ -1507,24 +1657,6 @@ __global__ void __launch_bounds__(256) k_shrink_write(DevState st, const uint32_
       }
     }
   }
-}
-
-// Layers that were empty before the shrink take the next layer's offset (one block:
-// both offset arrays in LDS, the backward pass over the layers there).
-__global__ void __launch_bounds__(256) k_shrink_offsets(const int64_t* act_off,
-                                                        int64_t* act_off_new, int L,
-                                                        const int64_t* total) {
-  __shared__ int64_t o[kMaxLayers + 1], n[kMaxLayers + 1];
-  for (int l = threadIdx.x; l <= L; l += blockDim.x) {
-    o[l] = act_off[l];
-    n[l] = l == L ? *total : act_off_new[l];
-  }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    for (int l = L - 1; l >= 0; --l)
-      if (o[l] == o[l + 1]) n[l] = n[l + 1];
-  __syncthreads();
-  for (int l = threadIdx.x; l <= L; l += blockDim.x) act_off_new[l] = n[l];
 }
 
 // ---------------------------------------------------------------------------
@@ -1710,30 +1842,34 @@ hipError_t launch_requant(termezo_ctx* c, int patch) {
   return hipGetLastError();
 }
 
-hipError_t launch_requant_guarded(termezo_ctx* c, int force) {
+hipError_t launch_requant_guarded(termezo_ctx* c, int force, int take) {
   hipLaunchKernelGGL(k_guard, dim3(1), dim3(256), 0, c->stream, c->dev(), force, c->d_dense_off,
-                     c->compact ? 1 : 0, (const int64_t*)c->d_act_off);
+                     c->compact ? 1 : 0, (const int64_t*)c->d_act_off, take, c->d_S_part, c->d_S_alt,
+                     c->delta);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (force) return launch_requant(c, 1);      // every layer: one block per tile
-  const unsigned g = (unsigned)min(c->T, (int64_t)(c->n_cu > 0 ? 8 * c->n_cu : 2048));
-  if (c->dtype == TERMEZO_F32)
-    hipLaunchKernelGGL((k_requant_list<float>), dim3(g), dim3(kRqStream), 0, c->stream, c->dev(),
-                       c->d_act, c->d_wp, (const int64_t*)c->d_dense_off);
-  else
-    hipLaunchKernelGGL((k_requant_list<uint16_t>), dim3(g), dim3(kRqStream), 0, c->stream,
-                       c->dev(), c->d_act, c->d_wp, (const int64_t*)c->d_dense_off);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (c->k_bound <= 0) return hipSuccess;
+  const bool bf = c->dtype == TERMEZO_BF16;
   // sparse sets: one scattered code-word update per active; above 1/256 active the
-  // code words of the tiles with actives are rewritten whole (0.5 byte per weight)
-  if (c->k_bound * 256 <= c->D)
-    hipLaunchKernelGGL(k_patch_codes, dim3((unsigned)sparse_grid(c->k_bound)), dim3(256), 0,
-                       c->stream, c->dev(), c->d_act, c->d_act_off, c->d_wp);
-  else
-    hipLaunchKernelGGL(k_patch_tiles, dim3((unsigned)c->T), dim3(kRqThreads), 0, c->stream,
-                       c->dev(), c->d_act, c->d_wp);
+  // code words of the tiles with actives are rewritten whole (0.5 byte per weight).  Either
+  // launch also requantises the layers that failed the guard.
+  if (c->k_bound * 256 <= c->D) {
+    const int pb = c->k_bound > 0 ? (int)sparse_grid(c->k_bound) : 0;
+    const int lb = (int)min(c->T, (int64_t)(c->n_cu > 0 ? 8 * c->n_cu : 2048));
+    if (bf)
+      hipLaunchKernelGGL(k_patch_codes<uint16_t>, dim3((unsigned)(pb + lb)), dim3(256), 0, c->stream,
+                         c->dev(), c->d_act, c->d_act_off, c->d_wp, (const int64_t*)c->d_dense_off, pb);
+    else
+      hipLaunchKernelGGL(k_patch_codes<float>, dim3((unsigned)(pb + lb)), dim3(256), 0, c->stream,
+                         c->dev(), c->d_act, c->d_act_off, c->d_wp, (const int64_t*)c->d_dense_off, pb);
+  } else {
+    if (bf)
+      hipLaunchKernelGGL(k_patch_tiles<uint16_t>, dim3((unsigned)c->T), dim3(kRqThreads), 0, c->stream,
+                         c->dev(), c->d_act, c->d_wp);
+    else
+      hipLaunchKernelGGL(k_patch_tiles<float>, dim3((unsigned)c->T), dim3(kRqThreads), 0, c->stream,
+                         c->dev(), c->d_act, c->d_wp);
+  }
   return hipGetLastError();
 }
 
@@ -1743,64 +1879,67 @@ hipError_t launch_ref_init(termezo_ctx* c, double xi_lo) {
   return hipGetLastError();
 }
 
-hipError_t launch_ref_after_update(termezo_ctx* c, double xi_lo) {
-  hipLaunchKernelGGL(k_ref_after_update, dim3((unsigned)((c->L + 255) / 256)), dim3(256), 0,
-                     c->stream, c->dev(), xi_lo);
+hipError_t launch_thresholds_update(termezo_ctx* c, double xi_lo) {
+  hipLaunchKernelGGL(k_thresholds_update, dim3((unsigned)((c->L + 63) / 64)), dim3(64), 0, c->stream,
+                     c->dev(), c->d_S_part, c->delta, xi_lo);
   return hipGetLastError();
 }
 
-hipError_t launch_tile_ranges(termezo_ctx* c) {
+hipError_t launch_tile_ranges(termezo_ctx* c, const int64_t* old_off, const int64_t* total) {
   const int64_t g = max((int64_t)1, min((int64_t)2048, (c->T + 1 + 255) / 256));
   hipLaunchKernelGGL(k_tile_ranges, dim3(g), dim3(256), 0, c->stream, c->dev(), c->d_act,
-                     c->d_act_off);
+                     c->d_act_off, old_off, total);
   return hipGetLastError();
 }
-
 
 hipError_t launch_perturb_delta(termezo_ctx* c, int64_t k, uint64_t seed, float se, bool pair) {
   if (k <= 0) return hipSuccess;
   const int64_t g = sparse_grid(k);
   const void* wcp = c->mirror ? c->d_wc : nullptr;
   float* wpm = pair ? c->d_wpm : nullptr;
-  int64_t* sa = pair ? c->d_S_alt : nullptr;
   float* zs = pair ? c->d_zs : nullptr;
   if (c->dtype == TERMEZO_F32) {
     if (pair)
       hipLaunchKernelGGL((k_perturb_delta<float, true>), dim3(g), dim3(256), 0, c->stream,
                          c->dev(), c->d_act, c->d_act_off, seed, se, c->d_wp,
-                         (const float*)wcp, wpm, sa, zs);
+                         (const float*)wcp, wpm, c->d_S_part, zs);
     else
       hipLaunchKernelGGL((k_perturb_delta<float, false>), dim3(g), dim3(256), 0, c->stream,
                          c->dev(), c->d_act, c->d_act_off, seed, se, c->d_wp,
-                         (const float*)wcp, wpm, sa, zs);
+                         (const float*)wcp, wpm, c->d_S_part, zs);
   } else {
     if (pair)
       hipLaunchKernelGGL((k_perturb_delta<uint16_t, true>), dim3(g), dim3(256), 0, c->stream,
                          c->dev(), c->d_act, c->d_act_off, seed, se, c->d_wp,
-                         (const uint16_t*)wcp, wpm, sa, zs);
+                         (const uint16_t*)wcp, wpm, c->d_S_part, zs);
     else
       hipLaunchKernelGGL((k_perturb_delta<uint16_t, false>), dim3(g), dim3(256), 0, c->stream,
                          c->dev(), c->d_act, c->d_act_off, seed, se, c->d_wp,
-                         (const uint16_t*)wcp, wpm, sa, zs);
+                         (const uint16_t*)wcp, wpm, c->d_S_part, zs);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_set_coeff(termezo_ctx* c, float a) {
-  hipLaunchKernelGGL(k_set_coeff, dim3(1), dim3(1), 0, c->stream, c->d_scal, a);
-  return hipGetLastError();
+static CoefSource coef_source(termezo_ctx* c, const UpdateCoefs& u, int K) {
+  CoefSource s = {};
+  if (u.a)
+    for (int q = 0; q < K && q < kMaxK; ++q) s.a[q] = u.a[q];
+  s.plus = u.plus;
+  s.minus = u.minus;
+  s.dev = u.device ? c->d_scal : nullptr;
+  s.out = c->d_scal;
+  s.eps = u.eps;
+  s.lr = u.lr;
+  s.stride = u.stride;
+  s.divide = u.divide ? 1 : 0;
+  return s;
 }
 
-hipError_t launch_coeff_from_losses(termezo_ctx* c, const float* fp, const float* fm, float eps,
-                                    float lr) {
-  hipLaunchKernelGGL(k_coeff_from_losses, dim3(1), dim3(1), 0, c->stream, fp, fm, eps, lr,
-                     c->d_scal, c->d_err);
-  return hipGetLastError();
-}
-
-hipError_t launch_update(termezo_ctx* c, int64_t k, const SeedList& seeds) {
-  if (k <= 0) return hipSuccess;
+hipError_t launch_update(termezo_ctx* c, int64_t k, const SeedList& seeds, const UpdateCoefs& u) {
+  // an empty set still takes one block: it forms the coefficients of the theta updates and
+  // reports a non-finite one
   const int64_t g = sparse_grid(k);
+  const CoefSource src = coef_source(c, u, seeds.K);
   void* wcp = c->mirror ? c->d_wc : nullptr;
   const int wl = c->compact ? 0 : 1;           // the caller's latents, unless dropped
   // one direction whose draws the pair pass kept for the same active list: read them
@@ -1808,19 +1947,10 @@ hipError_t launch_update(termezo_ctx* c, int64_t k, const SeedList& seeds) {
       (seeds.K == 1 && c->z_valid && c->z_seed == seeds.s[0]) ? c->d_zs : nullptr;
   if (c->dtype == TERMEZO_F32)
     hipLaunchKernelGGL(k_update<float>, dim3(g), dim3(256), 0, c->stream, c->dev(), c->d_act,
-                       c->d_act_off, seeds, (const float*)c->d_scal, c->d_wp, (float*)wcp,
-                       wl, zs);
+                       c->d_act_off, seeds, src, c->d_wp, (float*)wcp, wl, zs, c->d_S_part);
   else
     hipLaunchKernelGGL(k_update<uint16_t>, dim3(g), dim3(256), 0, c->stream, c->dev(), c->d_act,
-                       c->d_act_off, seeds, (const float*)c->d_scal, (uint16_t*)c->d_wp,
-                       (uint16_t*)wcp, wl, zs);
-  return hipGetLastError();
-}
-
-hipError_t launch_set_coeffs(termezo_ctx* c, const float* a, int K) {
-  CoefList cl = {};
-  for (int q = 0; q < K && q < kMaxK; ++q) cl.a[q] = a[q];
-  hipLaunchKernelGGL(k_set_coeffs, dim3(1), dim3(kMaxK), 0, c->stream, c->d_scal, cl, K);
+                       c->d_act_off, seeds, src, (uint16_t*)c->d_wp, (uint16_t*)wcp, wl, zs, c->d_S_part);
   return hipGetLastError();
 }
 
@@ -1831,14 +1961,7 @@ hipError_t launch_es_coeffs(termezo_ctx* c, const float* rewards, int N, float l
   return hipGetLastError();
 }
 
-hipError_t launch_coeffs_multi_from_losses(termezo_ctx* c, const float* losses, int K, float eps,
-                                           float lr) {
-  hipLaunchKernelGGL(k_coeffs_multi_from_losses, dim3(1), dim3(kMaxK), 0, c->stream, losses, K,
-                     eps, lr, c->d_scal, c->d_err);
-  return hipGetLastError();
-}
-
-hipError_t launch_shrink(termezo_ctx* c, int64_t k) {
+hipError_t launch_shrink(termezo_ctx* c, int64_t k, const int64_t** total_out) {
   // entries per thread: 4 .. kShrinkPer, about 2048 blocks for large lists
   int per = 4;
   while (per < kShrinkPer && k > (int64_t)2048 * 256 * per) per *= 2;
@@ -1854,20 +1977,23 @@ hipError_t launch_shrink(termezo_ctx* c, int64_t k) {
     hipLaunchKernelGGL(k_shrink_count<float>, dim3(nb), dim3(256), 0, c->stream, c->dev(),
                        c->d_act_off, (const float*)c->d_wp, c->xi0, per, c->d_blk_cnt,
                        c->d_shrink_flags);
-  hipLaunchKernelGGL(k_blocks_scan, dim3(1), dim3(1024), 0, c->stream, c->d_blk_cnt, nb, total);
-  // offsets of layers without any entry are fixed afterwards
+  // up to 1024 blocks each block of the write pass adds up the counts before it (at most four
+  // per thread) instead of waiting for one more launch (a scan of 272 counts took 2.3 us and
+  // the gap before it); offsets of layers without any entry are fixed with the tile ranges
+  const int scanned = nb > 1024;
+  if (scanned)
+    hipLaunchKernelGGL(k_blocks_scan, dim3(1), dim3(1024), 0, c->stream, c->d_blk_cnt, nb, total);
   if (bf)
     hipLaunchKernelGGL(k_shrink_write<uint16_t>, dim3(nb), dim3(256), 0, c->stream, c->dev(),
                        c->d_act, c->d_act_off, (const uint16_t*)c->d_wp, per, c->d_blk_cnt,
-                       (const uint64_t*)c->d_shrink_flags, c->d_act_tmp, c->d_act_off_tmp,
+                       scanned, total, (const uint64_t*)c->d_shrink_flags, c->d_act_tmp, c->d_act_off_tmp,
                        (uint16_t*)(c->mirror ? c->d_wc_tmp : nullptr));
   else
     hipLaunchKernelGGL(k_shrink_write<float>, dim3(nb), dim3(256), 0, c->stream, c->dev(),
                        c->d_act, c->d_act_off, (const float*)c->d_wp, per, c->d_blk_cnt,
-                       (const uint64_t*)c->d_shrink_flags, c->d_act_tmp, c->d_act_off_tmp,
+                       scanned, total, (const uint64_t*)c->d_shrink_flags, c->d_act_tmp, c->d_act_off_tmp,
                        (float*)(c->mirror ? c->d_wc_tmp : nullptr));
-  hipLaunchKernelGGL(k_shrink_offsets, dim3(1), dim3(256), 0, c->stream, c->d_act_off,
-                     c->d_act_off_tmp, c->L, total);
+  *total_out = total;
   return hipGetLastError();
 }
 
