@@ -667,6 +667,35 @@ __device__ __forceinline__ void gauss_quad(uint64_t seed, uint64_t q, uint32_t s
   box_muller(x.c, x.d, z[2], z[3]);     // ids 4q+2, 4q+3: cos, sin of the pair (x2, x3)
 }
 
+// The draws of four consecutive ids g0 .. g0+3 on stream 0: one quad when they are one, else
+// two Philox calls and the two or three Box-Muller pairs they touch.  (Once one latent of a
+// dense layer has left the set, every later run of four entries straddles two quads; entry by
+// entry these runs took the pair pass of 6.95e7 actives from 330 to about 600 us.)
+__device__ __forceinline__ void gauss_run(uint64_t seed, uint64_t g0, float z[4]) {
+  const uint64_t q = g0 >> 2;
+  const uint32_t s = (uint32_t)g0 & 3u;
+  if (s == 0) {
+    gauss_quad(seed, q, 0u, z);
+    return;
+  }
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  const U4 x = philox10((uint32_t)q, (uint32_t)(q >> 32), 0u, 0u, k0, k1);
+  const U4 y = philox10((uint32_t)(q + 1), (uint32_t)((q + 1) >> 32), 0u, 0u, k0, k1);
+  float c, d;
+  if (s == 1) {
+    box_muller(x.a, x.b, c, z[0]);
+    box_muller(x.c, x.d, z[1], z[2]);
+    box_muller(y.a, y.b, z[3], d);
+  } else if (s == 2) {
+    box_muller(x.c, x.d, z[0], z[1]);
+    box_muller(y.a, y.b, z[2], z[3]);
+  } else {
+    box_muller(x.c, x.d, c, z[0]);
+    box_muller(y.a, y.b, z[1], z[2]);
+    box_muller(y.c, y.d, z[3], d);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Perturbation at the actives: w' = fma(se, z, w), stored compactly; the
 // exact change of the fixed-point |w| sum goes to the partial sums.  Each thread walks kRun
@@ -691,19 +720,31 @@ __device__ __forceinline__ int run_entries(const uint32_t* act, int64_t j0, int6
   return n;
 }
 
-// Latents at four local indices: one load when they are the consecutive,
-// 4-aligned i0 .. i0+3 (dense runs), four gathers otherwise.
+// Sixteen or eight bytes at an address of any element alignment (one access either way).
+template <typename V, typename T>
+__device__ __forceinline__ V load_any(const T* p) {
+  V v;
+  __builtin_memcpy(&v, p, sizeof(V));
+  return v;
+}
+template <typename V, typename T>
+__device__ __forceinline__ void store_any(T* p, V v) {
+  __builtin_memcpy(p, &v, sizeof(V));
+}
+
+// Latents at four local indices: one load when they are consecutive (dense runs), four
+// gathers otherwise.
 __device__ __forceinline__ void gather4(const float* w, const uint32_t i[4], int n, float v[4]) {
-  if (n == 4 && i[3] == i[0] + 3 && (i[0] & 3u) == 0) {
-    const float4 a = *reinterpret_cast<const float4*>(w + i[0]);
+  if (n == 4 && i[3] == i[0] + 3) {
+    const float4 a = load_any<float4>(w + i[0]);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
   } else {
     for (int r = 0; r < 4; ++r) v[r] = r < n ? w[i[r]] : 0.0f;
   }
 }
 __device__ __forceinline__ void gather4(const uint16_t* w, const uint32_t i[4], int n, float v[4]) {
-  if (n == 4 && i[3] == i[0] + 3 && (i[0] & 3u) == 0) {
-    const uint2 a = *reinterpret_cast<const uint2*>(w + i[0]);
+  if (n == 4 && i[3] == i[0] + 3) {
+    const uint2 a = load_any<uint2>(w + i[0]);
     v[0] = __uint_as_float(a.x << 16);
     v[1] = __uint_as_float(a.x & 0xFFFF0000u);
     v[2] = __uint_as_float(a.y << 16);
@@ -728,16 +769,16 @@ __device__ __forceinline__ uint2 pack_exact4(const float v[4]) {
 }
 // (bf16: v holds bf16 numbers)
 __device__ __forceinline__ void scatter4(float* w, const uint32_t i[4], int n, const float v[4]) {
-  if (n == 4 && i[3] == i[0] + 3 && (i[0] & 3u) == 0) {
-    *reinterpret_cast<float4*>(w + i[0]) = make_float4(v[0], v[1], v[2], v[3]);
+  if (n == 4 && i[3] == i[0] + 3) {
+    store_any(w + i[0], make_float4(v[0], v[1], v[2], v[3]));
   } else {
     for (int r = 0; r < 4; ++r)
       if (r < n) w[i[r]] = v[r];
   }
 }
 __device__ __forceinline__ void scatter4(uint16_t* w, const uint32_t i[4], int n, const float v[4]) {
-  if (n == 4 && i[3] == i[0] + 3 && (i[0] & 3u) == 0) {
-    *reinterpret_cast<uint2*>(w + i[0]) = pack_exact4(v);
+  if (n == 4 && i[3] == i[0] + 3) {
+    store_any(w + i[0], pack_exact4(v));
   } else {
     for (int r = 0; r < 4; ++r)
       if (r < n) w[i[r]] = (uint16_t)(__float_as_uint(v[r]) >> 16);
@@ -843,13 +884,13 @@ __global__ void __launch_bounds__(256) k_perturb_delta(DevState st,
     else if (one)
       gather4(reinterpret_cast<const T*>(st.w[lr]), i, n, wv);
     const uint64_t g0 = one ? (uint64_t)(st.gid0[lr] + i[0]) : 0ull;
-    if (one && n == 4 && i[3] == i[0] + 3 && (g0 & 3u) == 0) {
-      // a whole Philox quad (dense runs): one draw, no per-entry layer walk
+    if (one && n == 4 && i[3] == i[0] + 3) {
+      // consecutive ids (dense runs): drawn together, no per-entry layer walk
       if (l != lr) {
         flush_layer();
         l = lr;
       }
-      if (se != 0.0f) gauss_quad(seed, g0 >> 2, 0u, z);
+      if (se != 0.0f) gauss_run(seed, g0, z);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         v[r] = se != 0.0f ? fmaf(se, z[r], wv[r]) : wv[r];
@@ -1133,8 +1174,8 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
     else if (one)
       gather4(reinterpret_cast<const T*>(st.w[lr]), i, n, wv);
     const uint64_t g0 = one ? (uint64_t)(st.gid0[lr] + i[0]) : 0ull;
-    if (one && n == 4 && i[3] == i[0] + 3 && (g0 & 3u) == 0) {
-      // a whole Philox quad (dense runs): one draw per direction, same fma chain
+    if (one && n == 4 && i[3] == i[0] + 3) {
+      // consecutive ids (dense runs): drawn together per direction, same fma chain
       if (l != lr) {
         flush_layer();
         l = lr;
@@ -1148,12 +1189,12 @@ __global__ void __launch_bounds__(256) k_update(DevState st, const uint32_t* __r
           const float4 zz = *reinterpret_cast<const float4*>(zs + j0);
           z[0] = zz.x; z[1] = zz.y; z[2] = zz.z; z[3] = zz.w;
         } else {
-          gauss_quad(seed, g0 >> 2, 0u, z);
+          gauss_run(seed, g0, z);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = fmaf(a, z[r], wv[r]);
         for (int q = 1; q < K; ++q) {
-          gauss_quad(seeds.s[q], g0 >> 2, 0u, z);
+          gauss_run(seeds.s[q], g0, z);
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = fmaf(scal[q], z[r], v[r]);
         }
