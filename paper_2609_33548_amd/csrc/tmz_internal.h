@@ -187,12 +187,13 @@ struct termezo_ctx {
   unsigned long long* d_hist = nullptr;      // kHistBins
   tmz::SelectState* d_sel = nullptr;
   uint32_t* d_tile_cnt = nullptr;            // 2 * T  (less, equal) per tile
-  int64_t* d_tile_out = nullptr;             // T      output offset per tile
   int64_t* d_tile_eqb = nullptr;             // T      equal keys before the tile
   int64_t* d_blk_cnt = nullptr;              // shrink block counts
   int64_t blk_cap = 0;
   uint64_t* d_shrink_flags = nullptr;        // shrink keep flags, one word per thread
   int64_t flag_cap = 0;
+  // pinned host words of the mask build's read-back: the error flag, then the selection state
+  int64_t* h_pin = nullptr;
   double* d_loss = nullptr;                  // loss accumulators
   float* d_scal = nullptr;                   // [0] update coefficient a, [1] g
   int n_cu = 0;                              // compute units of the device
@@ -257,25 +258,25 @@ namespace tmz {
 // Launchers (stream-ordered, no synchronisation).  Return hipSuccess or the
 // launch error.
 hipError_t launch_abs_sum(termezo_ctx* c, int64_t* S_out);
-hipError_t launch_thresholds(termezo_ctx* c, const int64_t* S, float* tau, float* beta);
+// mask build: |w| sums and thresholds (clean and current); selection -> d_sel; codes with the
+// mask's latents marked, tile counts, list positions; the list, wc (nullable: the latents in
+// list order) and the marked latents' codes
+hipError_t launch_build_sums(termezo_ctx* c);
+hipError_t launch_select(termezo_ctx* c, int64_t k0);
+hipError_t launch_codes_count(termezo_ctx* c, int inclusive);
+hipError_t launch_mask_write(termezo_ctx* c, int inclusive, void* wc);
 hipError_t launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipStream_t s);
-hipError_t launch_copy_i64(int64_t* dst, const int64_t* src, int64_t n, hipStream_t s);
-hipError_t launch_select(termezo_ctx* c, int64_t k0);     // three radix passes -> d_sel
-hipError_t launch_mask_compact_counts(termezo_ctx* c, int inclusive);  // -> act_off
-hipError_t launch_mask_compact_write(termezo_ctx* c, int inclusive);   // -> act
 // d_act, d_act_off -> d_tile_act; after a shrink (old_off: the offsets before it, total: the
 // new entry count) the offsets of layers without entries are completed first
 hipError_t launch_tile_ranges(termezo_ctx* c, const int64_t* old_off, const int64_t* total);
-// codes of w with tau_cur; with patch, the actives' codes from their perturbed values d_wp
-hipError_t launch_requant(termezo_ctx* c, int patch);
 // Guarded requantisation of a perturbation: layers whose threshold moved less than
 // the frozen weights' distance keep their frozen codes and get only the actives'
 // codes (sparse); the others are re-quantised densely.  take: the sums just left by a
 // perturbation pass (1: one sign, 2: a pair) are taken in first.
 hipError_t launch_requant_guarded(termezo_ctx* c, int force, int take);
-// after a dense requantisation of every layer at tau_cur (mask build): frozen codes refer
-// to tau_cur; every frozen weight is at least xi_lo from it
-hipError_t launch_ref_init(termezo_ctx* c, double xi_lo);
+// after a mask build: frozen codes refer to tau_cur; every frozen weight is at least xi_lo (from
+// the selected xi0) from it
+hipError_t launch_ref_init(termezo_ctx* c);
 // after an update: the clean sums and thresholds, and the frozen weights' bound (weights
 // leaving the set are frozen at tau_ref; their distance to the new clean threshold exceeds
 // xi0, so to tau_ref at least xi_lo - |tau - tau_ref|)

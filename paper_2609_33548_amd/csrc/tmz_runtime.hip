@@ -79,11 +79,8 @@ size_t dtype_size(termezo_dtype t) {
   return 0;
 }
 
-// Wait for the stream and surface a deferred numeric error.
-termezo_status sync_and_check(termezo_ctx* c) {
-  TMZ_HIP(c, hipStreamSynchronize(c->stream));
-  int32_t err = 0;
-  TMZ_HIP(c, hipMemcpy(&err, c->d_err, sizeof(err), hipMemcpyDeviceToHost));
+// A deferred error word as a status (and cleared on the device).
+termezo_status report_error(termezo_ctx* c, int32_t err) {
   if (err) {
     const int32_t zero = 0;
     TMZ_HIP(c, hipMemcpy(c->d_err, &zero, sizeof(zero), hipMemcpyHostToDevice));
@@ -97,6 +94,14 @@ termezo_status sync_and_check(termezo_ctx* c) {
     return fail(c, (err & ~8) ? TERMEZO_ERR_NUMERIC : TERMEZO_ERR_INVALID_ARG, msg);
   }
   return TERMEZO_OK;
+}
+
+// Wait for the stream and surface a deferred numeric error.
+termezo_status sync_and_check(termezo_ctx* c) {
+  TMZ_HIP(c, hipStreamSynchronize(c->stream));
+  int32_t err = 0;
+  TMZ_HIP(c, hipMemcpy(&err, c->d_err, sizeof(err), hipMemcpyDeviceToHost));
+  return report_error(c, err);
 }
 
 termezo_status ensure_active_capacity(termezo_ctx* c, int64_t k) {
@@ -197,7 +202,6 @@ void free_all(termezo_ctx* c) {
   dfree(c->d_hist);
   dfree(c->d_sel);
   dfree(c->d_tile_cnt);
-  dfree(c->d_tile_out);
   dfree(c->d_tile_eqb);
   dfree(c->d_blk_cnt);
   dfree(c->d_shrink_flags);
@@ -206,6 +210,8 @@ void free_all(termezo_ctx* c) {
   dfree(c->d_xq);
   dfree(c->d_xs);
   dfree(c->d_xrs);
+  if (c->h_pin) (void)hipHostFree(c->h_pin);
+  c->h_pin = nullptr;
   if (c->d_wc) (void)hipFree(c->d_wc);
   if (c->d_wc_tmp) (void)hipFree(c->d_wc_tmp);
   c->d_wc = c->d_wc_tmp = nullptr;
@@ -311,10 +317,10 @@ termezo_status termezo_create(const termezo_layer* layers, int32_t n_layers,
   chk(dalloc(&c->d_hist, kHistBins), "alloc");
   chk(dalloc(&c->d_sel, 1), "alloc");
   chk(dalloc(&c->d_tile_cnt, (size_t)(2 * c->T)), "alloc");
-  chk(dalloc(&c->d_tile_out, (size_t)c->T), "alloc");
   chk(dalloc(&c->d_tile_eqb, (size_t)c->T), "alloc");
   chk(dalloc(&c->d_loss, 4), "alloc");
   chk(dalloc(&c->d_scal, kScalLen), "alloc");
+  chk(hipHostMalloc((void**)&c->h_pin, 64, hipHostMallocDefault), "alloc pinned");
   chk(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device),
       "device attribute");
   if (st == TERMEZO_OK) {
@@ -378,49 +384,46 @@ termezo_status termezo_build_mask(termezo_ctx* c, float rho0, float delta, int32
   c->codes_valid = false;
   c->pending_perturb = false;
   c->delta = delta;
-  TMZ_HIP(c, launch_abs_sum(c, c->d_S_clean));
-  TMZ_HIP(c, launch_thresholds(c, c->d_S_clean, c->d_tau, c->d_beta));
-  termezo_status st = sync_and_check(c);
-  if (st != TERMEZO_OK) return st;
-
-  TMZ_HIP(c, launch_select(c, k0));
-  // counts and offsets first: the inclusive reading may admit more than k0
   const int inclusive = tie_inclusive ? 1 : 0;
-  TMZ_HIP(c, launch_mask_compact_counts(c, inclusive));
-  int64_t total = 0;
-  TMZ_HIP(c, hipMemcpyAsync(&total, c->d_act_off + c->L, sizeof(int64_t), hipMemcpyDeviceToHost,
-                            c->stream));
-  TMZ_HIP(c, hipStreamSynchronize(c->stream));
-  st = ensure_active_capacity(c, total);
+  TMZ_HIP(c, launch_build_sums(c));
+  TMZ_HIP(c, launch_select(c, k0));
+  TMZ_HIP(c, launch_codes_count(c, inclusive));
+  // the exclusive reading admits exactly k0; the inclusive one may admit more
+  int64_t total = k0;
+  if (inclusive) {
+    TMZ_HIP(c, hipMemcpyAsync(&total, c->d_act_off + c->L, sizeof(int64_t), hipMemcpyDeviceToHost,
+                              c->stream));
+    const termezo_status st = sync_and_check(c);
+    if (st != TERMEZO_OK) return st;
+  }
+  termezo_status st = ensure_active_capacity(c, total);
   if (st != TERMEZO_OK) return st;
-  TMZ_HIP(c, launch_mask_compact_write(c, inclusive));
-  TMZ_HIP(c, launch_tile_ranges(c, nullptr, nullptr));
   // sparse sets: keep the active latents in list order as well (contiguous reads in the
   // perturbation and the update instead of gathers; the update writes both copies)
   c->mirror = false;
   if (total > 0 && total * 8 <= c->D) {
     st = ensure_wc_capacity(c, total);
     if (st != TERMEZO_OK) return st;
-    TMZ_HIP(c, launch_active_values(c, 0, total, c->d_wc, 0, 0));
     c->mirror = true;
   }
+  TMZ_HIP(c, launch_mask_write(c, inclusive, c->mirror ? c->d_wc : nullptr));
+  TMZ_HIP(c, launch_ref_init(c));
 
-  // clean codes: current = clean
-  TMZ_HIP(c, launch_copy_i64(c->d_S_cur, c->d_S_clean, c->L, c->stream));
-  TMZ_HIP(c, launch_thresholds(c, c->d_S_cur, c->d_tau_cur, c->d_beta_cur));
-  TMZ_HIP(c, launch_requant(c, 0));
-
-  SelectState sel;
-  TMZ_HIP(c, hipMemcpyAsync(&sel, c->d_sel, sizeof(sel), hipMemcpyDeviceToHost, c->stream));
-  st = sync_and_check(c);
+  // one wait for the whole build: the error word and the selection come back together
+  TMZ_HIP(c, hipMemcpyAsync(c->h_pin, c->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+  TMZ_HIP(c, hipMemcpyAsync(c->h_pin + 1, c->d_sel, sizeof(SelectState), hipMemcpyDeviceToHost,
+                            c->stream));
+  TMZ_HIP(c, hipStreamSynchronize(c->stream));
+  st = report_error(c, *reinterpret_cast<const int32_t*>(c->h_pin));
   if (st != TERMEZO_OK) return st;
+  SelectState sel;
+  std::memcpy(&sel, c->h_pin + 1, sizeof(sel));
   float xi0;
   std::memcpy(&xi0, &sel.prefix, sizeof(float));
   c->xi0 = xi0;
   // every inactive weight has fp32 distance >= xi0 to the clean threshold the codes were
   // just computed with, so an exact distance >= xi0 - ulp(xi0) / 2
   c->xi_lo = (double)xi0 - 0.5 * ((double)std::nextafter(xi0, INFINITY) - (double)xi0);
-  TMZ_HIP(c, launch_ref_init(c, c->xi_lo));
   c->k0 = total;
   c->k_bound = total;
   c->tie_inclusive = inclusive;
@@ -795,7 +798,7 @@ termezo_status termezo_memory_footprint(termezo_ctx* c, int64_t* library_bytes,
   const int64_t dsz = (int64_t)dtype_size(c->dtype);
   int64_t b = c->D / 4;                                          // 2-bit codes
   b += L * (8 * 8 + 4 * 4 + 4 + 8 + 4 + 8) + 3 * (L + 1) * 8;    // per-layer state, offsets
-  b += T * (4 + 8 + 8 + 8 + 8 + 8) + 8;                          // tile tables and scratch
+  b += T * (4 + 8 + 8 + 8 + 8) + 8;                              // tile tables and scratch
   b += cap * (4 + 4 + 4 + 4 + 4) + c->blk_cap * 8 + c->flag_cap * 8;  // lists, w' of both
                                                                     // signs, z, shrink
   b += L * 8;                                                    // |w| sums of the other sign

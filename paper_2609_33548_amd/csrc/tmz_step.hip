@@ -50,6 +50,24 @@ __device__ __forceinline__ float storage_round(const uint16_t*, float v) {
   return bf16_to_f32(f32_to_bf16_rne(v));
 }
 
+// Global-address-space views (the pointers are computed from device tables,
+// so the compiler would otherwise emit FLAT accesses).
+typedef const __attribute__((address_space(1))) v4u gv4u_c;
+typedef __attribute__((address_space(1))) v4u gv4u;
+typedef __attribute__((address_space(1))) uint32_t gu32;
+
+__device__ __forceinline__ void vec_values(const v4u* b, int nvec, float* out, const float*) {
+  for (int v = 0; v < nvec; ++v)
+    for (int i = 0; i < 4; ++i) out[4 * v + i] = __uint_as_float(b[v][i]);
+}
+__device__ __forceinline__ void vec_values(const v4u* b, int nvec, float* out, const uint16_t*) {
+  for (int v = 0; v < nvec; ++v)
+    for (int i = 0; i < 4; ++i) {
+      out[8 * v + 2 * i] = __uint_as_float(b[v][i] << 16);
+      out[8 * v + 2 * i + 1] = __uint_as_float(b[v][i] & 0xFFFF0000u);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Wave / block reductions (wave64).
 // ---------------------------------------------------------------------------
@@ -166,9 +184,11 @@ struct BlockSums {
 // ---------------------------------------------------------------------------
 // Fixed-point |w| sums, one contiguous range of tiles per block.
 // ---------------------------------------------------------------------------
+// (16-byte chunk c of a tile goes to lane c % 256: a load covers 4 KB of consecutive bytes.)
 template <typename T>
 __global__ void __launch_bounds__(256) k_abs_sum(DevState st, int64_t* S_out, int64_t tpb) {
   __shared__ unsigned long long red[4];
+  constexpr int EPC = 16 / (int)sizeof(T), CPT = kTile / EPC / 256;
   const int64_t t0 = (int64_t)blockIdx.x * tpb;
   const int64_t t1 = min(st.T, t0 + tpb);
   unsigned long long acc = 0;
@@ -185,15 +205,23 @@ __global__ void __launch_bounds__(256) k_abs_sum(DevState st, int64_t* S_out, in
       cur = l;
     }
     const int64_t start = st.tile_start[t];
-    const int64_t cnt = min((int64_t)kTile, st.n[l] - start);
+    const int cnt = (int)min((int64_t)kTile, st.n[l] - start);
     const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
-    for (int64_t e = (int64_t)threadIdx.x * 16; e < cnt; e += 256 * 16) {
-      float v[16];
-      load16(w + e, v);
+    v4u buf[CPT];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        bad |= !in_fix_range(v[j]);
-        acc += fix_abs(v[j]);
+    for (int v = 0; v < CPT; ++v) {
+      const int e = (v * 256 + (int)threadIdx.x) * EPC;
+      buf[v] = *(gv4u_c*)(w + (e < cnt ? e : 0));
+    }
+#pragma unroll
+    for (int v = 0; v < CPT; ++v) {
+      if ((v * 256 + (int)threadIdx.x) * EPC >= cnt) continue;
+      float x[EPC];
+      vec_values(&buf[v], 1, x, (const T*)nullptr);
+#pragma unroll
+      for (int j = 0; j < EPC; ++j) {
+        bad |= !in_fix_range(x[j]);
+        acc += fix_abs(x[j]);
       }
     }
   }
@@ -202,16 +230,6 @@ __global__ void __launch_bounds__(256) k_abs_sum(DevState st, int64_t* S_out, in
     if (threadIdx.x == 0 && s) atomicAdd((unsigned long long*)&S_out[cur], s);
   }
   if (bad) atomicOr(st.err, 1);
-}
-
-// tau = fp32(0.5 (S 2^-36 / n + delta)), beta = fp32(S 2^-36 / n + delta).
-__global__ void k_thresholds(const int64_t* S, const int64_t* n, float delta, float* tau,
-                             float* beta, int L) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= L) return;
-  const double b = ((double)S[l] * 0x1p-36) / (double)n[l] + (double)delta;
-  beta[l] = (float)b;
-  tau[l] = (float)(0.5 * b);
 }
 
 // Partial |w| sums: kSumSlots rows of the L layers (rows of whole 128-byte lines) for each of
@@ -230,8 +248,20 @@ __device__ __forceinline__ int64_t take_sum(int64_t* part, int L, int which, int
   for (int i = 0; i < kSumSlots; ++i) p[i * ld] = 0;
   return t;
 }
+// tau = fp32(0.5 b), beta = fp32(b), b = S 2^-36 / n + delta in fp64.
 __device__ __forceinline__ double layer_scale(int64_t S, int64_t n, float delta) {
   return ((double)S * 0x1p-36) / (double)n + (double)delta;
+}
+
+// Thresholds of a mask build: the clean ones and, equal to them, the current ones.
+__global__ void k_thresholds_build(DevState st, float delta) {
+  const int l = blockIdx.x * blockDim.x + threadIdx.x;
+  if (l >= st.L) return;
+  const int64_t S = st.S_clean[l];
+  const double b = layer_scale(S, st.n[l], delta);
+  st.S_cur[l] = S;
+  st.beta[l] = st.beta_cur[l] = (float)b;
+  st.tau[l] = st.tau_cur[l] = (float)(0.5 * b);
 }
 
 // After an update: the clean sums take the update's changes, new clean thresholds; and the
@@ -258,12 +288,6 @@ __global__ void k_fill_u64(unsigned long long* p, int64_t n, unsigned long long 
     p[i] = v;
 }
 
-__global__ void k_copy_i64(int64_t* dst, const int64_t* src, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
-}
-
 // ---------------------------------------------------------------------------
 // Radix selection of xi0 over the distance keys.  d >= 0, so its fp32 bit
 // pattern is a monotone uint32 key.  Pass p histograms 11/11/10 bits of the
@@ -273,9 +297,15 @@ __device__ __forceinline__ uint32_t dist_key(float w, float tau) {
   return __float_as_uint(fabsf(fabsf(w) - tau));
 }
 
+__device__ __forceinline__ bool key_bin(uint32_t key, int pass, uint32_t prefix, uint32_t* bin) {
+  *bin = pass == 0 ? key >> 21 : (pass == 1 ? (key >> 10) & 0x7FFu : key & 0x3FFu);
+  return pass == 0 || (pass == 1 ? (key >> 21) == (prefix >> 21) : (key >> 10) == (prefix >> 10));
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_hist(DevState st, int pass, const SelectState* sel,
                                               unsigned long long* hist, int64_t tpb) {
+  constexpr int EPC = 16 / (int)sizeof(T), CPT = kTile / EPC / 256;
   __shared__ uint32_t h[kHistBins];
   for (int i = threadIdx.x; i < kHistBins; i += 256) h[i] = 0;
   __syncthreads();
@@ -286,21 +316,23 @@ __global__ void __launch_bounds__(256) k_hist(DevState st, int pass, const Selec
     const int l = st.tile_layer[t];
     const float tau = st.tau[l];
     const int64_t start = st.tile_start[t];
-    const int64_t cnt = min((int64_t)kTile, st.n[l] - start);
+    const int cnt = (int)min((int64_t)kTile, st.n[l] - start);
     const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
-    for (int64_t e = (int64_t)threadIdx.x * 16; e < cnt; e += 256 * 16) {
-      float v[16];
-      load16(w + e, v);
+    v4u buf[CPT];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const uint32_t key = dist_key(v[j], tau);
-        if (pass == 0) {
-          atomicAdd(&h[key >> 21], 1u);
-        } else if (pass == 1) {
-          if ((key >> 21) == (prefix >> 21)) atomicAdd(&h[(key >> 10) & 0x7FFu], 1u);
-        } else {
-          if ((key >> 10) == (prefix >> 10)) atomicAdd(&h[key & 0x3FFu], 1u);
-        }
+    for (int v = 0; v < CPT; ++v) {
+      const int e = (v * 256 + (int)threadIdx.x) * EPC;
+      buf[v] = *(gv4u_c*)(w + (e < cnt ? e : 0));
+    }
+#pragma unroll
+    for (int v = 0; v < CPT; ++v) {
+      if ((v * 256 + (int)threadIdx.x) * EPC >= cnt) continue;
+      float x[EPC];
+      vec_values(&buf[v], 1, x, (const T*)nullptr);
+#pragma unroll
+      for (int j = 0; j < EPC; ++j) {
+        uint32_t bin;
+        if (key_bin(dist_key(x[j], tau), pass, prefix, &bin)) atomicAdd(&h[bin], 1u);
       }
     }
   }
@@ -309,145 +341,343 @@ __global__ void __launch_bounds__(256) k_hist(DevState st, int pass, const Selec
     if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
 }
 
-// Find the bucket holding the k0-th key, extend the prefix, clear the histogram.
-__global__ void k_select_bucket(SelectState* sel, unsigned long long* hist, int pass) {
-  if (threadIdx.x == 0) {
-    const unsigned long long need = sel->k0 - sel->less;
-    unsigned long long c = 0;
-    uint32_t b = 0;
-    const uint32_t nb = pass == 2 ? 1024u : 2048u;
-    for (b = 0; b < nb; ++b) {
-      if (c + hist[b] >= need) break;
-      c += hist[b];
-    }
-    sel->less += c;
-    const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-    sel->prefix |= b << shift;
-  }
+// ---------------------------------------------------------------------------
+// bf16 latents: a magnitude is one of 2^15 bit patterns, so one pass over the latents that
+// counts them per layer holds everything the build needs to know of the values: the exact
+// |w| sum, and, once the threshold is known, how many latents lie at each distance.  The
+// radix passes then run over the counts.  One block of 16 waves per compute unit with all
+// 2^15 counters in LDS (spread over enough of them that few lanes of a wave meet on one);
+// 1.39e8 latents: 60 us in place of 96 (sums) and 3 x 89 (radix passes over the latents, whose
+// eleven-bit bins crowd the LDS atomics).
+// ---------------------------------------------------------------------------
+constexpr int kMagBins = 1 << 15;
+
+__global__ void __launch_bounds__(1024) k_mag_hist(DevState st, uint32_t* counts, int64_t tpb) {
+  __shared__ uint32_t h[kMagBins];
+  const int tid = threadIdx.x;
+  for (int i = tid; i < kMagBins; i += 1024) h[i] = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < kHistBins; i += blockDim.x) hist[i] = 0;
-}
-
-__global__ void k_select_init(SelectState* sel, unsigned long long k0) {
-  sel->k0 = k0;
-  sel->less = 0;
-  sel->prefix = 0;
-  sel->pad = 0;
-}
-
-// ---------------------------------------------------------------------------
-// Mask compaction: per-tile counts, single-block scan, ordered write.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) k_mask_count(DevState st, const SelectState* sel,
-                                                    uint32_t* tile_cnt) {
-  __shared__ unsigned long long red[4];
-  const uint32_t xi = sel->prefix;
-  for (int64_t t = blockIdx.x; t < st.T; t += gridDim.x) {
+  const int64_t t0 = (int64_t)blockIdx.x * tpb;
+  const int64_t t1 = min(st.T, t0 + tpb);
+  bool bad = false;
+  auto load = [&](int64_t t) __attribute__((always_inline)) {     // one 16-byte chunk per thread
     const int l = st.tile_layer[t];
-    const float tau = st.tau[l];
-    const int64_t start = st.tile_start[t];
-    const int64_t cnt = min((int64_t)kTile, st.n[l] - start);
-    const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
-    uint32_t nl = 0, ne = 0;
-    for (int64_t e = (int64_t)threadIdx.x * 16; e < cnt; e += 256 * 16) {
-      float v[16];
-      load16(w + e, v);
+    const int64_t start = st.tile_start[t], e = (int64_t)tid * 8;
+    const uint16_t* w = reinterpret_cast<const uint16_t*>(st.w[l]) + start;
+    return *(gv4u_c*)(w + (e < st.n[l] - start ? e : 0));
+  };
+  v4u nx = {0u, 0u, 0u, 0u}, nx2 = {0u, 0u, 0u, 0u};
+  if (t0 < t1) nx = load(t0);
+  if (t0 + 1 < t1) nx2 = load(t0 + 1);
+  for (int64_t t = t0; t < t1; ++t) {
+    const v4u b = nx;
+    nx = nx2;
+    if (t + 2 < t1) nx2 = load(t + 2);
+    const int l = st.tile_layer[t];
+    if ((int64_t)tid * 8 < st.n[l] - st.tile_start[t]) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const uint32_t key = dist_key(v[j], tau);
-        nl += key < xi;
-        ne += key == xi;
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t lo = b[i] & 0x7FFFu, hi = (b[i] >> 16) & 0x7FFFu;
+        bad |= max(lo, hi) >= 0x4080u;            // |w| >= 4, infinite or NaN
+        atomicAdd(&h[lo], 1u);
+        atomicAdd(&h[hi], 1u);
       }
     }
-    const unsigned long long s = block_sum_u64(((unsigned long long)ne << 32) | nl, red);
-    if (threadIdx.x == 0) {
-      tile_cnt[2 * t] = (uint32_t)s;
-      tile_cnt[2 * t + 1] = (uint32_t)(s >> 32);
+    if (t + 1 == t1 || st.tile_layer[t + 1] != l) {  // the layer's counts (a layer fits 32 bits)
+      __syncthreads();
+      for (int i = tid; i < kMagBins; i += 1024) {
+        const uint32_t c = h[i];
+        if (c) {
+          atomicAdd(&counts[(int64_t)l * kMagBins + i], c);
+          h[i] = 0;
+        }
+      }
+      __syncthreads();
     }
   }
+  if (bad) atomicOr(st.err, 1);
 }
 
-// One block of 256 threads: per tile, equal-keys-before and output offsets;
-// per layer, the first output position.
-__global__ void __launch_bounds__(256) k_mask_scan(const SelectState* sel, const uint32_t* tile_cnt,
-                                                   const int32_t* tile_layer, int64_t T, int L,
-                                                   int inclusive, int64_t* tile_out,
-                                                   int64_t* tile_eqb, int64_t* act_off) {
-  __shared__ long long lds[256];
-  const int64_t need = (int64_t)(sel->k0 - sel->less);  // equal keys to admit (exact-k)
-  const int64_t per = (T + 255) / 256;
-  const int64_t a = min(T, (int64_t)threadIdx.x * per), b = min(T, a + per);
-  long long tot;
-  long long eq = 0;
-  for (int64_t t = a; t < b; ++t) eq += tile_cnt[2 * t + 1];
-  long long eqb = block_excl_scan_i64(eq, lds, &tot);
-  long long sel_sum = 0;
-  for (int64_t t = a; t < b; ++t) {
-    const long long e = tile_cnt[2 * t + 1];
-    const long long q = inclusive ? e : max(0ll, min(e, (long long)need - eqb));
-    tile_eqb[t] = eqb;
-    sel_sum += (long long)tile_cnt[2 * t] + q;
-    eqb += e;
-  }
-  long long off = block_excl_scan_i64(sel_sum, lds, &tot);
-  for (int64_t t = a; t < b; ++t) {
-    const long long e = tile_cnt[2 * t + 1];
-    const long long q = inclusive ? e : max(0ll, min(e, (long long)need - tile_eqb[t]));
-    tile_out[t] = off;
-    if (t == 0 || tile_layer[t] != tile_layer[t - 1]) act_off[tile_layer[t]] = off;
-    off += (long long)tile_cnt[2 * t] + q;
-  }
-  if (threadIdx.x == 0) act_off[L] = tot;
+// One block per layer: its |w| sum.
+__global__ void __launch_bounds__(256) k_mag_sum(DevState st, const uint32_t* counts) {
+  __shared__ unsigned long long red[4];
+  const uint32_t* c = counts + (int64_t)blockIdx.x * kMagBins;
+  unsigned long long acc = 0;
+  for (int i = threadIdx.x; i < kMagBins; i += 256)
+    acc += (unsigned long long)c[i] * fix_abs(__uint_as_float((uint32_t)i << 16));
+  acc = block_sum_u64(acc, red);
+  if (threadIdx.x == 0) st.S_clean[blockIdx.x] = (int64_t)acc;
 }
 
-// Ordered write: every thread owns 32 consecutive elements of the tile.
+// A radix pass over the counts: 8 blocks per layer.
+__global__ void __launch_bounds__(256) k_mag_pass(DevState st, const uint32_t* counts, int pass,
+                                                  const SelectState* sel, unsigned long long* hist) {
+  __shared__ unsigned long long h[kHistBins];
+  for (int i = threadIdx.x; i < kHistBins; i += 256) h[i] = 0;
+  __syncthreads();
+  const uint32_t prefix = sel->prefix;
+  const int l = blockIdx.x / 8, part = blockIdx.x % 8;
+  const float tau = st.tau[l];
+  const uint32_t* c = counts + (int64_t)l * kMagBins;
+#pragma unroll 4
+  for (int i = part * (kMagBins / 8) + threadIdx.x; i < (part + 1) * (kMagBins / 8); i += 256) {
+    const uint32_t n = c[i];
+    uint32_t bin;
+    if (n && key_bin(dist_key(__uint_as_float((uint32_t)i << 16), tau), pass, prefix, &bin))
+      atomicAdd(&h[bin], (unsigned long long)n);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kHistBins; i += 256)
+    if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// Find the bucket holding the k0-th key, extend the prefix, clear the histogram.  One block,
+// eight bins per thread (one thread over the 2048 bins took 26 us).
+__global__ void __launch_bounds__(256) k_select_bucket(SelectState* sel, unsigned long long* hist,
+                                                       int pass) {
+  __shared__ unsigned long long wtot[4];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  unsigned long long v[8], own = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    v[i] = hist[tid * 8 + i];
+    own += v[i];
+  }
+  const unsigned long long need = sel->k0 - sel->less;
+  const unsigned long long inc = (unsigned long long)wave_incl_scan_i64((long long)own);
+  if (lane == 63) wtot[wid] = inc;
+  __syncthreads();                               // every thread has read sel and the bins
+  unsigned long long c = inc - own;              // keys in the earlier bins
+#pragma unroll
+  for (int w = 0; w < 4; ++w) c += w < wid ? wtot[w] : 0;
+  if (c < need && c + own >= need) {             // the thread whose bins reach it (k0 <= keys)
+    int b = 0;
+    while (c + v[b] < need) c += v[b++];
+    sel->less += c;
+    sel->prefix |= (uint32_t)(tid * 8 + b) << (pass == 0 ? 21 : (pass == 1 ? 10 : 0));
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) hist[tid * 8 + i] = 0;
+}
+
+// Selection state and a cleared histogram.
+__global__ void __launch_bounds__(256) k_select_init(SelectState* sel, unsigned long long k0,
+                                                     unsigned long long* hist) {
+  if (threadIdx.x == 0) {
+    sel->k0 = k0;
+    sel->less = 0;
+    sel->prefix = 0;
+    sel->pad = 0;
+  }
+  for (int i = threadIdx.x; i < kHistBins; i += 256) hist[i] = 0;
+}
+
+__device__ __forceinline__ uint32_t code_word(const float* v, float tau) {
+  uint32_t word = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) word |= ternary_code(v[q], tau) << code_shift(q);
+  return word;
+}
+
+constexpr int kRqThreads = 128;
+// Threads of the dense requantisation stream (one 8192-element tile per block: four
+// 16-byte chunks per thread for bf16 latents); with non-temporal code stores this
+// measured 6.1 TB/s against 5.2 TB/s for 128 threads and ordinary stores.
+constexpr int kRqStream = 256;
+
+// Code bits of the 16 / CPW consecutive elements v[] that start at element
+// (part * 16 / CPW) of a code word.
+template <int N>
+__device__ __forceinline__ uint32_t partial_word(const float* v, int part, float tau) {
+  uint32_t word = 0;
+#pragma unroll
+  for (int q = 0; q < N; ++q) word |= ternary_code(v[q], tau) << code_shift(part * N + q);
+  return word;
+}
+
+// OR of a code word's parts held by CPW adjacent lanes (all of them get it).
+template <int CPW>
+__device__ __forceinline__ uint32_t join_word(uint32_t w) {
+#pragma unroll
+  for (int m = 1; m < CPW; m <<= 1) w |= (uint32_t)__shfl_xor((int)w, m, 64);
+  return w;
+}
+
+// ---------------------------------------------------------------------------
+// Mask and clean codes: one pass over the latents writes the codes and counts each tile's
+// keys below and at xi0, a scan turns the counts into list positions, an ordered pass over
+// the codes writes the list.  A latent with key <= xi0 gets the fourth code value, 3, which no
+// weight has: the last pass reads the 2-bit codes in place of the latents, looks up only the
+// marked ones and writes their codes back (1.39e8 latents at 1e-3: count 44, write 71 and
+// codes 45 us in three passes over the latents; 52 and 13 us in these two).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kMarked = 3u;
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_codes_count(DevState st, const SelectState* sel,
+                                                     uint32_t* tile_cnt) {
+  constexpr int EPC = 16 / (int)sizeof(T);       // elements per 16-byte chunk
+  constexpr int CPW = 16 / EPC;                  // chunks per code word
+  constexpr int CPT = kTile / EPC / 256;         // chunks per thread
+  __shared__ unsigned long long red[4];
+  const uint32_t xi = sel->prefix;
+  const int64_t t = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int l = st.tile_layer[t];
+  const int64_t start = st.tile_start[t];
+  const int cnt = (int)min((int64_t)kTile, st.n[l] - start);
+  const float tau = st.tau[l];
+  const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
+  gu32* out = (gu32*)(st.codes + st.code_off[l] + start / 16);
+  v4u buf[CPT];
+#pragma unroll
+  for (int v = 0; v < CPT; ++v) {
+    const int e = (v * 256 + tid) * EPC;
+    buf[v] = __builtin_nontemporal_load((gv4u_c*)(w + (e < cnt ? e : 0)));   // clamped
+  }
+  uint32_t nl = 0, ne = 0;
+#pragma unroll
+  for (int v = 0; v < CPT; ++v) {
+    const int c = v * 256 + tid;
+    const bool in = c * EPC < cnt;
+    float x[EPC];
+    vec_values(&buf[v], 1, x, (const T*)nullptr);
+    uint32_t word = 0;
+#pragma unroll
+    for (int q = 0; q < EPC; ++q) {
+      const uint32_t key = dist_key(x[q], tau);
+      nl += in && key < xi;
+      ne += in && key == xi;
+      word |= (key <= xi ? kMarked : ternary_code(x[q], tau)) << code_shift((c % CPW) * EPC + q);
+    }
+    word = join_word<CPW>(word);
+    if (tid % CPW == 0 && in) __builtin_nontemporal_store(word, &out[c / CPW]);
+  }
+  const unsigned long long s = block_sum_u64(((unsigned long long)ne << 32) | nl, red);
+  if (tid == 0) {
+    tile_cnt[2 * t] = (uint32_t)s;
+    tile_cnt[2 * t + 1] = (uint32_t)(s >> 32);
+  }
+}
+
+// One block: per tile, the equal keys before it and its first list position (also the tile
+// ranges of the requantisation); per layer, the first list position.  Exactly k0 keys are
+// admitted, the equal ones in id order, so the equal ones admitted before a tile are the
+// smaller of those before it and those to admit, and one scan of both counts does.  Four
+// tiles per thread and round (256 threads walking T / 256 tiles each, one after another,
+// took 129 us for 17,000 tiles).
+__global__ void __launch_bounds__(1024) k_mask_scan(DevState st, const SelectState* sel,
+                                                    const uint32_t* tile_cnt, int inclusive,
+                                                    int64_t* tile_eqb, int64_t* act_off) {
+  __shared__ long long wl[16], we[16];
+  const long long need = inclusive ? INT64_MAX : (long long)(sel->k0 - sel->less);
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  long long cl = 0, ce = 0;                      // counts before this round
+  for (int64_t t0 = 0; t0 < st.T; t0 += 4096) {
+    const int64_t t = t0 + 4 * tid;
+    long long vl[4], ve[4], sl = 0, se = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      vl[i] = t + i < st.T ? tile_cnt[2 * (t + i)] : 0;
+      ve[i] = t + i < st.T ? tile_cnt[2 * (t + i) + 1] : 0;
+      sl += vl[i];
+      se += ve[i];
+    }
+    const long long il = wave_incl_scan_i64(sl), ie = wave_incl_scan_i64(se);
+    if (lane == 63) {
+      wl[wid] = il;
+      we[wid] = ie;
+    }
+    __syncthreads();
+    long long bl = cl + il - sl, be = ce + ie - se;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      bl += w < wid ? wl[w] : 0;
+      be += w < wid ? we[w] : 0;
+      cl += wl[w];
+      ce += we[w];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (t + i < st.T) {
+        const long long off = bl + min(be, need);
+        st.tile_act[t + i] = off;
+        tile_eqb[t + i] = be;
+        const int l = st.tile_layer[t + i];
+        if (t + i == 0 || l != st.tile_layer[t + i - 1]) act_off[l] = off;
+      }
+      bl += vl[i];
+      be += ve[i];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) st.tile_act[st.T] = act_off[st.L] = cl + min(ce, need);
+}
+
+// The list in order, from the marks in the codes: a thread owns two consecutive code words (32
+// elements) of its block's tile.  The marked latents are looked up, classified (below or at
+// xi0; of the equal ones the tile admits its quota) and get their codes; with wc the admitted
+// ones are also copied there in list order.
 template <typename T>
 __global__ void __launch_bounds__(256) k_mask_write(DevState st, const SelectState* sel,
                                                     const uint32_t* tile_cnt,
-                                                    const int64_t* tile_out,
                                                     const int64_t* tile_eqb, int inclusive,
-                                                    uint32_t* act) {
-  __shared__ long long lds[256];
+                                                    uint32_t* act, T* wc) {
+  __shared__ unsigned long long wtot[4];
   const uint32_t xi = sel->prefix;
-  const int64_t need = (int64_t)(sel->k0 - sel->less);
-  for (int64_t t = blockIdx.x; t < st.T; t += gridDim.x) {
-    const int l = st.tile_layer[t];
-    const float tau = st.tau[l];
-    const int64_t start = st.tile_start[t];
-    const int64_t cnt = min((int64_t)kTile, st.n[l] - start);
-    const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
-    const int64_t e0 = (int64_t)threadIdx.x * 32;
-    uint32_t lmask = 0, emask = 0;
-    for (int h = 0; h < 2; ++h) {
-      const int64_t e = e0 + 16 * h;
-      if (e < cnt) {
-        float v[16];
-        load16(w + e, v);
+  const long long need = inclusive ? INT64_MAX : (long long)(sel->k0 - sel->less);
+  const int64_t t = blockIdx.x;
+  if (tile_cnt[2 * t] + tile_cnt[2 * t + 1] == 0) return;   // no marks (block-uniform)
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int l = st.tile_layer[t];
+  const float tau = st.tau[l];
+  const int64_t start = st.tile_start[t];
+  const int nw = (int)(min((int64_t)kTile, st.n[l] - start) / 16);
+  const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
+  gu32* codes = (gu32*)(st.codes + st.code_off[l] + start / 16);
+  uint32_t word[2], lm = 0, em = 0;              // per element: below / at xi0
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const uint32_t key = dist_key(v[j], tau);
-          lmask |= (uint32_t)(key < xi) << (16 * h + j);
-          emask |= (uint32_t)(key == xi) << (16 * h + j);
-        }
-      }
+  for (int h = 0; h < 2; ++h) {
+    const int i = 2 * tid + h;
+    word[h] = i < nw ? codes[i] : 0u;
+    uint32_t mk = word[h] & (word[h] >> 1) & 0x55555555u;   // low bit of each marked code
+    if (mk == 0) continue;
+    uint32_t nword = word[h];
+    for (int q = 0; q < 16; ++q) {
+      const int sh = code_shift(q);
+      if (!((mk >> sh) & 1u)) continue;
+      const float x = load1(w, i * 16 + q);
+      if (dist_key(x, tau) < xi) lm |= 1u << (16 * h + q); else em |= 1u << (16 * h + q);
+      nword = (nword & ~(3u << sh)) | (ternary_code(x, tau) << sh);
     }
-    long long tot;
-    const long long packed = ((long long)__popc(emask) << 32) | __popc(lmask);
-    const long long pre = block_excl_scan_i64(packed, lds, &tot);
-    long long lb = pre & 0xFFFFFFFFll, eb = pre >> 32;
-    const long long etile = tile_cnt[2 * t + 1];
-    const long long quota = inclusive ? etile : max(0ll, min(etile, (long long)need - tile_eqb[t]));
-    const int64_t base = tile_out[t];
-    for (int j = 0; j < 32; ++j) {
-      const uint32_t bit = 1u << j;
-      if (lmask & bit) {
-        act[base + lb + min(eb, quota)] = (uint32_t)(start + e0 + j);
-        ++lb;
-      } else if (emask & bit) {
-        if (eb < quota) act[base + lb + eb] = (uint32_t)(start + e0 + j);
-        ++eb;
-      }
+    codes[i] = nword;
+  }
+  // marks of the earlier threads of the tile (both counts in one scan)
+  const long long own = ((long long)__popc(em) << 32) | __popc(lm);
+  const long long inc = wave_incl_scan_i64(own);
+  if (lane == 63) wtot[wid] = (unsigned long long)inc;
+  __syncthreads();
+  long long pre = inc - own;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) pre += v < wid ? (long long)wtot[v] : 0;
+  long long lb = pre & 0xFFFFFFFFll, eb = pre >> 32;
+  const long long etile = tile_cnt[2 * t + 1];
+  const long long quota = max(0ll, min(etile, need - (long long)tile_eqb[t]));
+  const int64_t base = st.tile_act[t];
+  for (uint32_t m = lm | em; m; m &= m - 1) {
+    const int j = __builtin_ctz(m);
+    int64_t pos = -1;
+    if ((lm >> j) & 1u) {
+      pos = base + lb + min(eb, quota);
+      ++lb;
+    } else {
+      if (eb < quota) pos = base + lb + eb;
+      ++eb;
+    }
+    if (pos >= 0) {
+      const uint32_t i = (uint32_t)(tid * 32 + j);
+      act[pos] = (uint32_t)start + i;
+      if (wc) wc[pos] = w[i];
     }
   }
 }
@@ -506,59 +736,10 @@ __global__ void __launch_bounds__(256) k_tile_ranges(DevState st, const uint32_t
 // actives are patched with LDS atomics; with every element active, the codes
 // come from wp directly.
 // ---------------------------------------------------------------------------
-// Global-address-space views (the pointers are computed from device tables,
-// so the compiler would otherwise emit FLAT accesses).
-typedef const __attribute__((address_space(1))) v4u gv4u_c;
-typedef __attribute__((address_space(1))) v4u gv4u;
-typedef __attribute__((address_space(1))) uint32_t gu32;
-
-__device__ __forceinline__ void vec_values(const v4u* b, int nvec, float* out, const float*) {
-  for (int v = 0; v < nvec; ++v)
-    for (int i = 0; i < 4; ++i) out[4 * v + i] = __uint_as_float(b[v][i]);
-}
-__device__ __forceinline__ void vec_values(const v4u* b, int nvec, float* out, const uint16_t*) {
-  for (int v = 0; v < nvec; ++v)
-    for (int i = 0; i < 4; ++i) {
-      out[8 * v + 2 * i] = __uint_as_float(b[v][i] << 16);
-      out[8 * v + 2 * i + 1] = __uint_as_float(b[v][i] & 0xFFFF0000u);
-    }
-}
-
-__device__ __forceinline__ uint32_t code_word(const float* v, float tau) {
-  uint32_t word = 0;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) word |= ternary_code(v[q], tau) << code_shift(q);
-  return word;
-}
-
-constexpr int kRqThreads = 128;
-// Threads of the dense requantisation stream (one 8192-element tile per block: four
-// 16-byte chunks per thread for bf16 latents); with non-temporal code stores this
-// measured 6.1 TB/s against 5.2 TB/s for 128 threads and ordinary stores.
-constexpr int kRqStream = 256;
-
-// Code bits of the 16 / CPW consecutive elements v[] that start at element
-// (part * 16 / CPW) of a code word.
-template <int N>
-__device__ __forceinline__ uint32_t partial_word(const float* v, int part, float tau) {
-  uint32_t word = 0;
-#pragma unroll
-  for (int q = 0; q < N; ++q) word |= ternary_code(v[q], tau) << code_shift(part * N + q);
-  return word;
-}
-
-// OR of a code word's parts held by CPW adjacent lanes (all of them get it).
-template <int CPW>
-__device__ __forceinline__ uint32_t join_word(uint32_t w) {
-#pragma unroll
-  for (int m = 1; m < CPW; m <<= 1) w |= (uint32_t)__shfl_xor((int)w, m, 64);
-  return w;
-}
-
 // Loads are coalesced: 16-byte chunk c of the tile goes to lane c % 128, so
 // one load instruction covers 1 KB of consecutive bytes; a code word's chunks
 // (2 for bf16, 4 for fp32) sit in adjacent lanes and are joined by shuffles.
-template <typename T, bool PATCH, int NT = kRqStream>
+template <typename T, int NT = kRqStream>
 __device__ __forceinline__ void requant_tile(const DevState& st, const uint32_t* act,
                                              const float* wp, int64_t t) {
   constexpr int EPC = 16 / (int)sizeof(T);       // elements per 16-byte chunk
@@ -573,19 +754,13 @@ __device__ __forceinline__ void requant_tile(const DevState& st, const uint32_t*
   const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
   gu32* out = (gu32*)(st.codes + st.code_off[l] + start / 16);
   const bool owner = (tid % CPW) == 0;            // stores the word of its lane group
-  int64_t a0 = 0, a1 = 0;
-  uint32_t aw = 0;
-  float pw = 0.0f;
-  if (PATCH) {
-    a0 = st.tile_act[t];
-    a1 = st.tile_act[t + 1];
-    const int64_t jj = a0 + tid;
-    const int64_t jc = jj < a1 ? jj : (a0 < a1 ? a0 : 0);   // the list holds at least one slot
-    aw = act[jc];
-    pw = wp[jc];
-  }
+  const int64_t a0 = st.tile_act[t], a1 = st.tile_act[t + 1];
+  const int64_t jf = a0 + tid;
+  const int64_t jc = jf < a1 ? jf : (a0 < a1 ? a0 : 0);     // the list holds at least one slot
+  const uint32_t aw = act[jc];
+  const float pw = wp[jc];
   const int64_t na = a1 - a0;
-  if (PATCH && na == cnt) {
+  if (na == cnt) {
     // every element active: the codes come from wp (fp32, 4 per chunk)
     constexpr int FC = kTile / 4 / NT;   // 16 chunks per thread
     const float* src = wp + a0;
@@ -624,7 +799,7 @@ __device__ __forceinline__ void requant_tile(const DevState& st, const uint32_t*
     vec_values(&buf[v], 1, x, (const T*)nullptr);
     wd[v] = join_word<CPW>(partial_word<EPC>(x, c % CPW, tau));
   }
-  if (PATCH && na > 0) {
+  if (na > 0) {
 #pragma unroll
     for (int v = 0; v < CPT; ++v)
       if (owner) words[(v * NT + tid) / CPW] = wd[v];
@@ -651,11 +826,11 @@ __device__ __forceinline__ void requant_tile(const DevState& st, const uint32_t*
   }
 }
 
-// One tile per block: every tile of every layer (mask build, dense requantisation).
-template <typename T, bool PATCH>
+// One tile per block: every tile of every layer.
+template <typename T>
 __global__ void __launch_bounds__(kRqStream) k_requant_tile(DevState st, const uint32_t* act,
                                                             const float* wp) {
-  requant_tile<T, PATCH>(st, act, wp, blockIdx.x);
+  requant_tile<T>(st, act, wp, blockIdx.x);
 }
 
 // The four draws of Philox counter quad q on a stream: one Philox call and one
@@ -1318,12 +1493,13 @@ __global__ void __launch_bounds__(256) k_guard(DevState st, int force, int64_t* 
 
 // After a dense requantisation of every layer at tau_cur (the mask build): every
 // inactive weight's fp32 distance is at least xi0, so its exact distance is at
-// least xi_lo = xi0 - ulp(xi0)/2.
-__global__ void k_ref_init(DevState st, double xi_lo) {
+// least xi_lo = xi0 - ulp(xi0)/2 (the next fp32 number is the next bit pattern).
+__global__ void k_ref_init(DevState st, const SelectState* sel) {
   const int l = blockIdx.x * blockDim.x + threadIdx.x;
   if (l >= st.L) return;
+  const double xi = (double)__uint_as_float(sel->prefix), up = (double)__uint_as_float(sel->prefix + 1u);
   st.tau_ref[l] = st.tau_cur[l];
-  st.mref[l] = xi_lo;
+  st.mref[l] = xi - 0.5 * (up - xi);
 }
 
 // Rewrite the 2-bit code of local index i of layer l (other fields of the word may
@@ -1352,7 +1528,7 @@ __device__ __forceinline__ void requant_list(const DevState& st, const uint32_t*
       if (dense_off[mid] <= i) lo = mid; else hi = mid - 1;
     }
     __syncthreads();                             // the previous tile's LDS words are consumed
-    requant_tile<T, true>(st, act, wp, st.tile0[lo] + (i - dense_off[lo]));
+    requant_tile<T>(st, act, wp, st.tile0[lo] + (i - dense_off[lo]));
   }
 }
 
@@ -1414,7 +1590,7 @@ __global__ void __launch_bounds__(kRqThreads) k_patch_tiles(DevState st,
   const int64_t t = blockIdx.x;
   const int l = st.tile_layer[t];
   if (st.need[l]) {                              // block-uniform
-    requant_tile<T, true, kRqThreads>(st, act, wp, t);
+    requant_tile<T, kRqThreads>(st, act, wp, t);
     return;
   }
   const int64_t a0 = st.tile_act[t], a1 = st.tile_act[t + 1];
@@ -1797,33 +1973,47 @@ hipError_t launch_abs_sum(termezo_ctx* c, int64_t* S_out) {
   return hipGetLastError();
 }
 
-hipError_t launch_thresholds(termezo_ctx* c, const int64_t* S, float* tau, float* beta) {
-  hipLaunchKernelGGL(k_thresholds, dim3((c->L + 255) / 256), dim3(256), 0, c->stream, S, c->d_n,
-                     c->delta, tau, beta, c->L);
-  return hipGetLastError();
-}
-
 hipError_t launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipStream_t s) {
   const int64_t g = max((int64_t)1, min((int64_t)1024, (n + 255) / 256));
   hipLaunchKernelGGL(k_fill_u64, dim3(g), dim3(256), 0, s, p, n, v);
   return hipGetLastError();
 }
 
-hipError_t launch_copy_i64(int64_t* dst, const int64_t* src, int64_t n, hipStream_t s) {
-  const int64_t g = max((int64_t)1, min((int64_t)1024, (n + 255) / 256));
-  hipLaunchKernelGGL(k_copy_i64, dim3(g), dim3(256), 0, s, dst, src, n);
+// The counters of k_mag_hist live in the code buffer, which the build rewrites afterwards.
+static bool mag_counts_fit(const termezo_ctx* c) {
+  return c->dtype == TERMEZO_BF16 && (int64_t)c->L * kMagBins <= c->code_words;
+}
+
+hipError_t launch_build_sums(termezo_ctx* c) {
+  if (mag_counts_fit(c)) {
+    // (cleared two counters at a time)
+    hipError_t e = launch_fill_u64((unsigned long long*)c->d_codes, (int64_t)c->L * kMagBins / 2, 0,
+                                   c->stream);
+    if (e != hipSuccess) return e;
+    int64_t tpb;
+    const int64_t g = grid_for(c->T, c->n_cu > 0 ? c->n_cu : 256, &tpb);
+    hipLaunchKernelGGL(k_mag_hist, dim3(g), dim3(1024), 0, c->stream, c->dev(), c->d_codes, tpb);
+    hipLaunchKernelGGL(k_mag_sum, dim3(c->L), dim3(256), 0, c->stream, c->dev(),
+                       (const uint32_t*)c->d_codes);
+  } else {
+    const hipError_t e = launch_abs_sum(c, c->d_S_clean);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_thresholds_build, dim3((c->L + 255) / 256), dim3(256), 0, c->stream, c->dev(),
+                     c->delta);
   return hipGetLastError();
 }
 
 hipError_t launch_select(termezo_ctx* c, int64_t k0) {
-  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(1), 0, c->stream, c->d_sel,
-                     (unsigned long long)k0);
-  hipError_t e = launch_fill_u64(c->d_hist, kHistBins, 0, c->stream);
-  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, c->stream, c->d_sel,
+                     (unsigned long long)k0, c->d_hist);
   int64_t tpb;
   const int64_t g = grid_for(c->T, 2048, &tpb);
   for (int pass = 0; pass < 3; ++pass) {
-    if (c->dtype == TERMEZO_F32)
+    if (mag_counts_fit(c))
+      hipLaunchKernelGGL(k_mag_pass, dim3(8 * c->L), dim3(256), 0, c->stream, c->dev(),
+                         (const uint32_t*)c->d_codes, pass, c->d_sel, c->d_hist);
+    else if (c->dtype == TERMEZO_F32)
       hipLaunchKernelGGL(k_hist<float>, dim3(g), dim3(256), 0, c->stream, c->dev(), pass, c->d_sel,
                          c->d_hist, tpb);
     else
@@ -1834,28 +2024,26 @@ hipError_t launch_select(termezo_ctx* c, int64_t k0) {
   return hipGetLastError();
 }
 
-hipError_t launch_mask_compact_counts(termezo_ctx* c, int inclusive) {
-  const int64_t g = max((int64_t)1, min(c->T, (int64_t)8192));
+hipError_t launch_codes_count(termezo_ctx* c, int inclusive) {
   if (c->dtype == TERMEZO_F32)
-    hipLaunchKernelGGL(k_mask_count<float>, dim3(g), dim3(256), 0, c->stream, c->dev(), c->d_sel,
-                       c->d_tile_cnt);
-  else
-    hipLaunchKernelGGL(k_mask_count<uint16_t>, dim3(g), dim3(256), 0, c->stream, c->dev(),
+    hipLaunchKernelGGL(k_codes_count<float>, dim3((unsigned)c->T), dim3(256), 0, c->stream, c->dev(),
                        c->d_sel, c->d_tile_cnt);
-  hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(256), 0, c->stream, c->d_sel, c->d_tile_cnt,
-                     c->d_tile_layer, c->T, c->L, inclusive, c->d_tile_out, c->d_tile_eqb,
-                     c->d_act_off);
+  else
+    hipLaunchKernelGGL(k_codes_count<uint16_t>, dim3((unsigned)c->T), dim3(256), 0, c->stream,
+                       c->dev(), c->d_sel, c->d_tile_cnt);
+  hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(1024), 0, c->stream, c->dev(), c->d_sel,
+                     c->d_tile_cnt, inclusive, c->d_tile_eqb, c->d_act_off);
   return hipGetLastError();
 }
 
-hipError_t launch_mask_compact_write(termezo_ctx* c, int inclusive) {
-  const int64_t g = max((int64_t)1, min(c->T, (int64_t)8192));
+hipError_t launch_mask_write(termezo_ctx* c, int inclusive, void* wc) {
   if (c->dtype == TERMEZO_F32)
-    hipLaunchKernelGGL(k_mask_write<float>, dim3(g), dim3(256), 0, c->stream, c->dev(), c->d_sel,
-                       c->d_tile_cnt, c->d_tile_out, c->d_tile_eqb, inclusive, c->d_act);
+    hipLaunchKernelGGL(k_mask_write<float>, dim3((unsigned)c->T), dim3(256), 0, c->stream, c->dev(),
+                       c->d_sel, c->d_tile_cnt, c->d_tile_eqb, inclusive, c->d_act, (float*)wc);
   else
-    hipLaunchKernelGGL(k_mask_write<uint16_t>, dim3(g), dim3(256), 0, c->stream, c->dev(),
-                       c->d_sel, c->d_tile_cnt, c->d_tile_out, c->d_tile_eqb, inclusive, c->d_act);
+    hipLaunchKernelGGL(k_mask_write<uint16_t>, dim3((unsigned)c->T), dim3(256), 0, c->stream,
+                       c->dev(), c->d_sel, c->d_tile_cnt, c->d_tile_eqb, inclusive, c->d_act,
+                       (uint16_t*)wc);
   return hipGetLastError();
 }
 
@@ -1863,23 +2051,13 @@ static inline int64_t sparse_grid(int64_t k) {
   return max((int64_t)1, min((int64_t)8192, (k + 256 * kRun - 1) / (256 * kRun)));
 }
 
-hipError_t launch_requant(termezo_ctx* c, int patch) {
+// Every latent re-quantised with tau_cur, the actives' codes from their perturbed values d_wp.
+static hipError_t launch_requant(termezo_ctx* c) {
   const dim3 g((unsigned)c->T), b(kRqStream);
-  if (c->dtype == TERMEZO_F32) {
-    if (patch)
-      hipLaunchKernelGGL((k_requant_tile<float, true>), g, b, 0, c->stream, c->dev(), c->d_act,
-                         c->d_wp);
-    else
-      hipLaunchKernelGGL((k_requant_tile<float, false>), g, b, 0, c->stream, c->dev(), c->d_act,
-                         c->d_wp);
-  } else {
-    if (patch)
-      hipLaunchKernelGGL((k_requant_tile<uint16_t, true>), g, b, 0, c->stream, c->dev(), c->d_act,
-                         c->d_wp);
-    else
-      hipLaunchKernelGGL((k_requant_tile<uint16_t, false>), g, b, 0, c->stream, c->dev(), c->d_act,
-                         c->d_wp);
-  }
+  if (c->dtype == TERMEZO_F32)
+    hipLaunchKernelGGL(k_requant_tile<float>, g, b, 0, c->stream, c->dev(), c->d_act, c->d_wp);
+  else
+    hipLaunchKernelGGL(k_requant_tile<uint16_t>, g, b, 0, c->stream, c->dev(), c->d_act, c->d_wp);
   return hipGetLastError();
 }
 
@@ -1889,7 +2067,7 @@ hipError_t launch_requant_guarded(termezo_ctx* c, int force, int take) {
                      c->delta);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (force) return launch_requant(c, 1);      // every layer: one block per tile
+  if (force) return launch_requant(c);      // every layer: one block per tile
   const bool bf = c->dtype == TERMEZO_BF16;
   // sparse sets: one scattered code-word update per active; above 1/256 active the
   // code words of the tiles with actives are rewritten whole (0.5 byte per weight).  Either
@@ -1914,9 +2092,9 @@ hipError_t launch_requant_guarded(termezo_ctx* c, int force, int take) {
   return hipGetLastError();
 }
 
-hipError_t launch_ref_init(termezo_ctx* c, double xi_lo) {
+hipError_t launch_ref_init(termezo_ctx* c) {
   hipLaunchKernelGGL(k_ref_init, dim3((unsigned)((c->L + 255) / 256)), dim3(256), 0, c->stream,
-                     c->dev(), xi_lo);
+                     c->dev(), (const SelectState*)c->d_sel);
   return hipGetLastError();
 }
 

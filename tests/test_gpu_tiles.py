@@ -120,3 +120,46 @@ def test_decoder_ragged_tiles(orc, act, d, H, Hkv, F, V, S, B):
     assert np.all(got[:, -1] == 0.0)
     model.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("rho0,inclusive", [(1e-3, False), (0.02, True), (0.3, False), (1.0, False)])
+@pytest.mark.parametrize("shapes,bf16", [
+    ([(1024, 768), (800, 1040)], True),      # counted by magnitude (layers of 2^19 and more), with ties
+    ([(1024, 768), (800, 1040)], False),     # radix passes over the latents
+    ([(48, 80)] * 9 + [(16, 16)], True)])    # tiles of part of a layer, smaller than a block's share
+def test_mask_build_and_dense_runs(orc, shapes, bf16, rho0, inclusive):
+    """The mask, thresholds and clean codes of a build, rebuilt once, and two steps on it: with
+    every latent active the updates drop latents, so that later runs of ids straddle quads."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print(f"mask {shapes[0]} x {len(shapes)} bf16={bf16} rho0={rho0} incl={inclusive}", flush=True)
+    w = synth.latents(21, [o * i for o, i in shapes], bf16=bf16)
+    ref = orc.TerMeZOOracle([orc.Layer(o, i) for o, i in shapes], w, bf16=bf16)
+    tensors, off = [], 0
+    for o, i in shapes:
+        t = torch.from_numpy(w[off:off + o * i].reshape(o, i)).cuda()
+        tensors.append(t.to(torch.bfloat16) if bf16 else t)
+        off += o * i
+    ctx = termezo.Context(tensors)
+    ctx.build_mask(0.01)
+    assert ctx.build_mask(rho0, 1e-5, inclusive) == ref.build_mask(rho0, inclusive)
+    for l in range(len(shapes)):
+        st = ctx.layer_stats(l)
+        assert st["S"] == ref.S[l] and st["tau"] == st["tau_cur"] == ref.tau[l]
+        assert np.array_equal(ctx.mask(l), ref.active[l])
+        assert np.array_equal(ctx.codes(l), ref.clean_codes(l))
+    for t in range(2):
+        for sign in (1, -1):
+            ctx.perturb(5 + t, 1e-3, sign)
+            codes, taus, _ = ref.perturb(5 + t, 1e-3, sign)
+            for l in range(len(shapes)):
+                assert ctx.layer_stats(l)["tau_cur"] == taus[l]
+                assert np.array_equal(ctx.codes(l), codes[l])
+        # (1e-3: some of the farthest latents move out of the set)
+        assert ctx.update(0.7, 1e-3) == ref.update(0.7, 1e-3)
+    for l in range(len(shapes)):
+        assert ctx.layer_stats(l)["S"] == ref.S[l]
+        assert np.array_equal(ctx.mask(l), ref.active[l])
+    got = np.concatenate([t.float().cpu().numpy().ravel() for t in tensors])
+    assert np.array_equal(got, ref.w)
+    ctx.close()
