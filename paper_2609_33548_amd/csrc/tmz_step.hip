@@ -347,8 +347,8 @@ __global__ void __launch_bounds__(256) k_hist(DevState st, int pass, const Selec
 // |w| sum, and, once the threshold is known, how many latents lie at each distance.  The
 // radix passes then run over the counts.  One block of 16 waves per compute unit with all
 // 2^15 counters in LDS (spread over enough of them that few lanes of a wave meet on one);
-// 1.39e8 latents: 60 us in place of 96 (sums) and 3 x 89 (radix passes over the latents, whose
-// eleven-bit bins crowd the LDS atomics).
+// 1.39e8 latents: 54 us, near the 57 of a plain read at copy rate, in place of 96 (sums) and
+// 3 x 89 (radix passes over the latents, whose eleven-bit bins crowd the LDS atomics).
 // ---------------------------------------------------------------------------
 constexpr int kMagBins = 1 << 15;
 
@@ -360,53 +360,74 @@ __global__ void __launch_bounds__(1024) k_mag_hist(DevState st, uint32_t* counts
   const int64_t t0 = (int64_t)blockIdx.x * tpb;
   const int64_t t1 = min(st.T, t0 + tpb);
   bool bad = false;
-  auto load = [&](int64_t t) __attribute__((always_inline)) {     // one 16-byte chunk per thread
-    const int l = st.tile_layer[t];
-    const int64_t start = st.tile_start[t], e = (int64_t)tid * 8;
-    const uint16_t* w = reinterpret_cast<const uint16_t*>(st.w[l]) + start;
-    return *(gv4u_c*)(w + (e < st.n[l] - start ? e : 0));
-  };
-  v4u nx = {0u, 0u, 0u, 0u}, nx2 = {0u, 0u, 0u, 0u};
-  if (t0 < t1) nx = load(t0);
-  if (t0 + 1 < t1) nx2 = load(t0 + 1);
-  for (int64_t t = t0; t < t1; ++t) {
-    const v4u b = nx;
-    nx = nx2;
-    if (t + 2 < t1) nx2 = load(t + 2);
-    const int l = st.tile_layer[t];
-    if ((int64_t)tid * 8 < st.n[l] - st.tile_start[t]) {
+  auto count = [&](v4u b) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t lo = b[i] & 0x7FFFu, hi = (b[i] >> 16) & 0x7FFFu;
-        bad |= max(lo, hi) >= 0x4080u;            // |w| >= 4, infinite or NaN
-        atomicAdd(&h[lo], 1u);
-        atomicAdd(&h[hi], 1u);
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t lo = b[i] & 0x7FFFu, hi = (b[i] >> 16) & 0x7FFFu;
+      bad |= max(lo, hi) >= 0x4080u;              // |w| >= 4, infinite or NaN
+      atomicAdd(&h[lo], 1u);
+      atomicAdd(&h[hi], 1u);
+    }
+  };
+  // The block's tiles layer by layer: a layer's tiles are consecutive in memory, so the loop
+  // reads no tables (a tile's layer, its pointer and then its latents, one after another,
+  // took 160 us for the pass), four 16-byte chunks per thread in flight.
+  for (int64_t t = t0; t < t1;) {
+    const int l = st.tile_layer[t];
+    const int64_t n = st.n[l];
+    const int64_t a = st.tile_start[t], e = min(n, a + (t1 - t) * kTile);
+    const uint16_t* w = reinterpret_cast<const uint16_t*>(st.w[l]);
+    constexpr int U = 4;
+    constexpr int64_t kStep = 1024 * 8;
+    v4u nx[U];
+    int64_t p = a + (int64_t)tid * 8;              // this thread's first element (n % 16 == 0)
+#pragma unroll
+    for (int u = 0; u < U; ++u) nx[u] = *(gv4u_c*)(w + (p + u * kStep < e ? p + u * kStep : 0));
+    for (; p < e; p += U * kStep) {
+      v4u b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) b[u] = nx[u];
+      const int64_t q = p + U * kStep;
+#pragma unroll
+      for (int u = 0; u < U; ++u) nx[u] = *(gv4u_c*)(w + (q + u * kStep < e ? q + u * kStep : 0));
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (p + u * kStep < e) count(b[u]);
+    }
+    __syncthreads();
+    for (int i = tid; i < kMagBins; i += 1024) {   // (a layer's counts fit 32 bits)
+      const uint32_t c = h[i];
+      if (c) {
+        atomicAdd(&counts[(int64_t)l * kMagBins + i], c);
+        h[i] = 0;
       }
     }
-    if (t + 1 == t1 || st.tile_layer[t + 1] != l) {  // the layer's counts (a layer fits 32 bits)
-      __syncthreads();
-      for (int i = tid; i < kMagBins; i += 1024) {
-        const uint32_t c = h[i];
-        if (c) {
-          atomicAdd(&counts[(int64_t)l * kMagBins + i], c);
-          h[i] = 0;
-        }
-      }
-      __syncthreads();
-    }
+    __syncthreads();
+    t += (e - a + kTile - 1) / kTile;
   }
   if (bad) atomicOr(st.err, 1);
 }
 
 // One block per layer: its |w| sum.
-__global__ void __launch_bounds__(256) k_mag_sum(DevState st, const uint32_t* counts) {
-  __shared__ unsigned long long red[4];
-  const uint32_t* c = counts + (int64_t)blockIdx.x * kMagBins;
+__global__ void __launch_bounds__(1024) k_mag_sum(DevState st, const uint32_t* counts) {
+  __shared__ unsigned long long red[16];
+  const v4u* c = reinterpret_cast<const v4u*>(counts + (int64_t)blockIdx.x * kMagBins);
   unsigned long long acc = 0;
-  for (int i = threadIdx.x; i < kMagBins; i += 256)
-    acc += (unsigned long long)c[i] * fix_abs(__uint_as_float((uint32_t)i << 16));
-  acc = block_sum_u64(acc, red);
-  if (threadIdx.x == 0) st.S_clean[blockIdx.x] = (int64_t)acc;
+#pragma unroll
+  for (int k = 0; k < kMagBins / 4096; ++k) {
+    const int i = k * 1024 + threadIdx.x;
+    const v4u n = c[i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      acc += (unsigned long long)n[j] * fix_abs(__uint_as_float((uint32_t)(4 * i + j) << 16));
+  }
+  acc = wave_sum_u64(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) acc += red[w];
+    st.S_clean[blockIdx.x] = (int64_t)acc;
+  }
 }
 
 // A radix pass over the counts: 8 blocks per layer.
@@ -509,7 +530,8 @@ __device__ __forceinline__ uint32_t join_word(uint32_t w) {
 // the codes writes the list.  A latent with key <= xi0 gets the fourth code value, 3, which no
 // weight has: the last pass reads the 2-bit codes in place of the latents, looks up only the
 // marked ones and writes their codes back (1.39e8 latents at 1e-3: count 44, write 71 and
-// codes 45 us in three passes over the latents; 52 and 13 us in these two).
+// codes 45 us in three passes over the latents; 64 and 18 us in these two, of which 63 are
+// the bytes of the first at copy rate).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kMarked = 3u;
 
@@ -560,74 +582,73 @@ __global__ void __launch_bounds__(256) k_codes_count(DevState st, const SelectSt
   }
 }
 
-// One block: per tile, the equal keys before it and its first list position (also the tile
-// ranges of the requantisation); per layer, the first list position.  Exactly k0 keys are
-// admitted, the equal ones in id order, so the equal ones admitted before a tile are the
-// smaller of those before it and those to admit, and one scan of both counts does.  Four
-// tiles per thread and round (256 threads walking T / 256 tiles each, one after another,
-// took 129 us for 17,000 tiles).
+// Per tile, the equal keys before it and its first list position (also the tile ranges of the
+// requantisation); per layer, the first list position.  Exactly k0 keys are admitted, the
+// equal ones in id order, so the equal ones admitted before a tile are the smaller of those
+// before it and those to admit, and one scan of both counts does.  A block owns 1024 tiles, one
+// per thread, and first adds up all counts before them, 16-byte loads that no step waits for:
+// for 17,000 tiles (136 KB of counts) 7 us, in place of 129 for 256 threads that walked
+// T / 256 tiles each, one after another, and 35 for one block in rounds.
 __global__ void __launch_bounds__(1024) k_mask_scan(DevState st, const SelectState* sel,
                                                     const uint32_t* tile_cnt, int inclusive,
                                                     int64_t* tile_eqb, int64_t* act_off) {
-  __shared__ long long wl[16], we[16];
+  __shared__ long long wl[16], we[16], pl[16], pe[16];
   const long long need = inclusive ? INT64_MAX : (long long)(sel->k0 - sel->less);
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  long long cl = 0, ce = 0;                      // counts before this round
-  for (int64_t t0 = 0; t0 < st.T; t0 += 4096) {
-    const int64_t t = t0 + 4 * tid;
-    long long vl[4], ve[4], sl = 0, se = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      vl[i] = t + i < st.T ? tile_cnt[2 * (t + i)] : 0;
-      ve[i] = t + i < st.T ? tile_cnt[2 * (t + i) + 1] : 0;
-      sl += vl[i];
-      se += ve[i];
-    }
-    const long long il = wave_incl_scan_i64(sl), ie = wave_incl_scan_i64(se);
-    if (lane == 63) {
-      wl[wid] = il;
-      we[wid] = ie;
-    }
-    __syncthreads();
-    long long bl = cl + il - sl, be = ce + ie - se;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-      bl += w < wid ? wl[w] : 0;
-      be += w < wid ? we[w] : 0;
-      cl += wl[w];
-      ce += we[w];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (t + i < st.T) {
-        const long long off = bl + min(be, need);
-        st.tile_act[t + i] = off;
-        tile_eqb[t + i] = be;
-        const int l = st.tile_layer[t + i];
-        if (t + i == 0 || l != st.tile_layer[t + i - 1]) act_off[l] = off;
-      }
-      bl += vl[i];
-      be += ve[i];
-    }
-    __syncthreads();
+  const int64_t t0 = (int64_t)blockIdx.x * 1024, t = t0 + tid;
+  const bool in = t < st.T;
+  const uint2 c = in ? reinterpret_cast<const uint2*>(tile_cnt)[t] : make_uint2(0u, 0u);
+  const int lay = in ? st.tile_layer[t] : -1;
+  const int lay0 = in && t > 0 ? st.tile_layer[t - 1] : -1;
+  unsigned long long sl = 0, se = 0;             // counts before the block's tiles
+  const v4u* pc = reinterpret_cast<const v4u*>(tile_cnt);
+#pragma unroll 8
+  for (int64_t i = tid; i < t0 / 2; i += 1024) {
+    const v4u v = pc[i];
+    sl += (unsigned long long)v[0] + v[2];
+    se += (unsigned long long)v[1] + v[3];
   }
-  if (tid == 0) st.tile_act[st.T] = act_off[st.L] = cl + min(ce, need);
+  sl = wave_sum_u64(sl);
+  se = wave_sum_u64(se);
+  const long long il = wave_incl_scan_i64(c.x), ie = wave_incl_scan_i64(c.y);
+  if (lane == 63) {
+    wl[wid] = il;
+    we[wid] = ie;
+    pl[wid] = (long long)sl;
+    pe[wid] = (long long)se;
+  }
+  __syncthreads();
+  long long bl = il - c.x, be = ie - c.y;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    bl += pl[w] + (w < wid ? wl[w] : 0);
+    be += pe[w] + (w < wid ? we[w] : 0);
+  }
+  if (in) {
+    const long long off = bl + min(be, need);
+    st.tile_act[t] = off;
+    tile_eqb[t] = be;
+    if (lay != lay0) act_off[lay] = off;
+    if (t == st.T - 1) st.tile_act[st.T] = act_off[st.L] = bl + c.x + min(be + c.y, need);
+  }
 }
 
-// The list in order, from the marks in the codes: a thread owns two consecutive code words (32
+// The list in order, from the marks in the codes: a thread owns four consecutive code words (64
 // elements) of its block's tile.  The marked latents are looked up, classified (below or at
 // xi0; of the equal ones the tile admits its quota) and get their codes; with wc the admitted
 // ones are also copied there in list order.
 template <typename T>
-__global__ void __launch_bounds__(256) k_mask_write(DevState st, const SelectState* sel,
+__global__ void __launch_bounds__(128) k_mask_write(DevState st, const SelectState* sel,
                                                     const uint32_t* tile_cnt,
                                                     const int64_t* tile_eqb, int inclusive,
                                                     uint32_t* act, T* wc) {
-  __shared__ unsigned long long wtot[4];
+  static_assert(kTile / 16 == 4 * 128, "four code words per thread");
+  __shared__ unsigned long long wtot[2];
   const uint32_t xi = sel->prefix;
   const long long need = inclusive ? INT64_MAX : (long long)(sel->k0 - sel->less);
   const int64_t t = blockIdx.x;
-  if (tile_cnt[2 * t] + tile_cnt[2 * t + 1] == 0) return;   // no marks (block-uniform)
+  const uint2 tc = reinterpret_cast<const uint2*>(tile_cnt)[t];
+  const int64_t eqb = tile_eqb[t], base = st.tile_act[t];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int l = st.tile_layer[t];
   const float tau = st.tau[l];
@@ -635,37 +656,34 @@ __global__ void __launch_bounds__(256) k_mask_write(DevState st, const SelectSta
   const int nw = (int)(min((int64_t)kTile, st.n[l] - start) / 16);
   const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
   gu32* codes = (gu32*)(st.codes + st.code_off[l] + start / 16);
-  uint32_t word[2], lm = 0, em = 0;              // per element: below / at xi0
+  if (tc.x + tc.y == 0) return;                  // no marks (block-uniform)
+  uint32_t word[4];
+  uint64_t lm = 0, em = 0;                       // per element: below / at xi0
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = 2 * tid + h;
-    word[h] = i < nw ? codes[i] : 0u;
+  for (int h = 0; h < 4; ++h) word[h] = 4 * tid + h < nw ? codes[4 * tid + h] : 0u;
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
     uint32_t mk = word[h] & (word[h] >> 1) & 0x55555555u;   // low bit of each marked code
     if (mk == 0) continue;
     uint32_t nword = word[h];
-    for (int q = 0; q < 16; ++q) {
-      const int sh = code_shift(q);
-      if (!((mk >> sh) & 1u)) continue;
-      const float x = load1(w, i * 16 + q);
-      if (dist_key(x, tau) < xi) lm |= 1u << (16 * h + q); else em |= 1u << (16 * h + q);
+    for (; mk; mk &= mk - 1) {
+      const int sh = __builtin_ctz(mk), q = 4 * ((sh & 7) >> 1) + (sh >> 3);   // code_shift(q) = sh
+      const float x = load1(w, (4 * tid + h) * 16 + q);
+      if (dist_key(x, tau) < xi) lm |= 1ull << (16 * h + q); else em |= 1ull << (16 * h + q);
       nword = (nword & ~(3u << sh)) | (ternary_code(x, tau) << sh);
     }
-    codes[i] = nword;
+    codes[4 * tid + h] = nword;
   }
   // marks of the earlier threads of the tile (both counts in one scan)
-  const long long own = ((long long)__popc(em) << 32) | __popc(lm);
+  const long long own = ((long long)__popcll(em) << 32) | __popcll(lm);
   const long long inc = wave_incl_scan_i64(own);
   if (lane == 63) wtot[wid] = (unsigned long long)inc;
   __syncthreads();
-  long long pre = inc - own;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) pre += v < wid ? (long long)wtot[v] : 0;
+  const long long pre = inc - own + (wid ? (long long)wtot[0] : 0);
   long long lb = pre & 0xFFFFFFFFll, eb = pre >> 32;
-  const long long etile = tile_cnt[2 * t + 1];
-  const long long quota = max(0ll, min(etile, need - (long long)tile_eqb[t]));
-  const int64_t base = st.tile_act[t];
-  for (uint32_t m = lm | em; m; m &= m - 1) {
-    const int j = __builtin_ctz(m);
+  const long long quota = max(0ll, min((long long)tc.y, need - (long long)eqb));
+  for (uint64_t m = lm | em; m; m &= m - 1) {
+    const int j = __builtin_ctzll(m);
     int64_t pos = -1;
     if ((lm >> j) & 1u) {
       pos = base + lb + min(eb, quota);
@@ -675,7 +693,7 @@ __global__ void __launch_bounds__(256) k_mask_write(DevState st, const SelectSta
       ++eb;
     }
     if (pos >= 0) {
-      const uint32_t i = (uint32_t)(tid * 32 + j);
+      const uint32_t i = (uint32_t)(tid * 64 + j);
       act[pos] = (uint32_t)start + i;
       if (wc) wc[pos] = w[i];
     }
@@ -844,8 +862,8 @@ __device__ __forceinline__ void gauss_quad(uint64_t seed, uint64_t q, uint32_t s
 
 // The draws of four consecutive ids g0 .. g0+3 on stream 0: one quad when they are one, else
 // two Philox calls and the two or three Box-Muller pairs they touch.  (Once one latent of a
-// dense layer has left the set, every later run of four entries straddles two quads; entry by
-// entry these runs took the pair pass of 6.95e7 actives from 330 to about 600 us.)
+// dense layer has left the set, every later run of four entries straddles two quads; a
+// step over 6.95e7 actives takes 1080 us so, 1255 to 1450 with these runs entry by entry.)
 __device__ __forceinline__ void gauss_run(uint64_t seed, uint64_t g0, float z[4]) {
   const uint64_t q = g0 >> 2;
   const uint32_t s = (uint32_t)g0 & 3u;
@@ -1993,7 +2011,7 @@ hipError_t launch_build_sums(termezo_ctx* c) {
     int64_t tpb;
     const int64_t g = grid_for(c->T, c->n_cu > 0 ? c->n_cu : 256, &tpb);
     hipLaunchKernelGGL(k_mag_hist, dim3(g), dim3(1024), 0, c->stream, c->dev(), c->d_codes, tpb);
-    hipLaunchKernelGGL(k_mag_sum, dim3(c->L), dim3(256), 0, c->stream, c->dev(),
+    hipLaunchKernelGGL(k_mag_sum, dim3(c->L), dim3(1024), 0, c->stream, c->dev(),
                        (const uint32_t*)c->d_codes);
   } else {
     const hipError_t e = launch_abs_sum(c, c->d_S_clean);
@@ -2031,17 +2049,17 @@ hipError_t launch_codes_count(termezo_ctx* c, int inclusive) {
   else
     hipLaunchKernelGGL(k_codes_count<uint16_t>, dim3((unsigned)c->T), dim3(256), 0, c->stream,
                        c->dev(), c->d_sel, c->d_tile_cnt);
-  hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(1024), 0, c->stream, c->dev(), c->d_sel,
+  hipLaunchKernelGGL(k_mask_scan, dim3((unsigned)((c->T + 1023) / 1024)), dim3(1024), 0, c->stream, c->dev(), c->d_sel,
                      c->d_tile_cnt, inclusive, c->d_tile_eqb, c->d_act_off);
   return hipGetLastError();
 }
 
 hipError_t launch_mask_write(termezo_ctx* c, int inclusive, void* wc) {
   if (c->dtype == TERMEZO_F32)
-    hipLaunchKernelGGL(k_mask_write<float>, dim3((unsigned)c->T), dim3(256), 0, c->stream, c->dev(),
+    hipLaunchKernelGGL(k_mask_write<float>, dim3((unsigned)c->T), dim3(128), 0, c->stream, c->dev(),
                        c->d_sel, c->d_tile_cnt, c->d_tile_eqb, inclusive, c->d_act, (float*)wc);
   else
-    hipLaunchKernelGGL(k_mask_write<uint16_t>, dim3((unsigned)c->T), dim3(256), 0, c->stream,
+    hipLaunchKernelGGL(k_mask_write<uint16_t>, dim3((unsigned)c->T), dim3(128), 0, c->stream,
                        c->dev(), c->d_sel, c->d_tile_cnt, c->d_tile_eqb, inclusive, c->d_act,
                        (uint16_t*)wc);
   return hipGetLastError();
