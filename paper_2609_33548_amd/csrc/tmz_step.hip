@@ -637,6 +637,12 @@ __global__ void __launch_bounds__(1024) k_mask_scan(DevState st, const SelectSta
 // elements) of its block's tile.  The marked latents are looked up, classified (below or at
 // xi0; of the equal ones the tile admits its quota) and get their codes; with wc the admitted
 // ones are also copied there in list order.
+//   A tile with more than kTile / 32 marks (the usual mask takes 8 of a tile; a
+// mask may also take all) is classified from its latents instead, whole vectors at a time: one
+// dependent look-up per mark took 1059 us where all of 6.95e7 latents are in the mask, the
+// whole build takes 244 so.  The list goes through LDS and out in order;
+// a thread's entries are consecutive, so the LDS index skips two entries in 64 to spread the
+// lanes over the banks.
 template <typename T>
 __global__ void __launch_bounds__(128) k_mask_write(DevState st, const SelectState* sel,
                                                     const uint32_t* tile_cnt,
@@ -644,6 +650,7 @@ __global__ void __launch_bounds__(128) k_mask_write(DevState st, const SelectSta
                                                     uint32_t* act, T* wc) {
   static_assert(kTile / 16 == 4 * 128, "four code words per thread");
   __shared__ unsigned long long wtot[2];
+  __shared__ uint16_t ids[kTile + kTile / 32];
   const uint32_t xi = sel->prefix;
   const long long need = inclusive ? INT64_MAX : (long long)(sel->k0 - sel->less);
   const int64_t t = blockIdx.x;
@@ -657,22 +664,42 @@ __global__ void __launch_bounds__(128) k_mask_write(DevState st, const SelectSta
   const T* w = reinterpret_cast<const T*>(st.w[l]) + start;
   gu32* codes = (gu32*)(st.codes + st.code_off[l] + start / 16);
   if (tc.x + tc.y == 0) return;                  // no marks (block-uniform)
-  uint32_t word[4];
   uint64_t lm = 0, em = 0;                       // per element: below / at xi0
+  if (tc.x + tc.y > kTile / 32) {                // (block-uniform)
 #pragma unroll
-  for (int h = 0; h < 4; ++h) word[h] = 4 * tid + h < nw ? codes[4 * tid + h] : 0u;
+    for (int h = 0; h < 4; ++h) {
+      if (4 * tid + h >= nw) continue;
+      float v[16];
+      load16(w + (4 * tid + h) * 16, v);
+      uint32_t lo = 0, eq = 0, nword = 0;
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    uint32_t mk = word[h] & (word[h] >> 1) & 0x55555555u;   // low bit of each marked code
-    if (mk == 0) continue;
-    uint32_t nword = word[h];
-    for (; mk; mk &= mk - 1) {
-      const int sh = __builtin_ctz(mk), q = 4 * ((sh & 7) >> 1) + (sh >> 3);   // code_shift(q) = sh
-      const float x = load1(w, (4 * tid + h) * 16 + q);
-      if (dist_key(x, tau) < xi) lm |= 1ull << (16 * h + q); else em |= 1ull << (16 * h + q);
-      nword = (nword & ~(3u << sh)) | (ternary_code(x, tau) << sh);
+      for (int q = 0; q < 16; ++q) {
+        const uint32_t key = dist_key(v[q], tau);
+        lo |= (uint32_t)(key < xi) << q;
+        eq |= (uint32_t)(key == xi) << q;
+        nword |= ternary_code(v[q], tau) << code_shift(q);
+      }
+      lm |= (uint64_t)lo << (16 * h);
+      em |= (uint64_t)eq << (16 * h);
+      codes[4 * tid + h] = nword;
     }
-    codes[4 * tid + h] = nword;
+  } else {
+    uint32_t word[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) word[h] = 4 * tid + h < nw ? codes[4 * tid + h] : 0u;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      uint32_t mk = word[h] & (word[h] >> 1) & 0x55555555u;   // low bit of each marked code
+      if (mk == 0) continue;
+      uint32_t nword = word[h];
+      for (; mk; mk &= mk - 1) {
+        const int sh = __builtin_ctz(mk), q = 4 * ((sh & 7) >> 1) + (sh >> 3);   // code_shift(q) = sh
+        const float x = load1(w, (4 * tid + h) * 16 + q);
+        if (dist_key(x, tau) < xi) lm |= 1ull << (16 * h + q); else em |= 1ull << (16 * h + q);
+        nword = (nword & ~(3u << sh)) | (ternary_code(x, tau) << sh);
+      }
+      codes[4 * tid + h] = nword;
+    }
   }
   // marks of the earlier threads of the tile (both counts in one scan)
   const long long own = ((long long)__popcll(em) << 32) | __popcll(lm);
@@ -684,19 +711,22 @@ __global__ void __launch_bounds__(128) k_mask_write(DevState st, const SelectSta
   const long long quota = max(0ll, min((long long)tc.y, need - (long long)eqb));
   for (uint64_t m = lm | em; m; m &= m - 1) {
     const int j = __builtin_ctzll(m);
-    int64_t pos = -1;
+    int pos = -1;                                // within the tile's part of the list
     if ((lm >> j) & 1u) {
-      pos = base + lb + min(eb, quota);
+      pos = (int)(lb + min(eb, quota));
       ++lb;
     } else {
-      if (eb < quota) pos = base + lb + eb;
+      if (eb < quota) pos = (int)(lb + eb);
       ++eb;
     }
-    if (pos >= 0) {
-      const uint32_t i = (uint32_t)(tid * 64 + j);
-      act[pos] = (uint32_t)start + i;
-      if (wc) wc[pos] = w[i];
-    }
+    if (pos >= 0) ids[pos + 2 * (pos >> 6)] = (uint16_t)(tid * 64 + j);
+  }
+  __syncthreads();
+  const int n = (int)(tc.x + min((long long)tc.y, quota));
+  for (int p = tid; p < n; p += 128) {
+    const uint32_t i = ids[p + 2 * (p >> 6)];
+    act[base + p] = (uint32_t)start + i;
+    if (wc) wc[base + p] = w[i];
   }
 }
 
