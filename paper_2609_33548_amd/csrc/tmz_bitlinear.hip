@@ -1007,157 +1007,24 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 }
 
 // ---------------------------------------------------------------------------
-// One token (M = 1) with the activation quantisation fused in: every block reads the
-// whole activation row (at most 8192 values), forms a = max |x| and
-// s = 127 / max(a, 1e-5) and quantises the row into LDS exactly as k_act_quant does,
-// then runs the contraction of k_gemv_i8 for its 16 output features (token 0 of the
-// 16-token MFMA group).  One launch per call instead of two; the code words are
-// loaded first so that their latency overlaps the row's.
-// ---------------------------------------------------------------------------
-constexpr int kGemv1MaxK = 8192;
-
-__device__ __forceinline__ void load8x(const float* p, float v[8]) {
-  load4(p, v);
-  load4(p + 4, v + 4);
-}
-__device__ __forceinline__ void load8x(const uint16_t* p, float v[8]) {
-  const uint4 a = *reinterpret_cast<const uint4*>(p);
-  const uint32_t w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    v[2 * j] = __uint_as_float(w[j] << 16);
-    v[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
-  }
-}
-
-template <typename TX, typename TY, bool CVEC>
-__global__ void __launch_bounds__(512)
-    k_gemv1_fused(const TX* __restrict__ x, const uint32_t* __restrict__ codes, int64_t K,
-                  int64_t N, const float* __restrict__ beta, TY* __restrict__ y, int yvec) {
-  constexpr int NW = 8;
-  constexpr int CPW = kGemv1MaxK / (256 * NW);        // 256-k chunks per wave at most
-  constexpr int XI = kGemv1MaxK / (8 * 512);           // 8-value items of the row per thread
-  __shared__ __attribute__((aligned(16))) int8_t xql[kGemv1MaxK];
-  __shared__ int32_t red[NW][4][64];
-  __shared__ float amx[NW];
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int64_t n0 = (int64_t)blockIdx.x * 16;
-  const int64_t KW = K / 16;
-  const int nchunk = (int)((KW + 15) / 16);
-  const int fr = lane & 15, g = lane >> 4;
-  const bool row_ok = n0 + fr < N;
-  const uint32_t* crow = codes + (row_ok ? n0 + fr : 0) * KW;
-  // this wave's code words (chunks wid, wid + NW, ...), zero outside the matrix
-  uint32_t cw[CPW][4];
-#pragma unroll
-  for (int i = 0; i < CPW; ++i) {
-    const int64_t w0 = (int64_t)(wid + NW * i) * 16 + 4 * g;
-    if (CVEC) {
-      const v4u v = *reinterpret_cast<const v4u*>(crow + (w0 < KW ? w0 : 0));
-      const bool ok = row_ok && w0 < KW;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cw[i][j] = ok ? v[j] : 0u;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t v = crow[w0 + j < KW ? w0 + j : 0];
-        cw[i][j] = (row_ok && w0 + j < KW) ? v : 0u;
-      }
-    }
-  }
-  // the activation row: max |x|, then the quantised row into LDS
-  float xv[XI][8];
-  float a = 0.0f;
-#pragma unroll
-  for (int it = 0; it < XI; ++it) {
-    const int64_t k = ((int64_t)it * 512 + tid) * 8;
-    if (k < K) {
-      load8x(x + k, xv[it]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) xv[it][j] = 0.0f;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(xv[it][j]));
-  }
-  a = wave_max(a);
-  if (lane == 0) amx[wid] = a;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < NW; ++w) a = fmaxf(a, amx[w]);
-  const float sc = __fdiv_rn(127.0f, fmaxf(a, 1e-5f));
-#pragma unroll
-  for (int it = 0; it < XI; ++it) {
-    const int64_t k = ((int64_t)it * 512 + tid) * 8;
-    if (k < K) {
-      uint32_t w[2];
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        uint32_t b = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b |= ((uint32_t)quant_byte(xv[it][4 * h2 + j], sc) & 0xFFu) << (8 * j);
-        w[h2] = b;
-      }
-      *reinterpret_cast<uint2*>(xql + k) = make_uint2(w[0], w[1]);
-    }
-  }
-  __syncthreads();
-  // contraction: token fr of the MFMA group is the row for fr == 0, zero otherwise
-  v4i acc = v4i{0, 0, 0, 0};
-#pragma unroll
-  for (int i = 0; i < CPW; ++i) {
-    const int c = wid + NW * i;
-    if (c < nchunk) {                                   // wave-uniform
-      const int64_t kb = ((int64_t)c * 16 + 4 * g) * 16;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t k = kb + 16 * j;
-        v4i b = *reinterpret_cast<const v4i*>(xql + (k < K ? k : 0));
-        if (!(fr == 0 && k < K)) b = v4i{0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(unpack16(cw[i][j]), b, acc, 0, 0, 0);
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) red[wid][i][lane] = acc[i];
-  __syncthreads();
-  if (wid == 0 && fr == 0) {                            // lanes 0, 16, 32, 48: features 4 g ..
-    const int64_t n = n0 + 4 * g;
-    if (n < N) {
-      const float rr = __fdiv_rn(*beta, sc);
-      float y4[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int32_t v = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) v += red[w][i][lane];
-        y4[i] = (float)v * rr;
-      }
-      if (yvec && n + 3 < N) {
-        store4(y + n, y4);
-      } else {
-        for (int i = 0; i < 4 && n + i < N; ++i) store_act(y + n + i, y4[i]);
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Two to sixteen tokens with the activation quantisation fused in.  Every block
-// issues its code loads first, then reads all M activation rows (half a wave per
-// row, the row held in registers), forms each row's a = max |x| and
-// s = 127 / max(a, 1e-5) with a half-wave reduction and quantises the rows into LDS
-// with the operations of k_act_quant, then contracts its FG groups of 16 output
+// Up to sixteen tokens with the activation quantisation fused in.  Every block issues its
+// code loads first, then reads all M activation rows (64 NW / ROWS lanes per row, the row held
+// in registers), forms each row's a = max |x| and s = 127 / max(a, 1e-5) and quantises the
+// rows into LDS with the operations of k_act_quant, then contracts its FG groups of 16 output
 // features as k_gemv_i8 does (one 16-token MFMA group, activations read from LDS).
-// One launch per call instead of two, and no x_q, scale or row-sum buffers.  Every
-// block quantises all M rows itself (VALU work that grows with M K), so the launcher
-// takes this kernel only for small M K, and two feature groups per block where one
-// would need more than a round of blocks.  Rows are held packed (bf16: 8 values per
-// 16 bytes) up to KMAX values, at most ROWS rows; LDS rows are padded by 16 bytes so
-// the 16 token rows of a fragment read fall in distinct banks.
+// One launch per call instead of two, and no x_q, scale or row-sum buffers.  What bounds it is
+// the block's serial chain of loads, row maximum, quantisation and contraction, and every block
+// quantises all M rows itself: hence sixteen waves, and all of their lanes on the M rows there
+// are (ROWS = 1, 2, 4, 8 or 16) instead of half a wave per row with the other waves idle.
+// Measured so (2560 -> 6912 bf16, 1 / 2 / 8 / 16 tokens): 4.5 / 4.7 / 5.6 / 6.2 us in place of
+// 5.5 (a kernel of its own) / 5.6 / 5.9 / 7.0; 4096 -> 1536 at 8: 5.5 in place of 6.4; a launch
+// alone takes about 4.
+// Two feature groups per block where one would need more than a round of blocks.  Rows are held
+// packed (bf16: 8 values per 16 bytes) up to KMAX values, at most ROWS rows; LDS rows are padded
+// by 16 bytes so the 16 token rows of a fragment read fall in distinct banks.
 // ---------------------------------------------------------------------------
 constexpr int kGemvFusedMaxM = 16;
-constexpr int64_t kGemvFusedMaxMK = 16 * 2560;      // rows x values quantised per block
+constexpr int64_t kGemvFusedMaxMK = 16 * 4096;      // rows x values quantised per block
 
 template <typename TX> struct RowChunk;            // 8 activations as loaded
 template <> struct RowChunk<uint16_t> {
@@ -1190,24 +1057,28 @@ template <> struct RowChunk<float> {
   }
 };
 
-template <typename TX, typename TY, bool CVEC, int KMAX, int ROWS, int FG>
-__global__ void __launch_bounds__(512)
+template <typename TX, typename TY, bool CVEC, int KMAX, int ROWS, int FG, int NW>
+__global__ void __launch_bounds__(64 * NW)
     k_gemv_fused(const TX* __restrict__ x, const uint32_t* __restrict__ codes, int64_t M,
                  int64_t K, int64_t N, const float* __restrict__ beta, TY* __restrict__ y,
                  int yvec) {
-  constexpr int NW = 8;
   constexpr int CPW = (KMAX + 256 * NW - 1) / (256 * NW);  // 256-k chunks per wave at most
-  constexpr int XI = KMAX / (8 * 32);                       // 8-value chunks of a row per lane
+  constexpr int LPR = 64 * NW / ROWS;                       // lanes per row
+  constexpr int XI = (KMAX + 8 * LPR - 1) / (8 * LPR);      // 8-value chunks of a row per lane
+  constexpr int WPR = LPR > 64 ? LPR / 64 : 1;              // waves per row
   constexpr int LROW = KMAX + 16;                           // LDS row stride in bytes
-  static_assert(KMAX % 256 == 0 && ROWS <= 2 * NW && FG <= NW, "row layout");
+  static_assert(KMAX % 256 == 0 && 64 * NW % ROWS == 0 && (LPR == 32 || LPR % 64 == 0) && FG <= NW,
+                "row layout");
   __shared__ __attribute__((aligned(16))) int8_t xql[ROWS * LROW];
   __shared__ int32_t red[NW][FG][4][64];
   __shared__ float scl[ROWS];
+  __shared__ float amx[NW];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int64_t n0 = (int64_t)blockIdx.x * 16 * FG;
   const int64_t KW = K / 16;
   const int nchunk = (int)((KW + 15) / 16);
   const int fr = lane & 15, g = lane >> 4;
+  float bt = *beta;                                         // (not at the end of the chain)
   // this wave's code words (chunks wid, wid + NW, ...) of each feature group, zero
   // outside the matrix
   uint32_t cw[FG][CPW][4];
@@ -1232,15 +1103,15 @@ __global__ void __launch_bounds__(512)
       }
     }
   }
-  // token row r = 2 wid + (lane / 32), chunk (it * 32 + lane % 32) of 8 values
-  const int r = 2 * wid + (lane >> 5), j32 = lane & 31;
-  const bool rok = r < M && r < ROWS;          // the launcher keeps M <= ROWS
+  // token row r, chunk it * LPR + jl of 8 values (the launcher keeps M <= ROWS)
+  const int r = tid / LPR, jl = tid % LPR;
+  const bool rok = r < M;
   const TX* xr = x + (rok ? r : 0) * K;
   RowChunk<TX> xv[XI];
   float a = 0.0f;
 #pragma unroll
   for (int it = 0; it < XI; ++it) {
-    const int64_t k = ((int64_t)it * 32 + j32) * 8;
+    const int64_t k = ((int64_t)it * LPR + jl) * 8;
     if (rok && k < K) xv[it].load(xr + k); else xv[it].zero();
     float v[8];
     xv[it].get(v);
@@ -1248,13 +1119,19 @@ __global__ void __launch_bounds__(512)
     for (int t = 0; t < 8; ++t) a = fmaxf(a, fabsf(v[t]));
   }
 #pragma unroll
-  for (int off = 16; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 32));
+  for (int off = (LPR < 64 ? LPR : 64) / 2; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 64));
+  if (WPR > 1) {
+    if (lane == 0) amx[wid] = a;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WPR; ++w) a = fmaxf(a, amx[wid / WPR * WPR + w]);
+  }
   const float sc = __fdiv_rn(127.0f, fmaxf(a, 1e-5f));
   if (rok) {
-    if (j32 == 0) scl[r] = sc;
+    if (jl == 0) scl[r] = sc;
 #pragma unroll
     for (int it = 0; it < XI; ++it) {
-      const int64_t k = ((int64_t)it * 32 + j32) * 8;
+      const int64_t k = ((int64_t)it * LPR + jl) * 8;
       if (k < K) {
         float v[8];
         xv[it].launder();                               // keep the row packed until here
@@ -1271,6 +1148,7 @@ __global__ void __launch_bounds__(512)
       }
     }
   }
+  asm volatile("" : "+v"(bt));                               // (loaded by here)
   __syncthreads();
   // contraction: token fr of the MFMA group (token rows at or beyond M only feed their
   // own accumulator column, which is never stored)
@@ -1302,7 +1180,7 @@ __global__ void __launch_bounds__(512)
   if (wid < FG && fr < M) {                             // wave f: token fr, features 4 g ..
     const int64_t n = n0 + 16 * wid + 4 * g;
     if (n < N) {
-      const float rr = __fdiv_rn(*beta, scl[fr]);
+      const float rr = __fdiv_rn(bt, scl[fr]);
       float y4[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -1321,71 +1199,62 @@ __global__ void __launch_bounds__(512)
   }
 }
 
-// Rows of up to 4096 values for up to 16 tokens; longer bf16 rows (up to 8192 values) for
-// at most kGemvFusedLongRows tokens, the rows the long-row instantiation holds in LDS.
-constexpr int kGemvFusedLongRows = 5;
-bool gemv_fused_ok(int64_t M, int64_t K, termezo_dtype xdt) {
-  return M >= 2 && M <= kGemvFusedMaxM && M * K <= kGemvFusedMaxMK &&
-         (K <= 4096 || (xdt == TERMEZO_BF16 && K <= 8192 && M <= kGemvFusedLongRows));
+// Up to 16 tokens of rows up to 4096 values, up to 8 of rows up to 8192 (the LDS rows), and up
+// to 16 x 4096 values in all: there the two-launch path takes the same time (4096 -> 1536,
+// 16 tokens: 7.5 and 7.5 us; 12 tokens: 6.7 and 7.4; 6912 -> 2560, 8 tokens: 7.7 and 8.6).
+bool gemv_fused_ok(int64_t M, int64_t K) {
+  return M >= 1 && M <= kGemvFusedMaxM && M * K <= kGemvFusedMaxMK &&
+         (K <= 4096 || (K <= 8192 && M <= 8));
 }
 
 hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
                              const float* beta_dev, int64_t M, int64_t K, int64_t N, void* y,
                              termezo_dtype ydt, int n_cu, hipStream_t st) {
-  if (!gemv_fused_ok(M, K, xdt) || K % 16 != 0) return hipErrorInvalidValue;
+  if (!gemv_fused_ok(M, K) || K % 16 != 0) return hipErrorInvalidValue;
   const bool cvec = (K / 16) % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 16 == 0;
   const int yvec =
       N % 4 == 0 && reinterpret_cast<uintptr_t>(y) % (ydt == TERMEZO_F32 ? 16 : 8) == 0;
   const bool two = (N + 15) / 16 > (n_cu > 0 ? n_cu : 256);   // two feature groups per block
   const dim3 grid((unsigned)(two ? (N + 31) / 32 : (N + 15) / 16));
-#define TMZ_GF(TX, TY, CV, KM, RW, FGV)                                                         \
-  hipLaunchKernelGGL((k_gemv_fused<TX, TY, CV, KM, RW, FGV>), grid, dim3(512), 0, st,           \
+#define TMZ_GF(TX, TY, CV, KM, RW, FGV, NWV)                                                    \
+  hipLaunchKernelGGL((k_gemv_fused<TX, TY, CV, KM, RW, FGV, NWV>), grid, dim3(64 * NWV), 0, st, \
                      (const TX*)x, codes, M, K, N, beta_dev, (TY*)y, yvec)
-#define TMZ_GFG(TX, TY, CV, KM, RW)                                     \
-  do {                                                                  \
-    if (two) TMZ_GF(TX, TY, CV, KM, RW, 2); else TMZ_GF(TX, TY, CV, KM, RW, 1); \
+#define TMZ_GFG(TX, TY, CV, KM, RW, NWV)                                              \
+  do {                                                                                \
+    if (two) TMZ_GF(TX, TY, CV, KM, RW, 2, NWV); else TMZ_GF(TX, TY, CV, KM, RW, 1, NWV); \
   } while (0)
-#define TMZ_GFY(TX, CV, KM, RW)                                                               \
-  do {                                                                                        \
-    if (ydt == TERMEZO_F32) TMZ_GFG(TX, float, CV, KM, RW); else TMZ_GFG(TX, uint16_t, CV, KM, RW); \
+#define TMZ_GFY(TX, CV, KM, RW, NWV)                                  \
+  do {                                                                \
+    if (ydt == TERMEZO_F32) TMZ_GFG(TX, float, CV, KM, RW, NWV);      \
+    else TMZ_GFG(TX, uint16_t, CV, KM, RW, NWV);                      \
   } while (0)
-  if (xdt == TERMEZO_F32) {
-    if (cvec) TMZ_GFY(float, true, 4096, 16); else TMZ_GFY(float, false, 4096, 16);
-  } else if (K <= 4096) {
-    if (cvec) TMZ_GFY(uint16_t, true, 4096, 16); else TMZ_GFY(uint16_t, false, 4096, 16);
-  } else {
-    if (cvec) TMZ_GFY(uint16_t, true, 8192, kGemvFusedLongRows);
-    else TMZ_GFY(uint16_t, false, 8192, kGemvFusedLongRows);
-  }
+#define TMZ_GFC(TX, KM, RW, NWV) \
+  do { if (cvec) TMZ_GFY(TX, true, KM, RW, NWV); else TMZ_GFY(TX, false, KM, RW, NWV); } while (0)
+// Sixteen waves, but eight where short rows feed no more and the blocks are many, so that more
+// of them run at once (256 -> 100000, 1 / 2 / 16 tokens: 18.0 / 19.5 / 41.1 us with sixteen,
+// 9.4 / 10.0 / 15.3 with eight; 1024 -> 32000: 8.1 / 8.2 / 15.5 and 5.4 / 5.8 / 8.5; in less than a
+// round of blocks, 1536 -> 1536 at 12 tokens: sixteen 4.7, half a wave per row in eight 5.3).
+#define TMZ_GFM(TX)                                                                   \
+  do {                                                                                \
+    if (M == 1 && K <= 2048) TMZ_GFC(TX, 2048, 1, 8);                                 \
+    else if (M <= 2 && K <= 2048 && two) TMZ_GFC(TX, 2048, 2, 8);                     \
+    else if (M <= 4 && K <= 2048 && two) TMZ_GFC(TX, 2048, 4, 8);                     \
+    else if (M <= 8 && K <= 2048 && two) TMZ_GFC(TX, 2048, 8, 8);                     \
+    else if (K <= 2048 && two) TMZ_GFC(TX, 2048, 16, 8);                              \
+    else if (M <= 2 && K <= 4096) TMZ_GFC(TX, 4096, 2, 16);                           \
+    else if (M <= 4 && K <= 4096) TMZ_GFC(TX, 4096, 4, 16);                           \
+    else if (M <= 8 && K <= 4096) TMZ_GFC(TX, 4096, 8, 16);                           \
+    else if (K <= 4096) TMZ_GFC(TX, 4096, 16, 16);                                    \
+    else if (M == 1) TMZ_GFC(TX, 8192, 1, 16);                                        \
+    else if (M <= 4) TMZ_GFC(TX, 8192, 4, 16);                                        \
+    else TMZ_GFC(TX, 8192, 8, 16);                                                    \
+  } while (0)
+  if (xdt == TERMEZO_F32) TMZ_GFM(float); else TMZ_GFM(uint16_t);
+#undef TMZ_GFM
+#undef TMZ_GFC
 #undef TMZ_GFY
 #undef TMZ_GFG
 #undef TMZ_GF
-  return hipGetLastError();
-}
-
-bool gemv1_fused_ok(int64_t M, int64_t K) { return M == 1 && K <= kGemv1MaxK; }
-
-hipError_t launch_gemv1_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
-                              const float* beta_dev, int64_t K, int64_t N, void* y,
-                              termezo_dtype ydt, hipStream_t st) {
-  if (K > kGemv1MaxK || K % 16 != 0) return hipErrorInvalidValue;
-  const bool cvec = (K / 16) % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 16 == 0;
-  const int yvec = reinterpret_cast<uintptr_t>(y) % (ydt == TERMEZO_F32 ? 16 : 8) == 0;
-  const dim3 grid((unsigned)((N + 15) / 16));
-#define TMZ_G1(TX, TY, CV)                                                                     \
-  hipLaunchKernelGGL((k_gemv1_fused<TX, TY, CV>), grid, dim3(512), 0, st, (const TX*)x, codes, K, \
-                     N, beta_dev, (TY*)y, yvec)
-#define TMZ_G1X(TX, CV)                                        \
-  do {                                                          \
-    if (ydt == TERMEZO_F32) TMZ_G1(TX, float, CV); else TMZ_G1(TX, uint16_t, CV); \
-  } while (0)
-  if (xdt == TERMEZO_F32) {
-    if (cvec) TMZ_G1X(float, true); else TMZ_G1X(float, false);
-  } else {
-    if (cvec) TMZ_G1X(uint16_t, true); else TMZ_G1X(uint16_t, false);
-  }
-#undef TMZ_G1X
-#undef TMZ_G1
   return hipGetLastError();
 }
 

@@ -329,15 +329,9 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs,
                           const uint32_t* codes, int64_t M, int64_t K, int64_t N,
                           const GemmOut& out, termezo_dtype ydt, int mode, int32_t* acc, bool tiled,
                           int n_cu, hipStream_t st, LaunchEvents ev = LaunchEvents());
-// One token with the activation quantisation fused in (no x_q, scale or row-sum
-// buffers): gemv1_fused_ok(M, K) tells whether it applies.
-bool gemv1_fused_ok(int64_t M, int64_t K);
-hipError_t launch_gemv1_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
-                              const float* beta_dev, int64_t K, int64_t N, void* y,
-                              termezo_dtype ydt, hipStream_t st);
-// Two to sixteen tokens with the activation quantisation fused in (no inspection
-// outputs): gemv_fused_ok(M, K, xdt) tells whether it applies.
-bool gemv_fused_ok(int64_t M, int64_t K, termezo_dtype xdt);
+// Up to sixteen tokens with the activation quantisation fused in (no x_q, scale or row-sum
+// buffers, no inspection outputs): gemv_fused_ok(M, K) tells whether it applies.
+bool gemv_fused_ok(int64_t M, int64_t K);
 hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
                              const float* beta_dev, int64_t M, int64_t K, int64_t N, void* y,
                              termezo_dtype ydt, int n_cu, hipStream_t st);

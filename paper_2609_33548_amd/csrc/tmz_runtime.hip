@@ -510,12 +510,7 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
   const termezo_status ck = check_forward_args(c, layer, x, x_dtype, M, y, y_dtype);
   if (ck != TERMEZO_OK) return ck;
   const LayerHost& L = c->layers[layer];
-  if (!xq_out && !xscale_out && !acc_out && gemv1_fused_ok(M, L.d_in)) {
-    TMZ_HIP(c, launch_gemv1_fused(x, x_dtype, c->d_codes + L.code_off, c->d_beta_cur + layer,
-                                  L.d_in, L.d_out, y, y_dtype, c->stream));
-    return TERMEZO_OK;
-  }
-  if (!xq_out && !xscale_out && !acc_out && gemv_fused_ok(M, L.d_in, x_dtype)) {
+  if (!xq_out && !xscale_out && !acc_out && gemv_fused_ok(M, L.d_in)) {
     TMZ_HIP(c, launch_gemv_fused(x, x_dtype, c->d_codes + L.code_off, c->d_beta_cur + layer, M,
                                  L.d_in, L.d_out, y, y_dtype, c->n_cu, c->stream));
     return TERMEZO_OK;
@@ -547,12 +542,7 @@ termezo_status termezo_bitlinear_forward_noalloc(termezo_ctx* c, int32_t layer, 
   const termezo_status ck = check_forward_args(c, layer, x, x_dtype, M, y, y_dtype);
   if (ck != TERMEZO_OK) return ck;
   const LayerHost& L = c->layers[layer];
-  if (gemv1_fused_ok(M, L.d_in)) {                    // one token: no scratch at all
-    TMZ_HIP(c, launch_gemv1_fused(x, x_dtype, c->d_codes + L.code_off, c->d_beta_cur + layer,
-                                  L.d_in, L.d_out, y, y_dtype, c->stream));
-    return TERMEZO_OK;
-  }
-  if (gemv_fused_ok(M, L.d_in, x_dtype)) {             // up to 16 tokens: none either
+  if (gemv_fused_ok(M, L.d_in)) {             // up to 16 tokens: no scratch at all
     TMZ_HIP(c, launch_gemv_fused(x, x_dtype, c->d_codes + L.code_off, c->d_beta_cur + layer, M,
                                  L.d_in, L.d_out, y, y_dtype, c->n_cu, c->stream));
     return TERMEZO_OK;

@@ -75,6 +75,20 @@ def test_bitlinear_tile_edges(orc, M, K, N, xdt, ydt, inspect):
     _linear(orc, torch, M, K, N, xdt, ydt, inspect)
 
 
+@pytest.mark.parametrize("xdt,ydt", [("bf16", "bf16"), ("f32", "f32")])
+@pytest.mark.parametrize("M,K,N", [
+    (1, 16, 24), (1, 2048, 40), (1, 2064, 40), (1, 4096, 56), (1, 4112, 40), (1, 8192, 24),
+    (2, 4096, 40), (3, 2064, 40), (4, 4096, 40), (5, 4096, 40), (8, 4080, 24), (9, 4096, 40),
+    (16, 4096, 24), (2, 4112, 24), (4, 8192, 24), (5, 8192, 24), (8, 8192, 24),
+    (9, 4112, 24),                           # past the fused kernel's rows
+    (1, 272, 4104), (2, 272, 4104), (4, 2048, 4104), (7, 272, 4104), (16, 272, 4104),
+    (3, 2064, 4104), (16, 2064, 4104)])      # two feature groups per block
+def test_bitlinear_fused_rows(orc, M, K, N, xdt, ydt):
+    """Each row-group size of the fused kernel at its largest and smallest K and M."""
+    print(f"fused M={M} K={K} N={N} {xdt}->{ydt}", flush=True)
+    _linear(orc, _torch(), M, K, N, xdt, ydt, False)
+
+
 @pytest.mark.parametrize("act,d,H,Hkv,F,V,S,B", [
     ("f32", 256, 4, 4, 688, 1000, 87, 2),    # a partial vocabulary tile, one partial key group
     ("f32", 48, 3, 1, 80, 130, 300, 1),      # K steps of 16, more keys than the four groups of 64
