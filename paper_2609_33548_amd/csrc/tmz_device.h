@@ -331,8 +331,11 @@ __device__ __forceinline__ void dma4(const void* gptr, uint32_t lds_base) {
       : "memory", "m0");
 }
 
-// A raw buffer of `bytes` bytes at p (loads past its end return nothing), and the direct
-// load through it: 16 bytes per lane from p + voff + soff.
+// A raw buffer of `bytes` bytes at p, and the direct load through it: 16 bytes per lane from
+// p + voff + soff.  A lane whose voff lies past the end fetches nothing.  The scalar part must
+// not carry anything that the range check has to cover (whether it counts, and how the
+// check subtracts it, is not relied on): soff < bytes, and voff + soff in the buffer for every
+// lane whose voff is.
 typedef int v4i_rsrc __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v4i_rsrc buffer_of(const void* p, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)p;

@@ -19,6 +19,7 @@
 
 #include "tmz_device.h"
 #include "tmz_internal.h"
+#include "tmz_tiles.h"
 
 namespace tmz {
 
@@ -1481,9 +1482,10 @@ __global__ void __launch_bounds__(512) k_lmhead_bf16(const uint16_t* __restrict_
 // banks.  K assignment: in sub-step ks, lane half h supplies chunk
 // h * (2 BK / 32) + ks of its row for both operands.
 // Any number of tokens and vocabulary columns: the operands of a tile are buffers that end
-// with the matrices, so rows past the end fetch nothing, and in the last column tile the
-// columns past V count as minus infinity (1998 tokens x 32,000 at d 1536: 305 us on the
-// register-staged kernel, 179 us here).  Requires d % BK == 0.
+// with the matrices and a lane's offset holds its whole row, so rows past the end fetch
+// nothing, and in the last column tile the columns past V count as minus infinity (1998 tokens
+// x 32,000 at d 1536: 305 us on the register-staged kernel, 179 us here).  Requires
+// d % BK == 0.
 template <int STAGES, int BK, int NWN>
 __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ E, int64_t M,
@@ -1493,36 +1495,28 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
                                                           int64_t nvt) {
   constexpr int BM = 256, BN = 256, WM = 128, WN = BN / NWN, NT = 128 * NWN;
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int ROWB = 2 * BK, CPR = ROWB / 16;   // bytes and 16-byte chunks per stage row
+  using Loads = RowLoads<BK, NT>;
+  constexpr int ROWB = Loads::kRowB, CPR = Loads::kChunks;
   constexpr int OPB = BM * ROWB;                  // bytes per operand per stage
   constexpr int KS = CPR / 2;                     // MFMA sub-steps per stage
-  constexpr int IPW = BM * CPR / NT;              // loads per operand per wave per stage
-  static_assert(CPR == 8 || CPR == 4, "stage width");
+  constexpr int IPW = Loads::kPerWave;            // loads per operand per wave per stage
   static_assert(STAGES >= 2 && STAGES * 2 * OPB + BN / WN * BM * 8 <= 152 * 1024, "LDS");
   __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES * 2 * OPB];
   __shared__ float red[BN / WN][BM][2];           // per wave column: token max and sum of exp
   __shared__ int32_t lbl[BM];
-  auto sw = [](int row) __attribute__((always_inline)) {
-    return CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3);
-  };
+  auto sw = [](int row) __attribute__((always_inline)) { return Loads::swz(row); };
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid / (BN / WN), wn = wid % (BN / WN);
   const int64_t nmt = (M + BM - 1) / BM, ntiles = nmt * nvt;
   const int nk = (int)(d / BK);
 
-  // load j of wave w fills the 64 LDS chunks (w * IPW + j) * 64 .. + 63 of an operand:
-  // RPL rows of CPR chunks.  The chunk swizzle of those rows depends on j only through
-  // its parity, so two per-lane offsets serve every load of both operands (the rest of the
-  // offset is wave-uniform).
-  constexpr int RPL = 64 / CPR;                   // rows per 1 KB load
-  static_assert(IPW % 2 == 0, "loads per wave");
-  uint32_t off[2];
+  // load j of wave w fills the 64 LDS chunks (w * IPW + j) * 64 .. + 63 of an operand; the
+  // same per-lane offsets serve both operands.  (One operand's loads after the other's:
+  // alternating, 4096 x 128,256 at d 2560 took 2325 us in place of 2200.)
+  uint32_t off[IPW];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int row = (wid * IPW + p) * RPL + lane / CPR, lc = (lane % CPR) ^ sw(row);
-    off[p] = (uint32_t)(row * d * 2) + 16 * lc;
-  }
+  for (int j = 0; j < IPW; ++j) off[j] = Loads::lane_off(wid, j, lane, d);
   v4i_rsrc arsrc, brsrc;
   // tile it of the grouped (XCD-aware) order: its origin and its operands
   auto tile = [&](int64_t it, int64_t& m0, int64_t& n0) __attribute__((always_inline)) {
@@ -1536,14 +1530,12 @@ __global__ void __launch_bounds__(128 * NWN) k_lmhead_dma(const uint16_t* __rest
   const uint32_t wbase = __builtin_amdgcn_readfirstlane(wid) * IPW * 1024u;
   auto Ast = [&](int st) { return lds + st * 2 * OPB; };
   auto issue = [&](int kt, int st) __attribute__((always_inline)) {
-    const uint32_t koff = (uint32_t)kt * ROWB, rstep = (uint32_t)(RPL * d * 2);
+    const uint32_t koff = Loads::step_off(kt);
     const uint32_t ab = lds_offset(Ast(st)) + wbase, bb = ab + OPB;
 #pragma unroll
-    for (int j = 0; j < IPW; ++j) {
-      const uint32_t roff = (j & ~1) * rstep + koff;
-      dma16_buf(off[j & 1], arsrc, roff, ab + 1024u * j);
-      dma16_buf(off[j & 1], brsrc, roff, bb + 1024u * j);
-    }
+    for (int j = 0; j < IPW; ++j) dma16_buf(off[j], arsrc, koff, ab + 1024u * j);
+#pragma unroll
+    for (int j = 0; j < IPW; ++j) dma16_buf(off[j], brsrc, koff, bb + 1024u * j);
   };
 
   typedef uint32_t v4u __attribute__((ext_vector_type(4)));

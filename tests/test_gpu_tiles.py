@@ -177,3 +177,46 @@ def test_mask_build_and_dense_runs(orc, shapes, bf16, rho0, inclusive):
     got = np.concatenate([t.float().cpu().numpy().ravel() for t in tensors])
     assert np.array_equal(got, ref.w)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,H,V,B,S", [
+    (64, 1, 32003, 5, 123),                  # 3 x 126 tiles, more than there are compute units
+    (192, 2, 515, 3, 86),                    # three columns in the last tile, two rows
+    (128, 2, 256, 1, 257)])                  # one row in the last tile, whole columns
+def test_lmhead_partial_tiles(d, H, V, B, S):
+    """The LM head alone, per position against 64 bits.  The projections' codes are all zero, so
+    the head's input is the normalised embedding of the token; with entries of +-1/16 that is
+    +-1 exactly (the eps of the norm takes 1.3e-3, less than half a bf16 step below 1) and every
+    logit is exact in fp32.  A loss is the difference of the log-sum and a logit; the log-sum is off
+    by the rounding of the exponentials and their sums (a few 2^-23 of the sum, an absolute error of
+    its logarithm) and of the result (2^-24 of it): 1e-6 + 1e-6 of the log-sum.  A token's own column
+    weighs e^(d/16), a few percent to all of the sum: a tile left out, counted twice or taken from
+    other rows moves the losses of its tokens and labels by 5e-4 and more."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print(f"lm head d={d} V={V} M={B * S}", flush=True)
+    dev = torch.device("cuda")
+    shapes = [(d, d), (d, d), (d, d), (d, d), (64, d), (64, d), (d, 64)]
+    ctx = termezo.Context([torch.zeros(s, dtype=torch.bfloat16, device=dev) for s in shapes])
+    ctx.build_mask(0.01)
+    g = torch.Generator().manual_seed(9)
+    E = ((torch.randint(0, 2, (V, d), generator=g) * 2 - 1) * 0.0625).to(torch.bfloat16).to(dev)
+    tok = torch.randint(0, V, (B, S), generator=g, dtype=torch.int32)
+    tail = V - 1 - (V - 1) // 256 * 256 + 1                  # columns of the last tile
+    tok[:, ::5] = V - 1 - tok[:, ::5] % tail                 # many tokens and labels there
+    tok = tok.to(dev)
+    model = termezo.Model(ctx, 1, d, H, H, 64, V, E)
+    rows = torch.empty(B * S, device=dev)
+    ws = model.loss(tok, row_loss_dev=rows)
+    t = tok.flatten().long()
+    z = (E[t].double() * 16.0) @ E.double().t()
+    lse = torch.logsumexp(z, dim=1)
+    want = (lse - z.gather(1, torch.roll(t, -1)[:, None])[:, 0]).view(B, S)[:, :-1]
+    got = rows.view(B, S)
+    err = ((got[:, :-1].double() - want).abs() / (1.0 + lse.view(B, S)[:, :-1])).max().item()
+    print(f"  per position max {err:.2e} of 1 + log-sum", flush=True)
+    assert err <= 1e-6
+    assert bool((got[:, -1] == 0).all())
+    assert abs(ws - want.mean().item()) <= 1e-6 * (1.0 + lse.mean().item())
+    model.close()
+    ctx.close()
