@@ -137,6 +137,7 @@ termezo_status termezo_set_dense_requant(termezo_ctx* ctx, int32_t always_dense)
  * s_m = 127 / max(a_m, 1e-5), x_q = clamp(round_half_even(x * s_m), -128, 127);
  * acc[m][n] = sum_k x_q[m][k] * c[n][k] exactly in int32;
  * y[m][n] = float(acc) * (beta' / s_m) (rounded to bf16 if y is BF16).
+ * y may share memory with x: every row is quantised before y is written.
  * xq_out [M][d_in] int8, xscale_out [M] fp32 (s_m), acc_out [M][d_out] int32:
  * optional device outputs (nullable) for inspection.
  * Errors: INVALID_ARG (layer out of range, M <= 0, bad dtype, null x or y),

@@ -498,6 +498,18 @@ termezo_status check_forward_args(termezo_ctx* c, int32_t layer, const void* x,
   if (!c->codes_valid) return fail(c, TERMEZO_ERR_STATE, "no current codes (perturb first)");
   return TERMEZO_OK;
 }
+
+// Whether a call takes the fused small-M kernel.  Its blocks read x while others already write
+// y, so an output on the memory of the input goes through the quantised copy instead, which is
+// whole before anything is written.
+bool takes_fused(const LayerHost& L, const void* x, termezo_dtype x_dtype, int64_t M, const void* y,
+                 termezo_dtype y_dtype) {
+  if (!gemv_fused_ok(M, L.d_in)) return false;
+  const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+  const uintptr_t x1 = x0 + (uintptr_t)(M * L.d_in) * dtype_size(x_dtype);
+  const uintptr_t y1 = y0 + (uintptr_t)(M * L.d_out) * dtype_size(y_dtype);
+  return x1 <= y0 || y1 <= x0;
+}
 }  // namespace
 
 termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const void* x,
@@ -510,7 +522,7 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
   const termezo_status ck = check_forward_args(c, layer, x, x_dtype, M, y, y_dtype);
   if (ck != TERMEZO_OK) return ck;
   const LayerHost& L = c->layers[layer];
-  if (!xq_out && !xscale_out && !acc_out && gemv_fused_ok(M, L.d_in)) {
+  if (!xq_out && !xscale_out && !acc_out && takes_fused(L, x, x_dtype, M, y, y_dtype)) {
     TMZ_HIP(c, launch_gemv_fused(x, x_dtype, c->d_codes + L.code_off, c->d_beta_cur + layer, M,
                                  L.d_in, L.d_out, y, y_dtype, c->n_cu, c->stream));
     return TERMEZO_OK;
@@ -542,7 +554,7 @@ termezo_status termezo_bitlinear_forward_noalloc(termezo_ctx* c, int32_t layer, 
   const termezo_status ck = check_forward_args(c, layer, x, x_dtype, M, y, y_dtype);
   if (ck != TERMEZO_OK) return ck;
   const LayerHost& L = c->layers[layer];
-  if (gemv_fused_ok(M, L.d_in)) {             // up to 16 tokens: no scratch at all
+  if (takes_fused(L, x, x_dtype, M, y, y_dtype)) {   // up to 16 tokens: no scratch at all
     TMZ_HIP(c, launch_gemv_fused(x, x_dtype, c->d_codes + L.code_off, c->d_beta_cur + layer, M,
                                  L.d_in, L.d_out, y, y_dtype, c->n_cu, c->stream));
     return TERMEZO_OK;

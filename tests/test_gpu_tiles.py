@@ -89,6 +89,31 @@ def test_bitlinear_fused_rows(orc, M, K, N, xdt, ydt):
     _linear(orc, _torch(), M, K, N, xdt, ydt, False)
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("M,K,N,noalloc", [
+    (1, 256, 60000, False),                  # more blocks than run at once, for each row count
+    (16, 2576, 12992, False), (16, 2576, 12992, True),
+    (8, 4096, 4096, False), (7, 8192, 4096, False), (17, 2560, 2560, False)])
+def test_bitlinear_output_on_the_input(orc, M, K, N, noalloc, dt):
+    """y at the address of x: the result is that of separate buffers."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print(f"in place M={M} K={K} N={N} {dt} noalloc={noalloc}", flush=True)
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    W = torch.from_numpy(synth.latents(13, [N * K]).reshape(N, K)).cuda()
+    ctx = termezo.Context([W])
+    ctx.build_mask(0.01)
+    x = torch.from_numpy(synth.activations(14, M, K)).cuda().to(tdt)
+    want = torch.empty((M, N), dtype=tdt, device="cuda")
+    ctx.bitlinear_forward(0, x, want)
+    buf = torch.empty(M * max(K, N), dtype=tdt, device="cuda")
+    buf[:M * K] = x.flatten()
+    xb, yb = buf[:M * K].view(M, K), buf[:M * N].view(M, N)
+    (ctx.bitlinear_forward_noalloc if noalloc else ctx.bitlinear_forward)(0, xb, yb)
+    assert torch.equal(yb, want)
+    ctx.close()
+
+
 @pytest.mark.parametrize("act,d,H,Hkv,F,V,S,B", [
     ("f32", 256, 4, 4, 688, 1000, 87, 2),    # a partial vocabulary tile, one partial key group
     ("f32", 48, 3, 1, 80, 130, 300, 1),      # K steps of 16, more keys than the four groups of 64
