@@ -245,3 +245,66 @@ def test_lmhead_partial_tiles(d, H, V, B, S):
     assert abs(ws - want.mean().item()) <= 1e-6 * (1.0 + lse.mean().item())
     model.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("L,rho0", [(600, 2e-3), (2048, 2e-4), (257, 0.02), (256, 0.02)])
+def test_shrink_with_empty_layers(orc, L, rho0):
+    """Sets that leave layers empty, at the start, in the middle and at the end: the lists and
+    codes of every layer over steps that drop latents until none is left."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print(f"empty layers L={L} rho0={rho0}", flush=True)
+    shapes = [(16, 32)] * L
+    w = synth.latents(61, [512] * L, bf16=True)
+    ref = orc.TerMeZOOracle([orc.Layer(o, i) for o, i in shapes], w, bf16=True)
+    W = torch.from_numpy(w).cuda().to(torch.bfloat16).view(L, 16, 32)
+    ctx = termezo.Context(list(W))
+    assert ctx.build_mask(rho0) == ref.build_mask(rho0)
+    ks = [ref.k]
+    for t in range(12):
+        ctx.perturb(t, 1e-3, 1)
+        codes, _, _ = ref.perturb(t, 1e-3, 1)
+        lr = max(2e-5, rho0 / 200) if t < 8 else 0.1   # some leave per step, then the rest
+        k = ref.update(1.0, lr)
+        for l in range(0, L, 7):
+            assert np.array_equal(ctx.codes(l), codes[l]), (t, l)
+        assert ctx.update(1.0, lr) == k
+        for l in range(L):
+            assert np.array_equal(ctx.mask(l), ref.active[l]), (t, l)
+        ks.append(k)
+        if k == 0 and ks[-2] == 0:
+            break
+    print(f"  set sizes {ks}", flush=True)
+    assert ks[-1] == 0 and len(set(ks)) > 3
+    ctx.close()
+
+
+def test_update_of_an_empty_set_is_not_slower():
+    """2048 layers without a single active latent: an update costs no more than one of a
+    set with entries in every layer (twice as much is allowed for)."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print("time of an empty set", flush=True)
+    L = 2048
+    took = {}
+    for rho0 in (1.0, 2e-6):
+        W = torch.from_numpy(synth.latents(62, [512 * L], bf16=True)).cuda().to(torch.bfloat16)
+        ctx = termezo.Context(list(W.view(L, 16, 32)))
+        ctx.build_mask(rho0)
+        ctx.perturb(0, 1e-3, 1)
+        k = ctx.update(1000.0, 1e-3 if rho0 < 1 else 0.0)
+        assert (k == 0) == (rho0 < 1)
+        best = float("inf")
+        for t in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for s in range(10):
+                ctx.perturb(10 * t + s, 1e-3, 1)
+                ctx.update(0.0, 0.0, want_k=False)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100.0)
+        took[rho0] = best
+        ctx.close()
+    print(f"  us per step: {took}", flush=True)
+    assert took[2e-6] <= 2.0 * took[1.0]
