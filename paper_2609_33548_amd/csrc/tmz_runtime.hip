@@ -539,8 +539,8 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
   }
   if (!xs) xs = c->d_xs;
   if (xq_out && tiled)                                // the caller's copy, row-major
-    TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq_out, xs, c->d_xrs, false, c->n_cu, c->stream));
-  TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->n_cu, c->stream));
+    TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq_out, xs, c->d_xrs, false, c->stream));
+  TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, c->d_xrs, c->d_codes + L.code_off,
                                    c->d_beta_cur + layer, M, L.d_in, L.d_out, y, y_dtype, acc_out,
                                    tiled, c->n_cu, c->stream));
@@ -577,7 +577,7 @@ termezo_status termezo_bitlinear_forward_noalloc(termezo_ctx* c, int32_t layer, 
   int8_t* xq = reinterpret_cast<int8_t*>(base);
   float* xs = reinterpret_cast<float*>(base + xq_size);
   int32_t* xrs = reinterpret_cast<int32_t*>(base + xq_size + xs_bytes);
-  TMZ_HIP(c, launch_act_quant(x, x_dtype, M, L.d_in, xq, xs, xrs, tiled, c->n_cu, c->stream));
+  TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq, xs, xrs, tiled, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, xrs, c->d_codes + L.code_off, c->d_beta_cur + layer,
                                    M, L.d_in, L.d_out, y, y_dtype, nullptr, tiled, c->n_cu,
                                    c->stream));

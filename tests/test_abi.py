@@ -105,3 +105,17 @@ def test_bench_cpu_baseline_legs_are_combined_by_direction():
     assert t["value"] == 3.0 and t["cores"] == 1 and t["all_cores"]["cores"] == 16
     nested, a, b = bench.two_legs(lambda: {"perturb": {"value": 1.0, "unit": "GB/s"}}, {}, {})
     assert nested is None and a["perturb"]["value"] == 1.0
+
+
+def test_library_keeps_no_unguarded_process_wide_state():
+    """Contexts may be used from different threads, one each: what a call keeps belongs to its
+    context.  The only writable static objects are the scratch array's host stand-in and the
+    per-device cache of its address, which a mutex guards."""
+    import subprocess
+    from paper_2609_33548_amd import termezo
+    text = subprocess.run(["nm", "-C", termezo.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    names = [m.group(1) for m in re.finditer(r"^[0-9a-f]+ [bd] (.+)$", text, re.M)]
+    assert "(anonymous namespace)::g_scratch_mu" in names      # the listing shows static objects
+    ours = [n for n in names if "tmz::" in n or "termezo" in n or "anonymous namespace" in n]
+    assert sorted(ours) == ["(anonymous namespace)::g_scratch_addr",
+                            "(anonymous namespace)::g_scratch_mu"], ours
