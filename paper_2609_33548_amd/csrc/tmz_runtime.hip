@@ -527,20 +527,21 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
                                  L.d_in, L.d_out, y, y_dtype, c->n_cu, c->stream));
     return TERMEZO_OK;
   }
-  int8_t* xq = xq_out;
-  float* xs = xscale_out;
   termezo_status st = ensure_xs_capacity(c, M);       // the row sums live here in any case
   if (st != TERMEZO_OK) return st;
   const bool tiled = bitlinear_tiled_xq(M, L.d_in, L.d_out, y, y_dtype, c->n_cu);
-  if (!xq || tiled) {
+  const bool own = !xq_out || tiled;                  // the GEMM reads the library's copy of x_q
+  if (own) {
     st = ensure_xq_capacity(c, tiled ? xq_bytes(M, L.d_in) : M * L.d_in);
     if (st != TERMEZO_OK) return st;
-    xq = c->d_xq;
   }
-  if (!xs) xs = c->d_xs;
-  if (xq_out && tiled)                                // the caller's copy, row-major
-    TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq_out, xs, c->d_xrs, false, c->stream));
+  int8_t* xq = own ? c->d_xq : xq_out;
+  // the caller's outputs come from the last read of x: they may lie on its memory
+  float* xs = own && xq_out ? c->d_xs : xscale_out ? xscale_out : c->d_xs;
   TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->stream));
+  if (own && xq_out)                                  // the caller's copy, row-major
+    TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq_out, xscale_out ? xscale_out : xs,
+                                c->d_xrs, false, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, c->d_xrs, c->d_codes + L.code_off,
                                    c->d_beta_cur + layer, M, L.d_in, L.d_out, y, y_dtype, acc_out,
                                    tiled, c->n_cu, c->stream));

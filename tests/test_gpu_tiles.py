@@ -114,6 +114,32 @@ def test_bitlinear_output_on_the_input(orc, M, K, N, noalloc, dt):
     ctx.close()
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("K", [2560, 4096, 8192])
+def test_one_token_inspected_in_place(orc, K, dt):
+    """One token whose x_q and scale outputs lie on x itself: as with buffers of their own."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print(f"inspected in place K={K} {dt}", flush=True)
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    W = torch.from_numpy(synth.latents(15, [64 * K]).reshape(64, K)).cuda()
+    ctx = termezo.Context([W])
+    ctx.build_mask(0.01)
+    x = torch.from_numpy(synth.activations(16, 1, K)).cuda().to(tdt)
+    xq, s = torch.empty((1, K), dtype=torch.int8, device="cuda"), torch.empty(1, device="cuda")
+    want = torch.empty((1, 64), dtype=tdt, device="cuda")
+    ctx.bitlinear_forward(0, x, want, xq, s)
+    y = torch.empty_like(want)
+    on = x.clone()
+    ctx.bitlinear_forward(0, on, y, on.flatten().view(torch.int8)[:K])
+    assert torch.equal(y, want) and torch.equal(on.flatten().view(torch.int8)[:K], xq[0])
+    on = x.clone()
+    tail = on.flatten().view(torch.int8)[-4:].view(torch.float32)     # a scale on x's last bytes
+    ctx.bitlinear_forward(0, on, y, xq, tail)
+    assert torch.equal(y, want) and torch.equal(tail, s)
+    ctx.close()
+
+
 @pytest.mark.parametrize("act,d,H,Hkv,F,V,S,B", [
     ("f32", 256, 4, 4, 688, 1000, 87, 2),    # a partial vocabulary tile, one partial key group
     ("f32", 48, 3, 1, 80, 130, 300, 1),      # K steps of 16, more keys than the four groups of 64
