@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tmz_math.h"
+
 namespace tmz {
 
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -46,42 +48,12 @@ __device__ __forceinline__ U4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, ui
   return U4{c0, c1, c2, c3};
 }
 
-// ---------------------------------------------------------------------------
-// Natural log for Box-Muller radii, u in (0, 1]: u = m 2^e with
-// m in [sqrt(1/2), sqrt(2)); ln m = 2 atanh((m-1)/(m+1)) by its Taylor series
-// through the 11th power; ln2 split in an exact high part and a low part.
-// ---------------------------------------------------------------------------
-// The correctly rounded quotient n / d for the operands ln_unit has: d = m + 1 in [1.7, 2.5],
-// n = m - 1 zero or at least 2^-24, so nothing needs scaling and no special case occurs.  The
-// reciprocal estimate is refined once, the quotient corrected by its exact residual (equal
-// to the IEEE division for each of the 2^23 mantissas m, checked one by one).
-__device__ __forceinline__ float div_ln(float n, float d) {
-  float r = __builtin_amdgcn_rcpf(d);
-  r = fmaf(fmaf(-d, r, 1.0f), r, r);
-  const float q = n * r;
-  return fmaf(fmaf(-d, q, n), r, q);
-}
-
+// Natural log for Box-Muller radii, u in (0, 1] (the quotient from the hardware's reciprocal
+// estimate).
 __device__ __forceinline__ float ln_unit(float u) {
-  uint32_t bits = __float_as_uint(u);
-  int ex = int(bits >> 23) - 127;
-  uint32_t mant = bits & 0x7FFFFFu;
-  uint32_t mb = mant | 0x3F800000u;
-  if (mant > 0x3504F3u) {
-    mb -= 0x00800000u;
-    ex += 1;
-  }
-  const float m = __uint_as_float(mb);
-  const float f = div_ln(m - 1.0f, m + 1.0f);
-  const float f2 = 2.0f * f;
-  const float t = f * f;
-  float p = fmaf(0x1.745d18p-4f, t, 0x1.c71c72p-4f);  // 1/11, 1/9
-  p = fmaf(p, t, 0x1.24924ap-3f);                     // 1/7
-  p = fmaf(p, t, 0x1.99999ap-3f);                     // 1/5
-  p = fmaf(p, t, 0x1.555556p-2f);                     // 1/3
-  const float lm = fmaf(f2 * t, p, f2);
-  const float e = (float)ex;
-  return fmaf(e, 0x1.62e000p-1f, fmaf(e, 0x1.0bfbe8p-15f, lm));
+  return ln_unit_with(u, [](float n, float d) __attribute__((always_inline)) {
+    return quotient_from_rcp(n, d, __builtin_amdgcn_rcpf(d));
+  });
 }
 
 // sin and cos of 2 pi j / 2^24 for a 24-bit integer j: exact reduction to
