@@ -63,3 +63,25 @@ def test_noalloc_forward_rejects_sizes_beyond_the_scratch():
     ctx.bitlinear_forward_noalloc(0, x[:2424], y[:2424])   # the largest M that fits
     ctx.sync()
     ctx.close()
+
+
+@pytest.mark.parametrize("M,K,N", [(127, 131072, 16), (1, 1 << 20, 16), (100, 163840, 17)])
+def test_noalloc_forward_where_fragment_order_does_not_fit(M, K, N):
+    """The activations fit the scratch as rows, but not as the whole groups of 16 tokens that the
+    small-M kernel reads: the row-major kernels take the call, bit for bit the other call's result."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo as T
+    print(f"noalloc forward N={N} K={K} M={M}", flush=True)
+    assert M * K + 2048 <= 16 << 20 < (M + 15) // 16 * 16 * K + 4 * M
+    w = synth.torch_latents(7, N * K, torch.bfloat16, torch.device("cuda", 0)).view(N, K)
+    ctx = T.Context([w])
+    ctx.build_mask(1e-2)
+    ctx.perturb(3, 1e-3, 1)
+    x = synth.torch_normal(8, (M, K), torch.bfloat16, torch.device("cuda", 0))
+    y_ref = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ctx.bitlinear_forward(0, x, y_ref)
+    ctx.bitlinear_forward_noalloc(0, x, y)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+    ctx.close()
