@@ -1023,8 +1023,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 // packed (bf16: 8 values per 16 bytes) up to KMAX values, at most ROWS rows; LDS rows are padded
 // by 16 bytes so the 16 token rows of a fragment read fall in distinct banks.
 // ---------------------------------------------------------------------------
-constexpr int kGemvFusedMaxM = 16;
-constexpr int64_t kGemvFusedMaxMK = 16 * 4096;      // rows x values quantised per block
+static_assert(kGemvFusedMaxM * 4096 == kGemvFusedMaxMK && 8 * 8192 == kGemvFusedMaxMK, "gemv_fused_ok");
 
 template <typename TX> struct RowChunk;            // 8 activations as loaded
 template <> struct RowChunk<uint16_t> {
@@ -1203,8 +1202,7 @@ __global__ void __launch_bounds__(64 * NW)
 // to 16 x 4096 values in all: there the two-launch path takes the same time (4096 -> 1536,
 // 16 tokens: 7.5 and 7.5 us; 12 tokens: 6.7 and 7.4; 6912 -> 2560, 8 tokens: 7.7 and 8.6).
 bool gemv_fused_ok(int64_t M, int64_t K) {
-  return M >= 1 && M <= kGemvFusedMaxM && M * K <= kGemvFusedMaxMK &&
-         (K <= 4096 || (K <= 8192 && M <= 8));
+  return M >= 1 && M <= kGemvFusedMaxM && (K <= 4096 || (K <= 8192 && M <= 8));
 }
 
 hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
@@ -1340,7 +1338,7 @@ static float edge_cost(const EdgeTile& t, int64_t M, int64_t K, int64_t N, int n
 // units, which the edge tiles do not take; never a row so long that padding it to 16 tokens
 // would take a large buffer.
 bool gemm_tiled_xq(int64_t M, int64_t K, int64_t N, bool units, int n_cu) {
-  if (M > kGemvMaxM || xq_bytes(M, K) > (int64_t)64 << 20) return false;
+  if (M > kGemvMaxM || xq_bytes(M, K) > kTiledXqMax) return false;
   if (M <= 16 || !units) return true;
   const int64_t cu = n_cu > 0 ? n_cu : 256, rounds = ((N + 15) / 16 + cu - 1) / cu;
   return 3.0f + (float)rounds * 1e-5f * (float)((M + 15) / 16 * 16 * K) <=

@@ -199,13 +199,15 @@ struct termezo_ctx {
   // pinned host words of the mask build's read-back: the error flag, then the selection state
   int64_t* h_pin = nullptr;
   double* d_loss = nullptr;                  // loss accumulators
-  float* d_scal = nullptr;                   // [0] update coefficient a, [1] g
+  float* d_scal = nullptr;                   // the last update's coefficients [kMaxK]
   int n_cu = 0;                              // compute units of the device
   // resident blocks per compute unit of the row kernels' instantiations (0: not asked yet)
   int row_blocks[tmz::kRowKinds] = {};
   void* noalloc_scratch = nullptr;           // this device's address of the file-scope scratch
-  int8_t* d_xq = nullptr;                    // activation-quantisation scratch
+  int8_t* d_xq = nullptr;                    // activation-quantisation scratch (row-major)
   int64_t xq_cap = 0;
+  int8_t* d_xqt = nullptr;                   // the same in fragment order, for every layer's calls
+  int64_t xqt_cap = 0;
   float* d_xs = nullptr;                     // per-token scales
   int32_t* d_xrs = nullptr;                  // per-token sums of the int8 activations
   int64_t xs_cap = 0;                        // tokens d_xs and d_xrs hold
@@ -318,6 +320,7 @@ hipError_t launch_act_quant(termezo_ctx* c, const void* x, termezo_dtype xdt, in
 // shapes it is the faster one (units: the outputs come in whole 16-byte units), and the caller
 // hands the choice to the quantiser and to launch_gemm_i8.
 constexpr int kGemvMaxM = 128;
+constexpr int64_t kTiledXqMax = int64_t(64) << 20;   // bytes of x_q in fragment order at most
 bool gemm_tiled_xq(int64_t M, int64_t K, int64_t N, bool units, int n_cu);
 inline int64_t xq_bytes(int64_t M, int64_t K) {
   return M <= kGemvMaxM ? (M + 15) / 16 * 16 * ((K + 255) / 256 * 256) : M * K;
@@ -337,6 +340,8 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs,
                           int n_cu, hipStream_t st, LaunchEvents ev = LaunchEvents());
 // Up to sixteen tokens with the activation quantisation fused in (no x_q, scale or row-sum
 // buffers, no inspection outputs): gemv_fused_ok(M, K) tells whether it applies.
+constexpr int kGemvFusedMaxM = 16;
+constexpr int64_t kGemvFusedMaxMK = 16 * 4096;       // the most values M K that it says yes to
 bool gemv_fused_ok(int64_t M, int64_t K);
 hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
                              const float* beta_dev, int64_t M, int64_t K, int64_t N, void* y,

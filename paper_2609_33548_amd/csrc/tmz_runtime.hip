@@ -1,4 +1,5 @@
 // C ABI of the TerMeZO library: validation, buffer ownership, launch order.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -208,6 +209,7 @@ void free_all(termezo_ctx* c) {
   dfree(c->d_loss);
   dfree(c->d_scal);
   dfree(c->d_xq);
+  dfree(c->d_xqt);
   dfree(c->d_xs);
   dfree(c->d_xrs);
   if (c->h_pin) (void)hipHostFree(c->h_pin);
@@ -321,6 +323,17 @@ termezo_status termezo_create(const termezo_layer* layers, int32_t n_layers,
   chk(dalloc(&c->d_loss, 4), "alloc");
   chk(dalloc(&c->d_scal, kScalLen), "alloc");
   chk(hipHostMalloc((void**)&c->h_pin, 64, hipHostMallocDefault), "alloc pinned");
+  // The activation scratch grows with the tokens of a call, as M d_in and M, and only then: what
+  // calls need beyond that is here from the start (x_q in fragment order, padded to whole groups
+  // and chunks; the row-major copy of a call that usually takes the fused kernel), so that after
+  // a call of the largest size no smaller one allocates or frees, which a caller that
+  // captures its calls in graphs relies on.
+  int64_t kmax = 0;
+  for (const LayerHost& L : c->layers) kmax = std::max(kmax, L.d_in);
+  c->xqt_cap = std::min(xq_bytes(kGemvMaxM, kmax), kTiledXqMax);
+  chk(dalloc(&c->d_xqt, (size_t)c->xqt_cap), "alloc");
+  if (st == TERMEZO_OK) st = ensure_xq_capacity(c, kGemvFusedMaxMK);
+  if (st == TERMEZO_OK) st = ensure_xs_capacity(c, kGemvFusedMaxM);
   chk(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device),
       "device attribute");
   if (st == TERMEZO_OK) {
@@ -531,11 +544,11 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
   if (st != TERMEZO_OK) return st;
   const bool tiled = bitlinear_tiled_xq(M, L.d_in, L.d_out, y, y_dtype, c->n_cu);
   const bool own = !xq_out || tiled;                  // the GEMM reads the library's copy of x_q
-  if (own) {
-    st = ensure_xq_capacity(c, tiled ? xq_bytes(M, L.d_in) : M * L.d_in);
+  if (!xq_out) {
+    st = ensure_xq_capacity(c, M * L.d_in);
     if (st != TERMEZO_OK) return st;
   }
-  int8_t* xq = own ? c->d_xq : xq_out;
+  int8_t* xq = tiled ? c->d_xqt : xq_out ? xq_out : c->d_xq;
   // the caller's outputs come from the last read of x: they may lie on its memory
   float* xs = own && xq_out ? c->d_xs : xscale_out ? xscale_out : c->d_xs;
   TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->stream));
@@ -808,7 +821,7 @@ termezo_status termezo_memory_footprint(termezo_ctx* c, int64_t* library_bytes,
   b += 2 * (int64_t)kSumSlots * sum_row_len(c->L) * 8;             // partial sums
   if (c->mirror) b += 2 * c->wc_cap * dsz;                       // active latents (list order)
   b += (int64_t)kHistBins * 8 + (int64_t)sizeof(SelectState) + 4 * 8 + kScalLen * 4 + 4;
-  b += c->xq_cap + (c->xs_cap + rs_entries(c->xs_cap)) * 4;                                // activation-quant scratch
+  b += c->xq_cap + c->xqt_cap + (c->xs_cap + rs_entries(c->xs_cap)) * 4;   // activation-quant scratch
   for (const ThetaHost& t : c->theta) b += 2 * t.n * (int64_t)dtype_size(t.dtype);
   if (c->d_codes_snap) b += c->code_words * 4 + L * 4;               // codes snapshot
   if (library_bytes) *library_bytes = b;

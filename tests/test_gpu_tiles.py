@@ -140,6 +140,58 @@ def test_one_token_inspected_in_place(orc, K, dt):
     ctx.close()
 
 
+@pytest.mark.parametrize("warm,calls", [
+    ((129, 688), [(128, 688), (17, 688), (100, 16), (128, 272)]),   # padding past the largest call's bytes
+    ((200, 256), [(17, 2560), (1, 9008), (16, 2560)]),              # fewer values, more once padded
+    ((16, 4096), [(16, 4096), (1, 8192), (16, 2560)])])             # y on x after a call with its own y
+def test_smaller_calls_in_a_graph(warm, calls):
+    """After a call that is the largest in tokens and in values, smaller ones neither allocate
+    nor free: they can be captured, and the graph's results are the eager calls' on every
+    replay, with other calls in between."""
+    torch = _torch()
+    from paper_2609_33548_amd import termezo
+    print(f"graph after M={warm[0]} K={warm[1]}", flush=True)
+    in_place = warm == (16, 4096)
+    dev = torch.device("cuda", 0)
+    widths = sorted({k for _, k in calls + [warm]})
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ws = [synth.torch_latents(30 + j, 64 * k, torch.bfloat16, dev).view(64, k) for j, k in enumerate(widths)]
+        ctx = termezo.Context(ws, stream=stream)
+        ref = termezo.Context(ws, stream=stream)
+        ctx.build_mask(1e-2)
+        ref.build_mask(1e-2)
+        wx = synth.torch_normal(1, warm, torch.bfloat16, dev)
+        wy = torch.empty((warm[0], 64), dtype=torch.bfloat16, device=dev)
+        ctx.bitlinear_forward(widths.index(warm[1]), wx, wy)
+        xs, ys, want = [], [], []
+        for j, (m, k) in enumerate(calls):
+            buf = synth.torch_normal(2 + j, (m, k), torch.bfloat16, dev)
+            xs.append(buf)
+            ys.append(buf.flatten()[:m * 64].view(m, 64) if in_place
+                      else torch.empty((m, 64), dtype=torch.bfloat16, device=dev))
+            want.append(torch.empty((m, 64), dtype=torch.bfloat16, device=dev))
+            ref.bitlinear_forward(widths.index(k), buf, want[-1])
+        keep = [x.clone() for x in xs]
+        stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            for (_, k), x, y in zip(calls, xs, ys):
+                ctx.bitlinear_forward(widths.index(k), x, y)
+        for r in range(3):
+            for x, y, o in zip(xs, ys, keep):
+                y.zero_()
+                x.copy_(o)
+            g.replay()
+            for y, v in zip(ys, want):
+                assert torch.equal(y, v), r
+            ctx.bitlinear_forward(widths.index(warm[1]), wx, wy)
+            stream.synchronize()
+        del g
+        ctx.close()
+        ref.close()
+
+
 @pytest.mark.parametrize("act,d,H,Hkv,F,V,S,B", [
     ("f32", 256, 4, 4, 688, 1000, 87, 2),    # a partial vocabulary tile, one partial key group
     ("f32", 48, 3, 1, 80, 130, 300, 1),      # K steps of 16, more keys than the four groups of 64
