@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(256) k_act_quant(const T* __restrict__ x, int6
 // assignment.  Accumulator layout (32 x 32, 16 values per lane): column l % 32,
 // row 8 (r / 4) + 4 (l / 32) + (r % 4).  LDS rows are 128 data bytes + 16 pad
 // (144 B: 16-byte fragment reads of 16 consecutive rows hit distinct banks).
-// FULL = every tile is in bounds (M % BM = N % BN = K % BK = 0): no predication.
+// Any M, N and K % 16 == 0: loads and stores are predicated.
 // ---------------------------------------------------------------------------
 constexpr int kBK = 128;
 constexpr int kLdsStride = kBK + 16;
@@ -192,7 +192,7 @@ __device__ __forceinline__ void load4v(const uint16_t* p, float v[4]) {
   v[3] = __uint_as_float(a.y & 0xFFFF0000u);
 }
 
-template <int BM, int BN, int WM, int WN, bool FULL, typename TY, int MODE>
+template <int BM, int BN, int WM, int WN, typename TY, int MODE>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
     k_gemm_i8(const int8_t* __restrict__ xq, const float* __restrict__ s,
               const uint32_t* __restrict__ codes, int64_t M, int64_t K, int64_t N, GemmOut out,
@@ -235,27 +235,15 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
     for (int it = 0; it < A_CH; ++it) {
       const int c = tid + NT * it;
       const int row = c / CPR, col = c % CPR;
-      if (FULL || (m0 + row < M && k0 + 16 * col < K))
+      if (m0 + row < M && k0 + 16 * col < K)
         ra[it] = *reinterpret_cast<const v4u*>(abase + row * K + k0 + 16 * col);
       else
         ra[it] = v4u{0u, 0u, 0u, 0u};
     }
     const int64_t kw0 = k0 / 16;
-    if constexpr (FULL && B_WORDS == 4) {
-      const v4u v = *reinterpret_cast<const v4u*>(bbase + kw0);
-      rb[0] = v.x;
-      rb[1] = v.y;
-      rb[2] = v.z;
-      rb[3] = v.w;
-    } else if constexpr (FULL && B_WORDS == 2) {
-      const uint2 v = *reinterpret_cast<const uint2*>(bbase + kw0);
-      rb[0] = v.x;
-      rb[1] = v.y;
-    } else {
 #pragma unroll
-      for (int j = 0; j < B_WORDS; ++j)
-        rb[j] = (FULL || (n0 + brow < N && kw0 + bw0 + j < KW)) ? bbase[kw0 + j] : 0u;
-    }
+    for (int j = 0; j < B_WORDS; ++j)
+      rb[j] = n0 + brow < N && kw0 + bw0 + j < KW ? bbase[kw0 + j] : 0u;
   };
   auto lstore = [&](int buf) __attribute__((always_inline)) {
     int8_t* As = smem + buf * STAGE;
@@ -317,7 +305,7 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 #pragma unroll
   for (int b = 0; b < TN; ++b) {
     const int64_t n = n0 + wn * WN + b * 32 + (lane & 31);
-    if (!FULL && n >= N) continue;
+    if (n >= N) continue;
     int sg = 0;
     if (out.nseg > 1 && n >= out.nstart[1]) sg = 1;
     if (out.nseg > 2 && n >= out.nstart[2]) sg = 2;
@@ -329,7 +317,7 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int ro = a * 32 + 8 * (r >> 2) + (r & 3);
-        if (FULL || m0 + rl + ro < M) {
+        if (m0 + rl + ro < M) {
           const int32_t v = acc[a][b][r];
           const float yv = (float)v * rr[ro];
           TY* p = colp + (int64_t)ro * ld;
@@ -491,7 +479,7 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
       // a wave's column blocks b = 0 and 1 hold the gate and the up values of the same
       // 32 features in the same lanes
       const int64_t p = crow >> 6, c = crow & 63, f = 32 * p + (c & 31);
-      crow = (c < 32 ? 0 : N >> 1) + (EDGE == kOddTile ? min(f, (N >> 1) - 1) : f);
+      crow = (c < 32 ? 0 : N >> 1) + f;
     } else if constexpr (EDGE == kOddTile) {
       crow = min(crow, N - 1);
     }
@@ -503,7 +491,7 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
     boff[j] = (uint32_t)(4 * (crow * KW + bword[j]));
   }
 
-  static_assert(MODE != kGemmSwiGLU || WN == 64, "SwiGLU: gate and up blocks of one wave");
+  static_assert(MODE != kGemmSwiGLU || (WN == 64 && EDGE != kOddTile), "SwiGLU: gate and up blocks of one wave");
   // the segments' beta', for the epilogue's table of output scales
   float bet[kMaxSeg];
 #pragma unroll
@@ -1275,7 +1263,7 @@ hipError_t launch_act_quant(termezo_ctx* c, const void* x, termezo_dtype xdt, in
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, bool FULL>
+template <int BM, int BN, int WM, int WN>
 static hipError_t launch_tile(const int8_t* xq, const float* s, const uint32_t* codes, int64_t M,
                               int64_t K, int64_t N, const GemmOut& out, termezo_dtype ydt, int mode,
                               int32_t* acc, hipStream_t st, LaunchEvents ev) {
@@ -1283,17 +1271,17 @@ static hipError_t launch_tile(const int8_t* xq, const float* s, const uint32_t* 
   dim3 grid((unsigned)(((N + BN - 1) / BN) * ((M + BM - 1) / BM)));
   if (ydt == TERMEZO_F32) {
     if (mode == kGemmStore)
-      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, FULL, float, kGemmStore>), grid, dim3(NT), 0,
+      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, float, kGemmStore>), grid, dim3(NT), 0,
                             st, ev.start, ev.stop, 0, xq, s, codes, M, K, N, out, acc);
     else
-      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, FULL, float, kGemmResidual>), grid, dim3(NT),
+      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, float, kGemmResidual>), grid, dim3(NT),
                             0, st, ev.start, ev.stop, 0, xq, s, codes, M, K, N, out, acc);
   } else {
     if (mode == kGemmStore)
-      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, FULL, uint16_t, kGemmStore>), grid, dim3(NT),
+      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, uint16_t, kGemmStore>), grid, dim3(NT),
                             0, st, ev.start, ev.stop, 0, xq, s, codes, M, K, N, out, acc);
     else
-      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, FULL, uint16_t, kGemmResidual>), grid,
+      hipExtLaunchKernelGGL((k_gemm_i8<BM, BN, WM, WN, uint16_t, kGemmResidual>), grid,
                             dim3(NT), 0, st, ev.start, ev.stop, 0, xq, s, codes, M, K, N, out, acc);
   }
   return hipGetLastError();
@@ -1478,8 +1466,8 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
   const int64_t T = ((M + 255) / 256) * ((N + 255) / 256);
   if (!units_ok(out, ydt)) {                     // single outputs: the register-staged kernel
     if (T >= 256)
-      return launch_tile<256, 256, 128, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
-    return launch_tile<128, 128, 64, 64, false>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
+      return launch_tile<256, 256, 128, 64>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
+    return launch_tile<128, 128, 64, 64>(xq, s, codes, M, K, N, out, ydt, mode, acc, st, ev);
   }
   bool whole = M % 256 == 0 && N % 256 == 0 && K % kBK == 0 &&
                reinterpret_cast<uintptr_t>(codes) % 16 == 0;

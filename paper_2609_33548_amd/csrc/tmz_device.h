@@ -212,13 +212,6 @@ __device__ __forceinline__ uint32_t ternary_code(float w, float tau) {
 
 __device__ __forceinline__ int code_shift(int j) { return 8 * (j & 3) + 2 * (j >> 2); }
 
-// Expand the four codes of group i (offsets 4i..4i+3) to four int8 lanes.
-__device__ __forceinline__ uint32_t unpack_group(uint32_t word, int i) {
-  const uint32_t sel = (word >> (2 * i)) & 0x03030303u;
-  // byte selector 0 -> 0x00, 1 -> 0x01, 2 -> 0xFF
-  return __builtin_amdgcn_perm(0u, 0xFFFF0100u, sel);
-}
-
 // All 16 codes of a word as four int8 lanes of four (offsets 0..15) with one
 // shift: groups 0 and 2 (bits 0-1 of each byte of w and w >> 4) are byte
 // selectors 0, 1, 2 into 0x00, 0x01, 0xFF; groups 1 and 3 (bits 2-3), masked in

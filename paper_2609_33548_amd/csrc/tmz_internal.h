@@ -11,7 +11,6 @@
 namespace tmz {
 
 constexpr int kTile = 8192;          // elements per streaming tile (never straddles layers)
-constexpr int kBlock = 256;          // threads per block for streaming kernels
 constexpr int kHistBins = 2048;      // radix-select histogram width (11 bits)
 constexpr int kMaxLayers = 2048;     // layers per context (active-list offsets fit in LDS)
 

@@ -968,13 +968,13 @@ __global__ void __launch_bounds__(512) k_attn_bf16(const uint16_t* __restrict__ 
 //    tile's maximum exceeds it by more than 2^8 (in exp2 units); the
 //    normalised result does not depend on that choice.  Query tiles are
 //    dispatched heaviest first.
-// Requires S % 64 == 0 and S % QT == 0 (then vs = S).
+// Requires S % 64 == 0 and S % QT == 0 (V^T rows of S tokens).
 // ---------------------------------------------------------------------------
 template <int HD, int G>
 __global__ void __launch_bounds__(512) k_attn_gqa(const uint16_t* __restrict__ q,
                                                   const uint16_t* __restrict__ k,
                                                   const uint16_t* __restrict__ vt,
-                                                  uint16_t* __restrict__ o, int S, int vs, int Hkv,
+                                                  uint16_t* __restrict__ o, int S, int Hkv,
                                                   int nbh, int nqt, float scale_log2,
                                                   const float* __restrict__ rope_c,
                                                   const float* __restrict__ rope_s) {
@@ -1027,7 +1027,7 @@ __global__ void __launch_bounds__(512) k_attn_gqa(const uint16_t* __restrict__ q
     const int kr = c / CPR, kc = (c % CPR) ^ swk(kr);
     ksrc[j] = reinterpret_cast<const uint8_t*>(k + (base + kr) * rowkv + (int64_t)kvh * HD) + 16 * kc;
     const int vr = c / 8, vc = (c % 8) ^ swv(vr);
-    vsrc[j] = reinterpret_cast<const uint8_t*>(vt + (((int64_t)b * Hkv + kvh) * HD + vr) * vs) + 16 * vc;
+    vsrc[j] = reinterpret_cast<const uint8_t*>(vt + (((int64_t)b * Hkv + kvh) * HD + vr) * S) + 16 * vc;
   }
   auto issue = [&](int kt, int st) __attribute__((always_inline)) {
     const uint32_t kb = lds_offset(lds + st * 2 * TB), vb = kb + TB;
@@ -1915,7 +1915,7 @@ hipError_t run_attention(termezo_model* m, int B, int S, hipStream_t st) {
                    (G == 1 || G == 2 || G == 4 || G == 8) &&
                    S % 64 == 0 && S % (256 / G) == 0;
   if (gqa) {
-    const int nbh = B * c.n_kv_heads, nqt = (S + 256 / G - 1) / (256 / G);
+    const int nbh = B * c.n_kv_heads, nqt = S / (256 / G);
     if (m->hd == 128)
       hipLaunchKernelGGL(k_kv_prep<128>, pgrid, dim3(256), 0, st, (uint16_t*)m->k,
                          (const uint16_t*)m->v, (uint16_t*)m->vt, S, vs, c.n_kv_heads, m->rope_c,
@@ -1931,7 +1931,7 @@ hipError_t run_attention(termezo_model* m, int B, int S, hipStream_t st) {
 #define TMZ_GQA(HDV, GV)                                                                      \
   hipLaunchKernelGGL((k_attn_gqa<HDV, GV>), dim3((unsigned)(nqt * nbh)), dim3(512), 0, st,      \
                      (const uint16_t*)m->q, (const uint16_t*)m->k, (const uint16_t*)m->vt,     \
-                     (uint16_t*)m->attn, S, vs, c.n_kv_heads, nbh, nqt, sl2, m->rope_c, m->rope_s)
+                     (uint16_t*)m->attn, S, c.n_kv_heads, nbh, nqt, sl2, m->rope_c, m->rope_s)
     switch (m->hd * 16 + G) {
       case 128 * 16 + 1: TMZ_GQA(128, 1); break;
       case 128 * 16 + 2: TMZ_GQA(128, 2); break;

@@ -109,24 +109,6 @@ __device__ __forceinline__ long long wave_incl_scan_i64(long long v) {
   return v;
 }
 
-// Exclusive prefix sum over a 256-thread block of int64 values; returns the
-// exclusive prefix and writes the block total to *total.
-__device__ long long block_excl_scan_i64(long long v, long long* lds, long long* total) {
-  const int tid = threadIdx.x;
-  lds[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    long long add = tid >= off ? lds[tid - off] : 0;
-    __syncthreads();
-    lds[tid] += add;
-    __syncthreads();
-  }
-  const long long incl = lds[tid];
-  *total = lds[255];
-  __syncthreads();
-  return incl - v;
-}
-
 // Layer of active-list position j: largest l with act_off[l] <= j (L layers).
 __device__ __forceinline__ int layer_of(const int64_t* act_off, int L, int64_t j) {
   int lo = 0, hi = L - 1;
@@ -491,13 +473,6 @@ __global__ void __launch_bounds__(256) k_select_init(SelectState* sel, unsigned 
     sel->pad = 0;
   }
   for (int i = threadIdx.x; i < kHistBins; i += 256) hist[i] = 0;
-}
-
-__device__ __forceinline__ uint32_t code_word(const float* v, float tau) {
-  uint32_t word = 0;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) word |= ternary_code(v[q], tau) << code_shift(q);
-  return word;
 }
 
 constexpr int kRqThreads = 128;
