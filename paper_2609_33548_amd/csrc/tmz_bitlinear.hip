@@ -5,6 +5,7 @@
 
 #include "tmz_device.h"
 #include "tmz_internal.h"
+#include "tmz_tiles.h"
 
 namespace tmz {
 
@@ -718,9 +719,11 @@ __device__ __forceinline__ void gemm_tile_dma(const int8_t* __restrict__ xq,
     return reinterpret_cast<v4u*>(reinterpret_cast<TY*>(out.y[sg]) + tok * out.ld[sg] +
                                   (f - out.nstart[sg]));
   };
-  // residual inputs: all of a lane's units loaded up front (at most 16 units, else
-  // one slice at a time) so their latency overlaps the staging
-  constexpr int HPRE = MODE == kGemmResidual ? (TM * RPL <= 8 ? TM : 1) : 0;
+  // residual inputs: all of a lane's units loaded up front (at most 8 units, else
+  // one slice at a time) so their latency overlaps the staging; one slice at a time in the
+  // edge tiles, whose 128 registers hold no more (128 x 128 in fp32 spilled 24: 4096 x 1536 -> 1536
+  // 25.3 us, 21.5 so)
+  constexpr int HPRE = MODE == kGemmResidual ? (FULL && TM * RPL <= 8 ? TM : 1) : 0;
   v4u hin[HPRE > 0 ? HPRE : 1][RPL];
   if constexpr (HPRE == TM) {
 #pragma unroll
@@ -1293,34 +1296,14 @@ static hipError_t launch_tile(const int8_t* xq, const float* s, const uint32_t* 
 // (k_gemm_i8_dma_h), from three rounds of them and always for the SwiGLU gate|up product,
 // below that 256 x 256 tiles of 8 waves (128 x 64 per wave, two waves per SIMD) with the last
 // round cut into 128 x 128 quarter tiles when it would fill at most half of the compute
-// units; every other shape the edge tiles (k_gemm_i8_edge), which measured 1.1-3x faster
-// below one round (256 x 2560 -> 2560: 21.8 -> 8.4 us; 1024 x 6912 -> 2560: 49 -> 28 us) and
-// level with the whole-tile kernels at one to three rounds.  Other outputs: the
-// register-staged kernel, 256 x 256 blocks of 8 waves when the grid fills the chip,
-// 128 x 128 blocks of 4 waves otherwise.
-// The tiles of k_gemm_i8_edge and what a launch of T of them takes (us): the first tile of a
-// compute unit c0 + l K, each further one a + b K, fitted (rms error 7%) to the nine widths
-// of the decoders at 256 to 8192 tokens.  The tile with the least estimate is taken, which
-// is within 2.5% of the best of the measured tiles on average: the small tile while it is
-// what fills the compute units, the large ones when there are several per compute unit (a
-// 256-column tile moves half the bytes per product).
-struct EdgeTile {
-  int bm, bn;
-  float c0, l, a, b;
-};
-constexpr EdgeTile kEdge64 = {64, 64, 3.53f, 1.67e-3f, 0.72f, 1.16e-3f};
-constexpr EdgeTile kEdge128 = {128, 128, 5.72f, 2.90e-3f, 2.24f, 3.36e-3f};
-constexpr EdgeTile kEdge256 = {128, 256, 8.60f, 5.24e-3f, 3.28f, 6.42e-3f};
-constexpr EdgeTile kEdgeGlu = {64, 128, 5.23f, 2.25e-3f, 1.20f, 2.05e-3f};
-
-static float edge_cost(const EdgeTile& t, int64_t M, int64_t K, int64_t N, int n_cu) {
-  const int64_t T = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-  const int64_t cu = n_cu > 0 ? n_cu : 256;
-  return t.c0 + t.l * (float)K + (float)((T + cu - 1) / cu - 1) * (t.a + t.b * (float)K);
-}
+// units; every other shape the tile that choose_tile estimates the fastest: an edge tile
+// (k_gemm_i8_edge; 256 x 2560 -> 2560: 21.8 us as 128 x 256 tiles without edges, 8.4), or on whole tiles
+// those 128 x 256 ones (residual outputs from 5000 tokens, 6144 x 2560 -> 2560: 39.7 us
+// against 44.1 as 128 x 128).  Other outputs: the register-staged kernel, 256 x 256 blocks of 8 waves
+// when the grid fills the chip, 128 x 128 blocks of 4 waves otherwise.
 
 // Whether the launch takes the small-M kernel, whose activations come in fragment order:
-// up to kGemvMaxM tokens, unless the edge tiles are estimated faster (every block reads all
+// up to kGemvMaxM tokens, unless 64 x 64 tiles are estimated faster (every block reads all
 // the activations, 1e-5 us per byte and round of blocks: 128 x 2560 -> 6912 9.7 us against
 // 8.2, but 6912 -> 2560 10.1 against 15.3).  A few tokens always do, and outputs without whole
 // units, which the edge tiles do not take; never a row so long that padding it to 16 tokens
@@ -1329,8 +1312,9 @@ bool gemm_tiled_xq(int64_t M, int64_t K, int64_t N, bool units, int n_cu) {
   if (M > kGemvMaxM || xq_bytes(M, K) > kTiledXqMax) return false;
   if (M <= 16 || !units) return true;
   const int64_t cu = n_cu > 0 ? n_cu : 256, rounds = ((N + 15) / 16 + cu - 1) / cu;
+  const int64_t more = (((M + 63) / 64) * ((N + 63) / 64) + cu - 1) / cu - 1;   // 64 x 64 tiles
   return 3.0f + (float)rounds * 1e-5f * (float)((M + 15) / 16 * 16 * K) <=
-         edge_cost(kEdge64, M, K, N, n_cu);
+         3.53f + 1.67e-3f * (float)K + (float)more * (0.72f + 1.16e-3f * (float)K);
 }
 
 // Whole 16-byte output units, segment by segment: what the direct-load kernels need.
@@ -1376,22 +1360,24 @@ static int64_t dma_full_tiles(int64_t T, int n_cu) {
                         dim3((BM / WM) * (BN / WN) * 64), 0, st, ev.start, ev.stop, 0, xq, s, rs, \
                         codes, M, K, N, out, acc)
 
-// Any M and N (whole output units): the cheapest edge tile, or the odd-K one.
+// Any M and N (whole output units): the chosen edge tile, or the odd-K one.
 template <typename TY, int MD>
 static hipError_t launch_edge(const int8_t* xq, const float* s, const int32_t* rs,
                               const uint32_t* codes, int64_t M, int64_t K, int64_t N,
-                              const GemmOut& out, int32_t* acc, int n_cu, hipStream_t st,
+                              const GemmOut& out, int32_t* acc, GemmTile tile, hipStream_t st,
                               LaunchEvents ev) {
   if (K % 128 != 0 || reinterpret_cast<uintptr_t>(codes) % 16 != 0) {
     TMZ_EDGE(64, 64, 32, 32, TY, MD, 256, 2, kOddTile, 4);
     return hipGetLastError();
   }
-  const float c64 = edge_cost(kEdge64, M, K, N, n_cu), c128 = edge_cost(kEdge128, M, K, N, n_cu),
-              c256 = edge_cost(kEdge256, M, K, N, n_cu);
   const bool k256 = K % 256 == 0;                // K steps of 256 where they are whole
-  if (c256 <= c64 && c256 <= c128)
-    TMZ_EDGE(128, 256, 64, 64, TY, MD, 128, 3, kEdgeTile, 2);
-  else if (c128 <= c64) {
+  if constexpr (MD == kGemmStore) {
+    if (tile == kTile256) {
+      TMZ_EDGE(128, 256, 64, 64, TY, MD, 128, 3, kEdgeTile, 2);
+      return hipGetLastError();
+    }
+  }
+  if (tile == kTile128) {
     if (k256)
       TMZ_EDGE(128, 128, 64, 32, TY, MD, 256, 2, kEdgeTile, 2);
     else
@@ -1409,6 +1395,7 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
                           int32_t* acc, bool tiled, int n_cu, hipStream_t st, LaunchEvents ev) {
   // the direct-load paths read the row sums, four tokens per 16-byte load
   if (!rs || reinterpret_cast<uintptr_t>(rs) % 16 != 0) return hipErrorInvalidValue;
+  const int cu = n_cu > 0 ? n_cu : 256;
   if (mode == kGemmSwiGLU) {
     if (tiled || !gemm_swiglu_ok(M, K, N, ydt, codes) || out.nseg != 2 || out.nstart[1] * 2 != N || acc ||
         out.ld[0] % 8 != 0 || reinterpret_cast<uintptr_t>(out.y[0]) % 16 != 0)
@@ -1417,7 +1404,7 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
     // each: the two-blocks-per-CU tiles on whole 256-tiles from one round of them
     if (M % kDmaBM != 0 || N % kDmaBN != 0 || (M / kDmaBM) * (N / kDmaBN) < n_cu) {
       const bool k256 = K % 256 == 0;
-      if (edge_cost(kEdge256, M, K, N, n_cu) <= edge_cost(kEdgeGlu, M, K, N, n_cu))
+      if (choose_tile(kSwiGLU, M, K, N, false, cu) == kTile256)
         TMZ_EDGE(128, 256, 64, 64, uint16_t, kGemmSwiGLU, 128, 3, kEdgeTile, 2);
       else if (k256)
         TMZ_EDGE(64, 128, 32, 64, uint16_t, kGemmSwiGLU, 256, 2, kEdgeTile, 3);
@@ -1472,14 +1459,17 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs, c
   bool whole = M % 256 == 0 && N % 256 == 0 && K % kBK == 0 &&
                reinterpret_cast<uintptr_t>(codes) % 16 == 0;
   for (int i = 1; i < out.nseg; ++i) whole = whole && out.nstart[i] % 32 == 0;
-  if (!whole || T < n_cu) {
-#define TMZ_ANY(TY, MD) launch_edge<TY, MD>(xq, s, rs, codes, M, K, N, out, acc, n_cu, st, ev)
+  const GemmKind kind = mode == kGemmStore ? (ydt == TERMEZO_F32 ? kStoreF32 : kStoreBf16)
+                                           : (ydt == TERMEZO_F32 ? kResidualF32 : kResidualBf16);
+  const GemmTile tile = choose_tile(kind, M, K, N, whole, cu);
+  if (!whole || (T < n_cu && tile != kTileHalf)) {
+#define TMZ_ANY(TY, MD) launch_edge<TY, MD>(xq, s, rs, codes, M, K, N, out, acc, tile, st, ev)
     if (ydt == TERMEZO_F32)
       return mode == kGemmStore ? TMZ_ANY(float, kGemmStore) : TMZ_ANY(float, kGemmResidual);
     return mode == kGemmStore ? TMZ_ANY(uint16_t, kGemmStore) : TMZ_ANY(uint16_t, kGemmResidual);
 #undef TMZ_ANY
   }
-  if (use_half_tiles(T, n_cu)) {
+  if (use_half_tiles(T, n_cu) || T < n_cu) {
     dim3 gh((unsigned)(2 * T));
 #define TMZ_HALF(TY, MD) \
   hipExtLaunchKernelGGL((k_gemm_i8_dma_h<TY, MD>), gh, dim3(256), 0, st, ev.start, ev.stop, 0, xq, s, rs, \
