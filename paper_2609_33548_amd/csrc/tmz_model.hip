@@ -1224,7 +1224,8 @@ constexpr int kVT = 128;   // vocab columns per tile
 // steps of 32: lane half h loads the 16 consecutive values 16 h .. of its row (four 16-byte
 // loads, whole lines between the halves) and product j takes value j of both halves.  These
 // shapes are bound by latency and by the number of blocks, not by the operands (a thread per
-// logit, each reading two rows value by value, took 125 us for 256 x 1024 at d 256).
+// logit, each reading two rows value by value, took 125 us for 256 x 1024 at d 256).  The operands'
+// buffers do not all stay in registers: 160 bytes per lane of private memory.
 __global__ void __launch_bounds__(512) k_lmhead_f32(const float* __restrict__ x,
                                                     const float* __restrict__ E, int64_t M,
                                                     int64_t d, int64_t V,
