@@ -1248,13 +1248,13 @@ hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* c
 }
 
 // ===========================================================================
-hipError_t launch_act_quant(termezo_ctx* c, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
+hipError_t launch_act_quant(int n_cu, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
                             int8_t* xq, float* s, int32_t* rs, bool tiled, hipStream_t st) {
   // one wave per row, walking the rows of a resident grid (8192 x 2560: 13.9 us, a block per
   // row 20.9; 389 x 2560: 3.9 against 4.9), except for few long rows, where four waves share
   // a row's latency (48 x 6912: 5.2 against 5.5 alone, but 0.5 us more with the kernel after)
-  if (K <= kRowMaxK && (K <= 2560 || M >= 4 * (int64_t)c->n_cu))
-    return launch_row_quant(c, x, xdt, M, K, xq, s, rs, tiled, st);
+  if (K <= kRowMaxK && (K <= 2560 || M >= 4 * (int64_t)n_cu))
+    return launch_row_quant(n_cu, x, xdt, M, K, xq, s, rs, tiled, st);
 #define TMZ_AQ(T, TI) \
   hipLaunchKernelGGL((k_act_quant<T, TI>), dim3(M), dim3(256), 0, st, (const T*)x, K, xq, s, rs)
   if (xdt == TERMEZO_F32) {

@@ -85,10 +85,6 @@ struct UpdateCoefs {
   bool divide = false, device = false;
 };
 
-// Instantiations of the row kernel with a resident grid: four modes, with weights or without,
-// two layouts of the output, four row lengths.
-constexpr int kRowKinds = 4 * 2 * 2 * 4;
-
 // Rows of partial |w| sums (see k_perturb_delta): kSumSlots for each of two sums.
 constexpr int kSumSlots = 32;
 __host__ __device__ inline int64_t sum_row_len(int L) { return (L + 15) / 16 * 16; }
@@ -200,8 +196,6 @@ struct termezo_ctx {
   double* d_loss = nullptr;                  // loss accumulators
   float* d_scal = nullptr;                   // the last update's coefficients [kMaxK]
   int n_cu = 0;                              // compute units of the device
-  // resident blocks per compute unit of the row kernels' instantiations (0: not asked yet)
-  int row_blocks[tmz::kRowKinds] = {};
   void* noalloc_scratch = nullptr;           // this device's address of the file-scope scratch
   int8_t* d_xq = nullptr;                    // activation-quantisation scratch (row-major)
   int64_t xq_cap = 0;
@@ -312,7 +306,7 @@ hipError_t launch_mse(const float* y, const float* t, int64_t n, double* acc, fl
 // tile of tokens: it is allocated for rs_entries(M)).
 constexpr int64_t kRsPad = 256;
 inline int64_t rs_entries(int64_t M) { return (M + kRsPad - 1) / kRsPad * kRsPad; }
-hipError_t launch_act_quant(termezo_ctx* c, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
+hipError_t launch_act_quant(int n_cu, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
                             int8_t* xq, float* s, int32_t* rs, bool tiled, hipStream_t st);
 // Up to kGemvMaxM tokens a GEMM may take the small-M kernel, which reads x_q in fragment order
 // (tiled quantiser output) from a buffer of xq_bytes(M, K): gemm_tiled_xq says for which
@@ -326,7 +320,7 @@ inline int64_t xq_bytes(int64_t M, int64_t K) {
 }
 // The decoder's row kernel for the same (rows of at most kRowMaxK values, K % 8 == 0).
 constexpr int64_t kRowMaxK = 8192;
-hipError_t launch_row_quant(termezo_ctx* c, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
+hipError_t launch_row_quant(int n_cu, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
                             int8_t* xq, float* xs, int32_t* xrs, bool tiled, hipStream_t st);
 // Optional timing of one GEMM launch: non-null events take the start and the end of the
 // kernel's own execution (hipExtLaunchKernel), not the time around the launch.

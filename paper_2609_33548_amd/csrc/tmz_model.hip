@@ -9,6 +9,7 @@
 // silu(g) * u is stored in the activation dtype (by the fused gate|up GEMM
 // epilogue for bf16, by a row kernel otherwise) and then quantised.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <new>
 #include <string>
@@ -498,36 +499,37 @@ __global__ void __launch_bounds__(256) k_row(const T* __restrict__ x, const T* _
 // the row length needs: 3 (up to 1536 elements), 5 (2560), 8 (4096), 14 (7168),
 // else kRowChunks.
 template <int MODE, bool W, int CH, bool TILED>
-static unsigned row_pf_grid(int64_t M, termezo_ctx* c) {
-  constexpr int kind = ((MODE * 2 + W) * 2 + TILED) * 4 + (CH == 3 ? 0 : CH == 5 ? 1 : CH == 8 ? 2 : 3);
-  static_assert(kind < kRowKinds, "row kernels");
-  int per_cu = c->row_blocks[kind];             // resident blocks per compute unit
+static unsigned row_pf_grid(int64_t M, int n_cu) {
+  // Resident blocks per compute unit: a property of the kernel on the one architecture built for,
+  // asked once (13 us).  Threads that ask at the same time store the same number.
+  static std::atomic<int> asked{0};
+  int per_cu = asked.load(std::memory_order_relaxed);
   if (per_cu == 0) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_row_pf<MODE, W, CH, TILED>, 256, 0) ==
             hipSuccess && per_cu > 0) {
-      c->row_blocks[kind] = per_cu;
+      asked.store(per_cu, std::memory_order_relaxed);
     } else {                                    // one block each for this launch, asked again next time
       (void)hipGetLastError();
       per_cu = 1;
     }
   }
   const int64_t need = (M + 3) / 4;
-  const int64_t cap = (int64_t)per_cu * c->n_cu;
+  const int64_t cap = (int64_t)per_cu * n_cu;
   return (unsigned)(need < cap ? need : cap);
 }
 
 template <int MODE, typename T, bool W, bool TILED>
 static void row_launch_as(unsigned grid, hipStream_t s, const T* x, const T* u, int64_t M, int64_t K,
-                          float eps, int8_t* xq, float* xs, int32_t* xrs, T* xf, termezo_ctx* ctx) {
+                          float eps, int8_t* xq, float* xs, int32_t* xrs, T* xf, int n_cu) {
   const int64_t need = (K / 8 + 63) / 64;
   // the prefetching walk measured faster for the quantiser alone (12.7 against 13.1 us at
   // 8192 x 2560, 32.3 against 35.3 us at 8192 x 6912) and for rows of more than 8 chunks per
   // lane, slower for RMSNorm + quantiser at 2560 (14.3 against 13.7 us: more registers)
   if constexpr (sizeof(T) == 2 && MODE != kRowSwiGLU) {
-    if (ctx && ctx->n_cu > 0 && need <= 14 && (MODE == kRowQuant || need > 8)) {
+    if (n_cu > 0 && need <= 14 && (MODE == kRowQuant || need > 8)) {
 #define TMZ_ROWPF(CHN)                                                                        \
   hipLaunchKernelGGL((k_row_pf<MODE, W, CHN, TILED>),                                         \
-                     dim3(row_pf_grid<MODE, W, CHN, TILED>(M, ctx)), dim3(256), 0, s, x, u, M, \
+                     dim3(row_pf_grid<MODE, W, CHN, TILED>(M, n_cu)), dim3(256), 0, s, x, u, M, \
                      K, eps, xq, xs, xrs, xf)
       if (need <= 3)
         TMZ_ROWPF(3);
@@ -560,22 +562,22 @@ static void row_launch_as(unsigned grid, hipStream_t s, const T* x, const T* u, 
 template <int MODE, typename T, bool W = false>
 static void row_launch(unsigned grid, hipStream_t s, const T* x, const T* u, int64_t M, int64_t K,
                        float eps, int8_t* xq, float* xs, int32_t* xrs, T* xf, bool tiled,
-                       termezo_ctx* ctx = nullptr) {
+                       int n_cu = 0) {
   if constexpr (MODE != kRowNormStore) {
     if (tiled) {
-      row_launch_as<MODE, T, W, true>(grid, s, x, u, M, K, eps, xq, xs, xrs, xf, ctx);
+      row_launch_as<MODE, T, W, true>(grid, s, x, u, M, K, eps, xq, xs, xrs, xf, n_cu);
       return;
     }
   }
-  row_launch_as<MODE, T, W, false>(grid, s, x, u, M, K, eps, xq, xs, xrs, xf, ctx);
+  row_launch_as<MODE, T, W, false>(grid, s, x, u, M, K, eps, xq, xs, xrs, xf, n_cu);
 }
 
-hipError_t launch_row_quant(termezo_ctx* c, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
+hipError_t launch_row_quant(int n_cu, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
                             int8_t* xq, float* xs, int32_t* xrs, bool tiled, hipStream_t st) {
   const unsigned grid = (unsigned)((M + 3) / 4);
   if (xdt == TERMEZO_BF16)
     row_launch<kRowQuant, uint16_t>(grid, st, (const uint16_t*)x, (const uint16_t*)nullptr, M, K, 0.0f,
-                                    xq, xs, xrs, (uint16_t*)nullptr, tiled, c);
+                                    xq, xs, xrs, (uint16_t*)nullptr, tiled, n_cu);
   else
     row_launch<kRowQuant, float>(grid, st, (const float*)x, (const float*)nullptr, M, K, 0.0f, xq, xs,
                                  xrs, (float*)nullptr, tiled);
@@ -2153,7 +2155,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
 #define TMZ_NORM(T, MD, W)                                                                   \
   row_launch<MD, T, W>(rowg, s, (const T*)m->h,                                              \
                        nrm ? (const T*)nrm + (int64_t)wr * d : (const T*)nullptr, M, d,      \
-                       cf.norm_eps, xq, xs, m->xrs, (T*)xf, tiled, c)
+                       cf.norm_eps, xq, xs, m->xrs, (T*)xf, tiled, c->n_cu)
     if (bf) {
       if (xf) {
         if (nrm) TMZ_NORM(uint16_t, kRowNormStore, true); else TMZ_NORM(uint16_t, kRowNormStore, false);
@@ -2197,7 +2199,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     if (bf)
       row_launch<kRowQuant, uint16_t>(rowg, s, (const uint16_t*)m->attn, (const uint16_t*)nullptr,
                                       M, dq, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, t_o,
-                                      c);
+                                      c->n_cu);
     else
       row_launch<kRowQuant, float>(rowg, s, (const float*)m->attn, (const float*)nullptr, M, dq,
                                    0.0f, m->xq, m->xs, m->xrs, (float*)nullptr, t_o);
@@ -2225,7 +2227,7 @@ termezo_status termezo_model_loss(termezo_model* m, const int32_t* tokens, int32
     if (fused)
       row_launch<kRowQuant, uint16_t>(rowg, s, (const uint16_t*)m->g, (const uint16_t*)nullptr, M,
                                       F, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, t_d,
-                                      c);
+                                      c->n_cu);
     else if (bf)
       row_launch<kRowSwiGLU, uint16_t>(rowg, s, (const uint16_t*)m->g, (const uint16_t*)m->u, M,
                                        F, 0.0f, m->xq, m->xs, m->xrs, (uint16_t*)nullptr, t_d);

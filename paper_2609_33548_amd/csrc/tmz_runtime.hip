@@ -551,9 +551,9 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
   int8_t* xq = tiled ? c->d_xqt : xq_out ? xq_out : c->d_xq;
   // the caller's outputs come from the last read of x: they may lie on its memory
   float* xs = own && xq_out ? c->d_xs : xscale_out ? xscale_out : c->d_xs;
-  TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->stream));
+  TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->stream));
   if (own && xq_out)                                  // the caller's copy, row-major
-    TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq_out, xscale_out ? xscale_out : xs,
+    TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq_out, xscale_out ? xscale_out : xs,
                                 c->d_xrs, false, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, c->d_xrs, c->d_codes + L.code_off,
                                    c->d_beta_cur + layer, M, L.d_in, L.d_out, y, y_dtype, acc_out,
@@ -591,7 +591,7 @@ termezo_status termezo_bitlinear_forward_noalloc(termezo_ctx* c, int32_t layer, 
   int8_t* xq = reinterpret_cast<int8_t*>(base);
   float* xs = reinterpret_cast<float*>(base + xq_size);
   int32_t* xrs = reinterpret_cast<int32_t*>(base + xq_size + xs_bytes);
-  TMZ_HIP(c, launch_act_quant(c, x, x_dtype, M, L.d_in, xq, xs, xrs, tiled, c->stream));
+  TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq, xs, xrs, tiled, c->stream));
   TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, xrs, c->d_codes + L.code_off, c->d_beta_cur + layer,
                                    M, L.d_in, L.d_out, y, y_dtype, nullptr, tiled, c->n_cu,
                                    c->stream));

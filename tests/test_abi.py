@@ -109,13 +109,19 @@ def test_bench_cpu_baseline_legs_are_combined_by_direction():
 
 def test_library_keeps_no_unguarded_process_wide_state():
     """Contexts may be used from different threads, one each: what a call keeps belongs to its
-    context.  The only writable static objects are the scratch array's host stand-in and the
-    per-device cache of its address, which a mutex guards."""
+    context.  The only writable static objects are the per-device cache of the scratch array's
+    address, which a mutex guards, and the row kernels' resident blocks per compute unit, atomic
+    numbers that are the same for every context."""
     import subprocess
     from paper_2609_33548_amd import termezo
     text = subprocess.run(["nm", "-C", termezo.LIB_PATH], capture_output=True, text=True, check=True).stdout
     names = [m.group(1) for m in re.finditer(r"^[0-9a-f]+ [bd] (.+)$", text, re.M)]
     assert "(anonymous namespace)::g_scratch_mu" in names      # the listing shows static objects
-    ours = [n for n in names if "tmz::" in n or "termezo" in n or "anonymous namespace" in n]
-    assert sorted(ours) == ["(anonymous namespace)::g_scratch_addr",
-                            "(anonymous namespace)::g_scratch_mu"], ours
+    # (nm leaves numbered function-local statics mangled: _ZZN3tmz...E5asked.0)
+    ours = [n for n in names if "tmz" in n or "termezo" in n or "anonymous namespace" in n]
+    asked = [n for n in ours if re.search(r"row_pf_grid.*asked", n)]
+    assert asked, names
+    assert sorted(set(ours) - set(asked)) == ["(anonymous namespace)::g_scratch_addr",
+                                              "(anonymous namespace)::g_scratch_mu"], ours
+    src = open(os.path.join(ROOT, "paper_2609_33548_amd", "csrc", "tmz_model.hip")).read()
+    assert re.findall(r"static (\S+) asked", src) == ["std::atomic<int>"]
