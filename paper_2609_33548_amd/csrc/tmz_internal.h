@@ -199,8 +199,13 @@ struct termezo_ctx {
   void* noalloc_scratch = nullptr;           // this device's address of the file-scope scratch
   int8_t* d_xq = nullptr;                    // activation-quantisation scratch (row-major)
   int64_t xq_cap = 0;
-  int8_t* d_xqt = nullptr;                   // the same in fragment order, for every layer's calls
-  int64_t xqt_cap = 0;
+  // behind the codes: x_q in fragment order for every layer's calls, and row-major x_q, scales
+  // and row sums of small calls (up to kSmallXq values, kSmallTokens tokens)
+  int8_t* d_xqt = nullptr;
+  int8_t* d_xq0 = nullptr;
+  float* d_xs0 = nullptr;
+  int32_t* d_xrs0 = nullptr;
+  int64_t small_bytes = 0;
   float* d_xs = nullptr;                     // per-token scales
   int32_t* d_xrs = nullptr;                  // per-token sums of the int8 activations
   int64_t xs_cap = 0;                        // tokens d_xs and d_xrs hold
@@ -306,6 +311,7 @@ hipError_t launch_mse(const float* y, const float* t, int64_t n, double* acc, fl
 // tile of tokens: it is allocated for rs_entries(M)).
 constexpr int64_t kRsPad = 256;
 inline int64_t rs_entries(int64_t M) { return (M + kRsPad - 1) / kRsPad * kRsPad; }
+constexpr int64_t kSmallTokens = kRsPad;
 hipError_t launch_act_quant(int n_cu, const void* x, termezo_dtype xdt, int64_t M, int64_t K,
                             int8_t* xq, float* s, int32_t* rs, bool tiled, hipStream_t st);
 // Up to kGemvMaxM tokens a GEMM may take the small-M kernel, which reads x_q in fragment order
@@ -336,6 +342,7 @@ hipError_t launch_gemm_i8(const int8_t* xq, const float* s, const int32_t* rs,
 constexpr int kGemvFusedMaxM = 16;
 constexpr int64_t kGemvFusedMaxMK = 16 * 4096;       // the most values M K that it says yes to
 bool gemv_fused_ok(int64_t M, int64_t K);
+constexpr int64_t kSmallXq = kGemvFusedMaxMK;
 hipError_t launch_gemv_fused(const void* x, termezo_dtype xdt, const uint32_t* codes,
                              const float* beta_dev, int64_t M, int64_t K, int64_t N, void* y,
                              termezo_dtype ydt, int n_cu, hipStream_t st);

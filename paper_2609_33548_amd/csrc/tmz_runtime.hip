@@ -209,7 +209,6 @@ void free_all(termezo_ctx* c) {
   dfree(c->d_loss);
   dfree(c->d_scal);
   dfree(c->d_xq);
-  dfree(c->d_xqt);
   dfree(c->d_xs);
   dfree(c->d_xrs);
   if (c->h_pin) (void)hipHostFree(c->h_pin);
@@ -298,7 +297,21 @@ termezo_status termezo_create(const termezo_layer* layers, int32_t n_layers,
   chk(dalloc(&c->d_tile_start, (size_t)c->T), "alloc");
   chk(dalloc(&c->d_tile0, n_layers), "alloc");
   chk(dalloc(&c->d_tile_act, (size_t)c->T + 1), "alloc");
-  chk(dalloc(&c->d_codes, (size_t)words), "alloc codes");
+  // The activation scratch grows with the tokens of a call, as M d_in and M, and only then: what
+  // calls need beyond that lies behind the codes from the start (x_q in fragment order, padded to
+  // whole groups and chunks; the row-major copy of a call that usually takes the fused kernel), so
+  // that after a call of the largest size no smaller one allocates or frees, which a caller that
+  // captures its calls in graphs relies on.
+  int64_t kmax = 0;
+  for (const LayerHost& L : c->layers) kmax = std::max(kmax, L.d_in);
+  const int64_t code_bytes = (words * 4 + 255) / 256 * 256;
+  const int64_t xqt_bytes = std::min(xq_bytes(kGemvMaxM, kmax), kTiledXqMax);
+  c->small_bytes = xqt_bytes + kSmallXq + 8 * kSmallTokens;
+  chk(dalloc(&c->d_codes, (size_t)((code_bytes + c->small_bytes) / 4)), "alloc codes");
+  c->d_xqt = reinterpret_cast<int8_t*>(c->d_codes) + code_bytes;
+  c->d_xq0 = c->d_xqt + xqt_bytes;
+  c->d_xs0 = reinterpret_cast<float*>(c->d_xq0 + kSmallXq);
+  c->d_xrs0 = reinterpret_cast<int32_t*>(c->d_xs0 + kSmallTokens);
   chk(dalloc(&c->d_S_clean, n_layers), "alloc");
   chk(dalloc(&c->d_S_cur, n_layers), "alloc");
   chk(dalloc(&c->d_S_alt, n_layers), "alloc");
@@ -323,17 +336,6 @@ termezo_status termezo_create(const termezo_layer* layers, int32_t n_layers,
   chk(dalloc(&c->d_loss, 4), "alloc");
   chk(dalloc(&c->d_scal, kScalLen), "alloc");
   chk(hipHostMalloc((void**)&c->h_pin, 64, hipHostMallocDefault), "alloc pinned");
-  // The activation scratch grows with the tokens of a call, as M d_in and M, and only then: what
-  // calls need beyond that is here from the start (x_q in fragment order, padded to whole groups
-  // and chunks; the row-major copy of a call that usually takes the fused kernel), so that after
-  // a call of the largest size no smaller one allocates or frees, which a caller that
-  // captures its calls in graphs relies on.
-  int64_t kmax = 0;
-  for (const LayerHost& L : c->layers) kmax = std::max(kmax, L.d_in);
-  c->xqt_cap = std::min(xq_bytes(kGemvMaxM, kmax), kTiledXqMax);
-  chk(dalloc(&c->d_xqt, (size_t)c->xqt_cap), "alloc");
-  if (st == TERMEZO_OK) st = ensure_xq_capacity(c, kGemvFusedMaxMK);
-  if (st == TERMEZO_OK) st = ensure_xs_capacity(c, kGemvFusedMaxM);
   chk(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device),
       "device attribute");
   if (st == TERMEZO_OK) {
@@ -540,24 +542,30 @@ termezo_status termezo_bitlinear_forward(termezo_ctx* c, int32_t layer, const vo
                                  L.d_in, L.d_out, y, y_dtype, c->n_cu, c->stream));
     return TERMEZO_OK;
   }
-  termezo_status st = ensure_xs_capacity(c, M);       // the row sums live here in any case
-  if (st != TERMEZO_OK) return st;
   const bool tiled = bitlinear_tiled_xq(M, L.d_in, L.d_out, y, y_dtype, c->n_cu);
   const bool own = !xq_out || tiled;                  // the GEMM reads the library's copy of x_q
-  if (!xq_out) {
-    st = ensure_xq_capacity(c, M * L.d_in);
+  int8_t* xq = tiled ? c->d_xqt : xq_out ? xq_out : c->d_xq0;
+  if (!xq_out && M * L.d_in > kSmallXq) {
+    const termezo_status st = ensure_xq_capacity(c, M * L.d_in);
     if (st != TERMEZO_OK) return st;
+    if (!tiled) xq = c->d_xq;
   }
-  int8_t* xq = tiled ? c->d_xqt : xq_out ? xq_out : c->d_xq;
+  float* xs0 = c->d_xs0;
+  int32_t* xrs = c->d_xrs0;
+  if (M > kSmallTokens) {
+    const termezo_status st = ensure_xs_capacity(c, M);
+    if (st != TERMEZO_OK) return st;
+    xs0 = c->d_xs;
+    xrs = c->d_xrs;
+  }
   // the caller's outputs come from the last read of x: they may lie on its memory
-  float* xs = own && xq_out ? c->d_xs : xscale_out ? xscale_out : c->d_xs;
-  TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq, xs, c->d_xrs, tiled, c->stream));
+  float* xs = own && xq_out ? xs0 : xscale_out ? xscale_out : xs0;
+  TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq, xs, xrs, tiled, c->stream));
   if (own && xq_out)                                  // the caller's copy, row-major
-    TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq_out, xscale_out ? xscale_out : xs,
-                                c->d_xrs, false, c->stream));
-  TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, c->d_xrs, c->d_codes + L.code_off,
-                                   c->d_beta_cur + layer, M, L.d_in, L.d_out, y, y_dtype, acc_out,
-                                   tiled, c->n_cu, c->stream));
+    TMZ_HIP(c, launch_act_quant(c->n_cu, x, x_dtype, M, L.d_in, xq_out, xscale_out ? xscale_out : xs, xrs,
+                                false, c->stream));
+  TMZ_HIP(c, launch_bitlinear_gemm(xq, xs, xrs, c->d_codes + L.code_off, c->d_beta_cur + layer, M,
+                                   L.d_in, L.d_out, y, y_dtype, acc_out, tiled, c->n_cu, c->stream));
   return TERMEZO_OK;
 }
 
@@ -821,7 +829,7 @@ termezo_status termezo_memory_footprint(termezo_ctx* c, int64_t* library_bytes,
   b += 2 * (int64_t)kSumSlots * sum_row_len(c->L) * 8;             // partial sums
   if (c->mirror) b += 2 * c->wc_cap * dsz;                       // active latents (list order)
   b += (int64_t)kHistBins * 8 + (int64_t)sizeof(SelectState) + 4 * 8 + kScalLen * 4 + 4;
-  b += c->xq_cap + c->xqt_cap + (c->xs_cap + rs_entries(c->xs_cap)) * 4;   // activation-quant scratch
+  b += c->small_bytes + c->xq_cap + (c->xs_cap + rs_entries(c->xs_cap)) * 4;   // activation-quant scratch
   for (const ThetaHost& t : c->theta) b += 2 * t.n * (int64_t)dtype_size(t.dtype);
   if (c->d_codes_snap) b += c->code_words * 4 + L * 4;               // codes snapshot
   if (library_bytes) *library_bytes = b;
