@@ -57,7 +57,8 @@ PEAK_FP32_TFLOPS = 157.3         # MI355X fp32 vector, TFLOP/s
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bitlinear_gemm_traffic_2b_step.txt")
 # the GEMM kernels and every header they include (tile order, direct-to-LDS loads, unpacking)
 GEMM_SOURCES = [os.path.join(ROOT, "paper_2609_33548_amd", "csrc", f)
-                for f in ("tmz_bitlinear.hip", "tmz_device.h", "tmz_internal.h")]
+                for f in ("tmz_bitlinear.hip", "tmz_device.h", "tmz_internal.h",
+                          "tmz_tiles.h")]
 METRIC = "ZO steps/sec at 2B BitNet shape; perturb+requant GB/s; BitLinear int8 TOPS"
 ROWS = ("d1", "d2", "d3", "d4", "d5ab", "d5cd")
 
@@ -631,7 +632,7 @@ def measure_steps(torch, st, rho, eps, lr, steps, warmup, K=1, es=0, compact=Fal
                    "tokens_per_forward": c["batch"] * c["seq"], "latents": D,
                    "mask_ratio": rho, "k0": k0, "k_final": k_final, "eps": eps, "lr": lr},
         "roofline": {"bound": "mfma",
-                     "kernel": "k_gemm_i8_dma + k_gemm_i8_dma_h (BitLinear int8 x ternary "
+                     "kernel": "k_gemm_i8_dma, k_gemm_i8_dma_h, k_gemm_i8_edge (BitLinear int8 x ternary "
                                "GEMM, all four projections of a block)",
                      "achieved": gemm_tops, "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
                      "frac": gemm_tops / PEAK_INT8_TOPS,
