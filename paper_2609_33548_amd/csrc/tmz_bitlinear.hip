@@ -880,6 +880,10 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, BPC * (BM / WM) * 
 //   Codes: a lane loads 4 consecutive words of its feature (one 16-byte load) and the four
 // lane groups exchange them (a 4 x 4 transpose by lane swaps), so that group g holds word
 // 4 j + g for MFMA j.
+//   A chunk's codes are loaded while the chunk before it is worked on: waited for chunk by
+// chunk, a row of 16384 cost eight dependent trips (1 x 16384 -> 2048 on cold codes 17.3 us,
+// 16.6 so, 16.8 on the kernel that issued four chunks' loads at once).  Not with eight token groups,
+// where the loads of activations in between wait for it (96 x 16384 -> 2048 32.0 us, 32.4 so).
 // Accumulator (16 x 16, 4 values per lane): token l % 16, features
 // 4 (l / 16) .. 4 (l / 16) + 3.  Segment boundaries are multiples of 16.
 // ---------------------------------------------------------------------------
@@ -902,21 +906,32 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 #pragma unroll
   for (int tg = 0; tg < G; ++tg) acc[tg] = v4i{0, 0, 0, 0};
   const v4i* xl = reinterpret_cast<const v4i*>(xq) + lane;
-  for (int c = wid; c < nchunk; c += NW) {
-    // word 4 j + g of the chunk's 16 in cw[j] (anything past K: the activations are zero
-    // there; features past N only feed accumulators that are not stored)
-    uint32_t cw[4];
+  // word 4 j + g of a chunk's 16 in o[j] (CVEC: words 4 g + j, exchanged below; anything past K:
+  // the activations are zero there; features past N only feed accumulators that are not stored)
+  auto cload = [&](int c, uint32_t* o) __attribute__((always_inline)) {
     if (CVEC) {                                          // KW % 4 == 0: 4 words or none
       const int64_t w0 = (int64_t)c * 16 + 4 * g;
       const v4u v = *reinterpret_cast<const v4u*>(crow + (w0 < KW ? w0 : 0));
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cw[j] = v[j];
+      for (int j = 0; j < 4; ++j) o[j] = v[j];
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int64_t w = (int64_t)c * 16 + 4 * j + g;
-        cw[j] = crow[w < KW ? w : 0];
+        o[j] = crow[w < KW ? w : 0];
       }
+    }
+  };
+  constexpr bool AHEAD = G < 8;                          // codes loaded a chunk ahead
+  uint32_t nx[4] = {0u, 0u, 0u, 0u};
+  if (AHEAD && wid < nchunk) cload(wid, nx);
+  for (int c = wid; c < nchunk; c += NW) {
+    uint32_t cw[4];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) cw[j] = nx[j];
+    } else {
+      cload(c, cw);
     }
     v4i b[2][4];
     auto xload = [&](int tg, v4i* o) __attribute__((always_inline)) {
@@ -925,6 +940,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
       for (int j = 0; j < 4; ++j) o[j] = p[64 * j];
     };
     xload(0, b[0]);
+    if (AHEAD && c + NW < nchunk) cload(c + NW, nx);     // (wave-uniform)
     if (CVEC) {
       const auto a = __builtin_amdgcn_permlane32_swap(cw[0], cw[2], false, false);
       const auto e = __builtin_amdgcn_permlane32_swap(cw[1], cw[3], false, false);
