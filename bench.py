@@ -772,7 +772,7 @@ def sweep_latent(torch, termezo, synth, dev, cpu, compact_mode=True, reps=10):
         else:
             u_roof = {**_hbm(upd_gbs),
                       "note": "the draws come from the pair pass (no generator in the update); "
-                              "VALU busy about 65% (SQ counters in "
+                              "VALU busy about 30% (SQ counters in "
                               "profiles/latent_valu_2p4e9_latents.md)"}
         u = {"ratio": r, "k": k, "k_after": k_after, "latents": D, "us": t_u * 1e6,
              "algorithmic_bytes": b_u, "GB/s": upd_gbs, "roofline": u_roof}

@@ -138,6 +138,8 @@ termezo_status termezo_set_dense_requant(termezo_ctx* ctx, int32_t always_dense)
  * acc[m][n] = sum_k x_q[m][k] * c[n][k] exactly in int32;
  * y[m][n] = float(acc) * (beta' / s_m) (rounded to bf16 if y is BF16).
  * y may share memory with x: every row is quantised before y is written.
+ * The call allocates scratch when M or M * d_in exceeds every earlier call's of the context, and not
+ * otherwise: after one call of the largest size the smaller ones can be captured in a graph.
  * xq_out [M][d_in] int8, xscale_out [M] fp32 (s_m), acc_out [M][d_out] int32:
  * optional device outputs (nullable) for inspection.
  * Errors: INVALID_ARG (layer out of range, M <= 0, bad dtype, null x or y),
